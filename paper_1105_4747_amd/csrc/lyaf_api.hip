@@ -427,6 +427,11 @@ struct HostFieldPlan {
   int *h_row_of_y = nullptr, *d_row_of_y = nullptr;  // [n]: row of y, -1 if none
   int64_t h_row_of_y_cap = 0, d_row_of_y_cap = 0;
   int64_t d_rows_cap = 0, d_groups_cap = 0, d_lines_cap = 0, d_first_cap = 0;
+  // the fused mode kernel's slots (power3d only, built on its first use of the
+  // plan): 0 not built, 1 built, -1 these sight-lines do not fit
+  int slots = 0;
+  int *h_slots = nullptr, *d_slots = nullptr;
+  int64_t h_slots_cap = 0, d_slots_cap = 0;
 };
 std::map<Workspace *, HostFieldPlan> g_field_plans;
 
@@ -441,6 +446,7 @@ int ensure_field_plan(Workspace *ws, int64_t n, int64_t S, const int32_t *sx, co
   hipError_t e;
   if ((e = hipStreamSynchronize(ws->stream)) != hipSuccess) return map_err(e);
   hp.n = 0;
+  hp.slots = 0;
   // sight-lines ordered by row, then by their index
   std::vector<int32_t> order((size_t)S);
   std::iota(order.begin(), order.end(), 0);
@@ -495,6 +501,87 @@ int ensure_field_plan(Workspace *ws, int64_t n, int64_t S, const int32_t *sx, co
   hp.sx.assign(sx, sx + S);
   hp.sy.assign(sy, sy + S);
   hp.n = n;
+  return LYAF_OK;
+}
+
+// Distribution of the sight-lines over the fused mode kernel's threads: whole
+// rows, largest first, each to the thread with the fewest slots so far (the
+// rows without sight-lines take one slot, which stores their zero), threads
+// ordered by their first row so that a wave's rows end at about the same slot.
+// A row larger than the slots gets a thread of its own and spills.  Sight-lines
+// that do not fit (a crowded plane, or a row far above the others) leave
+// hp->slots = -1.  Layout of the upload, in int32: words, lines, first spill of
+// each thread, a pad to 8 bytes, the spill's (line, x) pairs.
+int ensure_power3d_slots(Workspace *ws, HostFieldPlan *hp, int n) {
+  if (hp->slots != 0) return LYAF_OK;
+  constexpr int T = kP3dModeThreads, K = kP3dModeSlots;
+  std::vector<int> order((size_t)n), load(T, 0), lead(T, -1);
+  std::vector<std::vector<int>> rows_of(T);
+  const auto first = [&](int y) { return hp->h_first[hp->h_row_of_y[y]]; };
+  const auto count = [&](int y) {
+    const int r = hp->h_row_of_y[y];
+    return r < 0 ? 0 : hp->h_first[r + 1] - hp->h_first[r];
+  };
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return count(a) > count(b); });
+  typedef std::pair<int, int> LoadOf;  // (slots used, thread): the least first
+  std::vector<LoadOf> heap;
+  for (int t = 0; t < T; ++t) heap.push_back({0, t});
+  const auto later = [](const LoadOf &a, const LoadOf &b) { return a > b; };
+  int n_spill = 0;
+  for (const int y : order) {
+    std::pop_heap(heap.begin(), heap.end(), later);
+    LoadOf &h = heap.back();
+    const int c = std::max(count(y), 1), take = std::min(c, K);
+    if (h.first + take > K || c - take > kP3dMaxSpill) {
+      hp->slots = -1;
+      return LYAF_OK;
+    }
+    rows_of[(size_t)h.second].push_back(y);
+    if (lead[(size_t)h.second] < 0) lead[(size_t)h.second] = c;
+    n_spill += c - take;
+    h.first += take;
+    std::push_heap(heap.begin(), heap.end(), later);
+  }
+  std::vector<int> threads(T);
+  std::iota(threads.begin(), threads.end(), 0);
+  std::stable_sort(threads.begin(), threads.end(),
+                   [&](int a, int b) { return lead[(size_t)a] > lead[(size_t)b]; });
+  const int64_t pad = ((int64_t)2 * K * T + T + 2) & ~int64_t(1);
+  const int64_t words = pad + 2 * (int64_t)n_spill;
+  hipError_t e;
+  if ((e = grow_host(hp->h_slots, hp->h_slots_cap, words)) != hipSuccess ||
+      (e = grow_dev(hp->d_slots, hp->d_slots_cap, words)) != hipSuccess)
+    return map_err(e);
+  int *w = hp->h_slots, *l = w + K * T, *sf = l + K * T, *sp = w + pad;
+  std::fill(w, w + K * T, 0);
+  std::fill(l, l + K * T, kP3dSlotUnused);
+  int ns = 0;
+  for (int t = 0; t < T; ++t) {
+    sf[t] = ns;
+    int k = 0;
+    for (const int y : rows_of[(size_t)threads[(size_t)t]]) {
+      const int c = count(y);
+      for (int j = 0; j < std::max(c, 1); ++j) {
+        const int2 line = c > 0 ? hp->h_lines[first(y) + j] : make_int2(kP3dSlotZero, 0);
+        if (j >= K) {  // a row of its own thread
+          sp[2 * ns] = line.x;
+          sp[2 * ns + 1] = line.y;
+          ++ns;
+          continue;
+        }
+        const bool last = j + 1 == std::min(std::max(c, 1), K);
+        w[k * T + t] = line.y | (last ? 0x800 : 0) | (y << 12);
+        l[k * T + t] = line.x;
+        ++k;
+      }
+    }
+  }
+  sf[T] = ns;
+  if ((e = hipMemcpyAsync(hp->d_slots, hp->h_slots, sizeof(int) * (size_t)words,
+                          hipMemcpyHostToDevice, ws->stream)) != hipSuccess)
+    return map_err(e);
+  hp->slots = 1;
   return LYAF_OK;
 }
 
@@ -849,17 +936,22 @@ int lyaf_flux_power_3d(const lyaf_power3d_params *pp, int64_t n_lines, const flo
   HostFieldPlan *hp = nullptr;
   if ((rc = ensure_field_plan(ws, n, n_lines, sx, sy, &hp))) return rc;
   if ((rc = ensure_twiddles(ws, st))) return rc;
+  if ((rc = ensure_power3d_slots(ws, hp, (int)n))) return rc;
+  // the fused kernel whenever the sight-lines fit its registers; a crowded
+  // plane (over about 7000 sight-lines, or one very long row) goes through D1
+  const bool modes = hp->slots > 0;
   const int64_t H = n / 2 + 1;
   const int nb = p3d_shell_bins((int)n, (int)pp->n_bins);
-  int y_grid = 0;
+  int geom_grid = 0, grid = 0;
   hipError_t e;
-  if ((e = p3d_kernel_attributes((int)n, nb, &y_grid)) != hipSuccess) return map_err(e);
-  const int C = p3d_y_columns((int)n);
-  y_grid = (int)std::min<int64_t>(y_grid, n * ((H + C - 1) / C));
-  const int64_t n_c = n_lines * H + n * (int64_t)hp->n_rows * H;  // G, D1
-  const int64_t p1d_parts = (n_lines + kP3dP1dChunk - 1) / kP3dP1dChunk;
+  if ((e = p3d_kernel_attributes((int)n, nb, modes, &geom_grid, &grid)) != hipSuccess)
+    return map_err(e);
+  // G, and D1 without the fused kernel
+  const int64_t n_c = n_lines * H + (modes ? 0 : n * (int64_t)hp->n_rows * H);
+  const int64_t p1d_parts = modes ? 0 : (n_lines + kP3dP1dChunk - 1) / kP3dP1dChunk;
   // P1d, P2d, data shells, geometry shells, P1d partials
-  const int64_t n_r = H + n * n + 2 * ((int64_t)y_grid * 2 * nb) + p1d_parts * H;
+  const int64_t n_shells = (int64_t)grid * 2 * nb;
+  const int64_t n_r = H + n * n + n_shells + (int64_t)geom_grid * 2 * nb + p1d_parts * H;
   const bool need_geom = ws->p3d_geom_n != (int)n || ws->p3d_geom_nb != nb;
   if (need_geom) ws->p3d_geom_n = ws->p3d_geom_nb = 0;
   if ((e = grow_dev(ws->p3d_c, ws->p3d_c_cap, n_c)) != hipSuccess ||
@@ -885,8 +977,16 @@ int lyaf_flux_power_3d(const lyaf_power3d_params *pp, int64_t n_lines, const flo
   a.P1d = ws->p3d_r;
   a.P2d = ws->p3d_r + H;
   a.shells = ws->p3d_r + H + n * n;
-  a.geom_part = a.shells + (int64_t)y_grid * 2 * nb;
-  a.p1d_part = a.geom_part + (int64_t)y_grid * 2 * nb;
+  a.geom_part = a.shells + n_shells;
+  a.p1d_part = a.geom_part + (int64_t)geom_grid * 2 * nb;
+  constexpr int kSlotInts = kP3dModeSlots * kP3dModeThreads;
+  const int *slots = modes ? hp->d_slots : nullptr;
+  a.slot_words = reinterpret_cast<const uint32_t *>(slots);
+  a.slot_lines = modes ? slots + kSlotInts : nullptr;
+  a.spill_first = modes ? slots + 2 * kSlotInts : nullptr;
+  a.spill = modes ? reinterpret_cast<const int2 *>(
+                        slots + ((2 * kSlotInts + kP3dModeThreads + 2) & ~1))
+                  : nullptr;
   a.geom = ws->p3d_geom;
   a.row_of_y = hp->d_row_of_y;
   a.counts = counts;
@@ -895,7 +995,8 @@ int lyaf_flux_power_3d(const lyaf_power3d_params *pp, int64_t n_lines, const flo
   a.p_box = p_box;
   a.twiddle = ws->ps_twiddle;
   if ((e = timed("flux_power_3d", st,
-                 [&] { return launch_power3d(a, y_grid, need_geom, st); })) != hipSuccess)
+                 [&] { return launch_power3d(a, modes, geom_grid, grid, need_geom, st); })) !=
+      hipSuccess)
     return map_err(e);
   ws->p3d_geom_n = (int)n;
   ws->p3d_geom_nb = nb;

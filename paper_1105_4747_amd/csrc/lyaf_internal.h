@@ -216,6 +216,14 @@ constexpr int kFieldLinesPerGroup = 8;
 constexpr int kP3dMaxN = 2048;        // pixels per sight-line = grid side
 constexpr int kP3dMaxLds = 160 * 1024;  // LDS of one workgroup
 constexpr int kP3dP1dChunk = 256;       // sight-lines per partial sum of P_1D
+// Slots of the fused mode kernel: sight-lines that each of its kP3dModeThreads
+// threads holds in registers, and the most that one of its rows reads from
+// memory besides.
+constexpr int kP3dModeThreads = 512;
+constexpr int kP3dModeSlots = 14;
+constexpr int kP3dMaxSpill = 16;
+constexpr int kP3dSlotZero = -1;        // a row without sight-lines
+constexpr int kP3dSlotUnused = -2;
 struct P3dArgs {
   const float *F;         // device [S][n] flux
   const double *w;        // device [S] weights or null (all 1)
@@ -227,6 +235,10 @@ struct P3dArgs {
   const int *row_of_y;    // device [n]: row index of y, -1 for rows without sight-lines
   const int *row_first;   // device [n_rows + 1]: the row's sight-lines in `lines`
   const int2 *lines;      // device [S]: (sight-line, x), grouped by row
+  const uint32_t *slot_words;  // device [slots][threads]: x | last of row << 11 | y << 12
+  const int *slot_lines;       // device [slots][threads]: sight-line, or a kP3dSlot* value
+  const int *spill_first;      // device [threads + 1]: each thread's run of `spill`
+  const int2 *spill;           // device: (sight-line, x) past the slots of a thread's first row
   double2 *G;             // device [S][H]: the sight-lines' transforms
   double *P1d;            // device [H]
   double *p1d_part;       // device [ceil(S / 256)][H] partial sums of P_1D
@@ -240,11 +252,13 @@ struct P3dArgs {
 };
 int p3d_shell_bins(int n, int n_bins);  // shells kept in LDS
 int p3d_y_columns(int n);               // mz per item of the y transform
-// Sets the kernels' LDS limits once per device; *y_grid: resident workgroups
-// of the y-transform kernel for grid side n and nb shells.
-hipError_t p3d_kernel_attributes(int n, int nb, int *y_grid);
+// Sets the kernels' LDS limits once per device; *geom_grid: workgroups of the
+// shells' geometry pass, *grid: workgroups that write shell sums (the fused mode
+// kernel when modes, else the y transform), for grid side n and nb shells.
+hipError_t p3d_kernel_attributes(int n, int nb, bool modes, int *geom_grid, int *grid);
 // need_geom: (re)compute the shells' counts and |m| sums into a.geom first.
-hipError_t launch_power3d(const P3dArgs &a, int y_grid, bool need_geom, hipStream_t st);
+hipError_t launch_power3d(const P3dArgs &a, bool modes, int geom_grid, int grid, bool need_geom,
+                          hipStream_t st);
 hipError_t launch_tau_adjoint(const Batch &b, const int2 *items, int64_t n_items,
                               const int64_t *item_base_dev, const float *g,
                               float *gdelta, float *gvpec, double *gT0,

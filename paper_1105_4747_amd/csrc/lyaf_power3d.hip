@@ -25,6 +25,12 @@
 //   p3d_w_kernel     one workgroup per mx: the rows' weight sums
 //                    sum_{s in row y} w_s e^{-2 pi i mx x_s / n}, placed in
 //                    their rows, transformed along y: P_2D,w(mx, .);
+//   p3d_modes_kernel the default: the sums over a row's sight-lines, the
+//                    transform along y and the shell sums, one mz at a time,
+//                    with the sight-lines' transforms in registers (no
+//                    intermediate).  The next two kernels take what does not
+//                    fit them (over about 7000 sight-lines, or a row of more
+//                    than 30), through D1 in memory;
 //   p3d_x_kernel     one workgroup per (row y in use, 64 consecutive mz):
 //                    D1(mx, y, mz) = sum_{s in row y} w_s G_s(mz) e^{-2 pi i mx x_s / n}
 //                    for every mx (a direct sum over the row's few sight-lines);
@@ -302,6 +308,224 @@ __global__ __launch_bounds__(kYThreads) void p3d_y_kernel(P3dArgs a, int lgC, in
   for (int i = threadIdx.x; i < 2 * nb; i += kYThreads) out[i] = bins[i];
 }
 
+// The modes of one mz at a time, straight from the sight-lines' transforms: no
+// D1 in memory.  Workgroup b takes an equal run of the (mz, p) sequence, p = 0 ..
+// n/2 standing for the pair mx = p, -p, so it stays on one mz (two at most) and
+// holds that mz's weighted G_s in registers, up to kModeSlots sight-lines per
+// thread.  A thread owns whole rows y (its sight-lines of a row are consecutive
+// slots, the last one flagged), so D1(+-p, y, mz) is a sum in one thread, stored
+// without atomics; the products of G with cos and sin serve both signs of mx
+// (four FMAs per sight-line for two modes).  Rows with more sight-lines than the
+// slots read the rest from memory in every step (at most kModeSpill).  The two
+// columns are transformed along y in LDS (radix 4, then 2; one element of
+// padding per 8 spreads the passes' strided writes over the banks), and the
+// modes (+-p, +-my), which share a shell, enter the LDS shell sums as one term.
+// Bound by LDS traffic (bank-conflicted table reads and pass writes: 2.8 ms of
+// LDS cycles at n = 1024 and 6250 sight-lines) and FP64 issue (2.2 ms).  There it
+// takes 4.4 ms, where the D1 form took 3.25 + 5.49 ms (and 8.6 GB of workspace).
+constexpr int kModeThreads = kP3dModeThreads;
+constexpr int kModeSlots = kP3dModeSlots;
+
+__device__ inline int fpad(int e) { return e + (e >> 3); }
+
+// One in-place Stockham pass of radix R (4 or 2) over the two columns: element
+// e of column c at buf[2 fpad(e) + c].  B butterflies per thread.
+template <int R, int B>
+__device__ inline void mode_pass(double2 *buf, const double2 *__restrict__ T, int n, int Ns) {
+  const int nq = 2 * n / R;  // butterflies of both columns
+  const int m = n / R;
+  const int step = kFftTableLen / (R * Ns);
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // addresses per pass, not held across the steps
+  double2 y[B][R];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    const int q = tid + b * kModeThreads;
+    if (q < nq) {
+      const int c = q & 1, j = q >> 1;
+      double2 x[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) x[r] = buf[2 * fpad(j + r * m) + c];
+      if (Ns > 1) {
+        const double2 w = T[(j & (Ns - 1)) * step];
+        x[1] = cmul(x[1], w);
+        if constexpr (R == 4) {
+          const double2 w2 = cmul(w, w);
+          x[2] = cmul(x[2], w2);
+          x[3] = cmul(x[3], cmul(w2, w));
+        }
+      }
+      if constexpr (R == 4) {
+        dft4(x[0], x[1], x[2], x[3], y[b][0], y[b][1], y[b][2], y[b][3]);
+      } else {
+        y[b][0] = cadd(x[0], x[1]);
+        y[b][1] = csub(x[0], x[1]);
+      }
+    }
+  }
+  lds_barrier();  // every read of this pass is done
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    const int q = tid + b * kModeThreads;
+    if (q < nq) {
+      const int c = q & 1, j = q >> 1, k = j & (Ns - 1);
+      const int base = (j - k) * R + k;
+#pragma unroll
+      for (int r = 0; r < R; ++r) buf[2 * fpad(base + r * Ns) + c] = y[b][r];
+    }
+  }
+  lds_barrier();
+}
+
+// B: butterflies of radix 4 per thread (1 up to n = 1024, 2 at 2048).
+template <int B>
+__global__ __launch_bounds__(kModeThreads) __attribute__((amdgpu_waves_per_eu(4))) void
+p3d_modes_kernel(P3dArgs a, int nb) {
+  extern __shared__ double2 lds_m[];  // two columns of fpad(n), n roots of unity, 2 nb sums
+  __shared__ double red[kModeThreads / 64];
+  const int n = a.n, H = a.H, half = n / 2, mask = n - 1;
+  double2 *buf = lds_m;
+  double2 *tw = lds_m + 2 * fpad(n);
+  double *bins = reinterpret_cast<double *>(tw + n);
+  const int tid = threadIdx.x;
+  for (int t = tid; t < n; t += kModeThreads) tw[t] = root_fwd(a.twiddle, t, n);
+  for (int i = tid; i < 2 * nb; i += kModeThreads) bins[i] = 0.0;
+  const double nn = (double)n * (double)n;
+  const double box_scale = a.L * a.L * a.L / (nn * nn * nn);
+
+  // this thread's slots: x | last-of-row flag << 11 | y << 12, and its rows' spill
+  uint32_t slot[kModeSlots];
+  double2 g[kModeSlots];
+  int used = 0;
+#pragma unroll
+  for (int k = 0; k < kModeSlots; ++k) {
+    slot[k] = a.slot_words[k * kModeThreads + tid];
+    if (a.slot_lines[k * kModeThreads + tid] != kP3dSlotUnused) used = k + 1;
+    g[k] = make_double2(0.0, 0.0);
+  }
+  for (int m = 32; m >= 1; m >>= 1) used = max(used, __shfl_xor(used, m));
+  used = __builtin_amdgcn_readfirstlane(used);  // slots that some lane of the wave uses
+  const int spill0 = a.spill_first[tid], spill1 = a.spill_first[tid + 1];
+  const bool any_spill = __any(spill1 > spill0);
+
+  const int steps = half + 1;
+  const int64_t total = (int64_t)H * steps;
+  const int first = (int)(total * blockIdx.x / gridDim.x);
+  const int last = (int)(total * (blockIdx.x + 1) / gridDim.x);
+  int mz = first / steps, p = first - mz * steps;
+  double noise = 0.0, wt = 1.0;  // P_1D(mz) + P_N, weight of mz
+  bool load = true;              // a new mz: its G_s and P_1D are still to be read
+  __syncthreads();               // the table and the cleared sums
+  for (int i = first; i < last; ++i) {
+    if (load) {
+      load = false;
+      double s2 = 0.0;  // sum over the sight-lines of |G_s|^2
+      int t = tid;
+      asm volatile("" : "+v"(t));  // addresses per mz, not held across the steps
+#pragma unroll
+      for (int k = 0; k < kModeSlots; ++k) {
+        const int line = a.slot_lines[k * kModeThreads + t];
+        if (line >= 0) {
+          const double2 v = a.G[(size_t)line * H + mz];
+          const double wl = a.w ? a.w[line] : 1.0;
+          g[k] = make_double2(wl * v.x, wl * v.y);
+          s2 = __builtin_fma(v.x, v.x, __builtin_fma(v.y, v.y, s2));
+        }
+      }
+      for (int o = spill0; o < spill1; ++o) {
+        const double2 v = a.G[(size_t)a.spill[o].x * H + mz];
+        s2 = __builtin_fma(v.x, v.x, __builtin_fma(v.y, v.y, s2));
+      }
+      for (int m = 32; m >= 1; m >>= 1) s2 += __shfl_xor(s2, m);
+      if ((tid & 63) == 0) red[tid >> 6] = s2;
+      lds_barrier();
+      s2 = red[0];
+#pragma unroll
+      for (int w = 1; w < kModeThreads / 64; ++w) s2 += red[w];
+      noise = a.L / nn * s2 / (double)a.n_lines + a.p_noise;
+      wt = (mz == 0 || mz == half) ? 1.0 : 2.0;
+    }
+    // D1(+-p, y, mz) of this thread's rows: sums of gx c, gy s, gy c, gx s with
+    // e^{-2 pi i p x / n} = c + i s
+    {
+      double sxc = 0.0, sys = 0.0, syc = 0.0, sxs = 0.0;
+      const auto add = [&](const double2 v, const double2 e) {
+        sxc = __builtin_fma(v.x, e.x, sxc);
+        sys = __builtin_fma(v.y, e.y, sys);
+        syc = __builtin_fma(v.y, e.x, syc);
+        sxs = __builtin_fma(v.x, e.y, sxs);
+      };
+      if (any_spill) {
+        for (int o = spill0; o < spill1; ++o) {
+          const int2 l = a.spill[o];  // (sight-line, x), of the thread's first row
+          const double2 v = a.G[(size_t)l.x * H + mz];
+          const double wl = a.w ? a.w[l.x] : 1.0;
+          add(make_double2(wl * v.x, wl * v.y), tw[(p * l.y) & mask]);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kModeSlots; ++k) {
+        if (k < used) {
+          uint32_t word = slot[k];
+          asm volatile("" : "+v"(word));  // decoded here, not held decoded across the steps
+          add(g[k], tw[(p * (int)(word & 0x7FFu)) & mask]);
+          if (word & 0x800u) {
+            double2 *d = buf + 2 * fpad((int)(word >> 12));
+            d[0] = make_double2(sxc - sys, sxs + syc);
+            d[1] = make_double2(sxc + sys, syc - sxs);
+            sxc = sys = syc = sxs = 0.0;
+          }
+        }
+      }
+    }
+    lds_barrier();
+    int Ns = 1;
+    while (Ns * 4 <= n) {
+      mode_pass<4, B>(buf, a.twiddle, n, Ns);
+      Ns *= 4;
+    }
+    if (Ns < n) mode_pass<2, 2 * B>(buf, a.twiddle, n, Ns);
+    const bool self_x = p == 0 || p == half;
+    const double *p2 = a.P2d + (size_t)p * n;
+    for (int my = tid; my <= half; my += kModeThreads) {
+      const int ym = (n - my) & mask;
+      const bool self_y = my == ym;
+      const double wa = p2[my], wb = p2[ym];
+      const int m2 = p * p + my * my + mz * mz;  // exact in FP32: below 2^24
+      int b = (int)__builtin_sqrtf((float)m2);
+      b -= (b * b > m2) ? 1 : 0;
+      b += ((b + 1) * (b + 1) <= m2) ? 1 : 0;
+      const double2 dp = buf[2 * fpad(my)], dm = buf[2 * fpad(my) + 1];
+      const double2 ep = buf[2 * fpad(ym)], em = buf[2 * fpad(ym) + 1];
+      const auto sq = [](const double2 v) { return __builtin_fma(v.x, v.x, v.y * v.y); };
+      double d2 = sq(dp), w2 = wa;
+      if (!self_y) {
+        d2 += sq(ep);
+        w2 += wb;
+      }
+      if (!self_x) {  // mx = -p: P_2D,w(-mx, my) = P_2D,w(mx, -my)
+        d2 += sq(dm);
+        if (!self_y) d2 += sq(em);
+        w2 *= 2.0;
+      }
+      if (b < nb) {
+        const double pbox = box_scale * d2;
+        atomicAdd(&bins[b], wt * __builtin_fma(-noise, w2, pbox));
+        atomicAdd(&bins[nb + b], wt * pbox);
+      }
+    }
+    if (++p == steps) {
+      p = 0;
+      ++mz;
+      load = true;
+    }
+    lds_barrier();  // the next step overwrites the columns
+  }
+  __syncthreads();
+  double *out = a.shells + (size_t)blockIdx.x * 2 * nb;
+  for (int i = tid; i < 2 * nb; i += kModeThreads) out[i] = bins[i];
+}
+
 // The shells' mode counts and sums of weighted |m|, summed over the
 // workgroups of the geometry pass in a fixed order.
 __global__ __launch_bounds__(kBinThreads) void p3d_geom_sum_kernel(P3dArgs a, int nb,
@@ -318,19 +542,38 @@ __global__ __launch_bounds__(kBinThreads) void p3d_geom_sum_kernel(P3dArgs a, in
   a.geom[nb + b] = t1;
 }
 
-// Sum the workgroups' shells in a fixed order; means per shell.
+// Sum the workgroups' shells in a fixed order; means per shell.  A workgroup
+// takes kBinShells consecutive shells: its threads split the partials into
+// kBinSlices strided shares (reads of consecutive shells, several in flight),
+// which are then added in order.  One thread per shell over all partials, each
+// read waiting for the last, took 80 us at 256 partials of 887 shells.
+constexpr int kBinShells = 16;
+constexpr int kBinSlices = kBinThreads / kBinShells;
 __global__ __launch_bounds__(kBinThreads) void p3d_bin_kernel(P3dArgs a, int nb, int n_parts) {
-  const int b = blockIdx.x * kBinThreads + threadIdx.x;
-  if (b >= a.n_bins) return;
-  double cnt = 0.0, km = 0.0, pt = 0.0, pb = 0.0;
+  __shared__ double sh[2][kBinSlices][kBinShells];
+  const int lane = threadIdx.x % kBinShells, slice = threadIdx.x / kBinShells;
+  const int b = blockIdx.x * kBinShells + lane;
+  double pt = 0.0, pb = 0.0;
   if (b < nb) {
-    cnt = a.geom[b];
-    km = a.geom[nb + b];
-    for (int p = 0; p < n_parts; ++p) {
+#pragma unroll 8
+    for (int p = slice; p < n_parts; p += kBinSlices) {
       const double *s = a.shells + (size_t)p * 2 * nb;
       pt += s[b];
       pb += s[nb + b];
     }
+  }
+  sh[0][slice][lane] = pt;
+  sh[1][slice][lane] = pb;
+  __syncthreads();
+  if (slice != 0 || b >= a.n_bins) return;
+  for (int k = 1; k < kBinSlices; ++k) {
+    pt += sh[0][k][lane];
+    pb += sh[1][k][lane];
+  }
+  double cnt = 0.0, km = 0.0;
+  if (b < nb) {
+    cnt = a.geom[b];
+    km = a.geom[nb + b];
   }
   const bool any = cnt > 0.0;
   a.counts[b] = cnt;
@@ -340,7 +583,11 @@ __global__ __launch_bounds__(kBinThreads) void p3d_bin_kernel(P3dArgs a, int nb,
 }
 
 bool g_attr_set[64] = {false};
-int g_resident[64] = {0};
+int g_cus[64] = {0};
+
+size_t modes_lds(int n, int nb) {
+  return sizeof(double2) * (size_t)(2 * (n + (n >> 3)) + n) + 2 * sizeof(double) * (size_t)nb;
+}
 
 }  // namespace
 
@@ -362,67 +609,81 @@ int p3d_y_columns(int n) {
   return C;
 }
 
-hipError_t p3d_kernel_attributes(int n, int nb, int *y_grid) {
+hipError_t p3d_kernel_attributes(int n, int nb, bool modes, int *geom_grid, int *grid) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (!g_attr_set[dev]) {
-    if ((e = hipFuncSetAttribute((const void *)p3d_y_kernel<false>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 kP3dMaxLds)) != hipSuccess ||
-        (e = hipFuncSetAttribute((const void *)p3d_y_kernel<true>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 kP3dMaxLds)) != hipSuccess)
-      return e;
-    if ((e = hipFuncSetAttribute((const void *)p3d_w_kernel,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)(sizeof(double2) * kP3dMaxN))) != hipSuccess)
-      return e;
+    const void *big[] = {(const void *)p3d_y_kernel<false>, (const void *)p3d_y_kernel<true>,
+                         (const void *)p3d_modes_kernel<1>, (const void *)p3d_modes_kernel<2>,
+                         (const void *)p3d_w_kernel};
+    for (const void *f : big)
+      if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   kP3dMaxLds - 1024)) != hipSuccess)
+        return e;
     hipDeviceProp_t prop;
     if ((e = hipGetDeviceProperties(&prop, dev)) != hipSuccess) return e;
-    g_resident[dev] = prop.multiProcessorCount;
+    g_cus[dev] = prop.multiProcessorCount;
     g_attr_set[dev] = true;
   }
   const int C = p3d_y_columns(n);
-  const size_t lds = sizeof(double2) * (size_t)n * C + 2 * sizeof(double) * (size_t)nb;
+  const int items = n * ((n / 2 + C) / C);  // n ceil(H / C), H = n/2 + 1
   int per_cu = 0;
+  const size_t lds = sizeof(double2) * (size_t)n * C + 2 * sizeof(double) * (size_t)nb;
   if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)p3d_y_kernel<false>,
                                                         kYThreads, lds)) != hipSuccess)
     return e;
-  *y_grid = std::max(1, per_cu) * g_resident[dev];
+  *geom_grid = std::min(std::max(1, per_cu) * g_cus[dev], items);
+  *grid = *geom_grid;
+  if (modes) {
+    const void *f = n > 1024 ? (const void *)p3d_modes_kernel<2> : (const void *)p3d_modes_kernel<1>;
+    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, kModeThreads,
+                                                          modes_lds(n, nb))) != hipSuccess)
+      return e;
+    const int64_t steps = (int64_t)(n / 2 + 1) * (n / 2 + 1);
+    *grid = (int)std::min<int64_t>((int64_t)std::max(1, per_cu) * g_cus[dev], steps);
+  }
   return hipSuccess;
 }
 
-hipError_t launch_power3d(const P3dArgs &a, int y_grid, bool need_geom, hipStream_t st) {
+hipError_t launch_power3d(const P3dArgs &a, bool modes, int geom_grid, int grid, bool need_geom,
+                          hipStream_t st) {
   const int n = a.n;
   const int C = p3d_y_columns(n);
   int lgC = 0;
   while ((1 << lgC) < C) ++lgC;
   const int n_chunks = (a.H + C - 1) / C;
   const int nb = p3d_shell_bins(n, a.n_bins);
-  const int grid = std::min(y_grid, n * n_chunks);
   if (need_geom) {  // once per grid and shell count: counts and mean |k|
-    hipLaunchKernelGGL(p3d_y_kernel<true>, dim3(grid), dim3(kYThreads),
+    hipLaunchKernelGGL(p3d_y_kernel<true>, dim3(geom_grid), dim3(kYThreads),
                        2 * sizeof(double) * (size_t)nb, st, a, lgC, n_chunks, nb);
     hipLaunchKernelGGL(p3d_geom_sum_kernel, dim3((nb + kBinThreads - 1) / kBinThreads),
-                       dim3(kBinThreads), 0, st, a, nb, grid);
+                       dim3(kBinThreads), 0, st, a, nb, geom_grid);
   }
   hipLaunchKernelGGL(p3d_line_kernel, dim3(a.n_lines), dim3(kLineThreads),
                      sizeof(double2) * (size_t)(n / 2), st, a);
-  const int p1d_kzb = (a.H + 63) / 64;
-  const int p1d_chunks = (a.n_lines + kP1dChunk - 1) / kP1dChunk;
-  hipLaunchKernelGGL(p3d_p1d_kernel, dim3(p1d_kzb * p1d_chunks), dim3(256), 0, st, a, p1d_kzb);
-  hipLaunchKernelGGL(p3d_p1d_sum_kernel, dim3((a.H + 255) / 256), dim3(256), 0, st, a,
-                     p1d_chunks);
   hipLaunchKernelGGL(p3d_w_kernel, dim3(n), dim3(kLineThreads), sizeof(double2) * (size_t)n,
                      st, a);
-  const int n_kzb = (a.H + 63) / 64;
-  hipLaunchKernelGGL(p3d_x_kernel, dim3(a.n_rows * n_kzb), dim3(kXThreads), 0, st, a, n_kzb);
-  hipLaunchKernelGGL(p3d_y_kernel<false>, dim3(grid), dim3(kYThreads),
-                     sizeof(double2) * (size_t)(n << lgC) + 2 * sizeof(double) * (size_t)nb,
-                     st, a, lgC, n_chunks, nb);
-  hipLaunchKernelGGL(p3d_bin_kernel, dim3((a.n_bins + kBinThreads - 1) / kBinThreads),
+  if (modes) {
+    const size_t lds = modes_lds(n, nb);
+    if (n > 1024)
+      hipLaunchKernelGGL(p3d_modes_kernel<2>, dim3(grid), dim3(kModeThreads), lds, st, a, nb);
+    else
+      hipLaunchKernelGGL(p3d_modes_kernel<1>, dim3(grid), dim3(kModeThreads), lds, st, a, nb);
+  } else {
+    const int p1d_kzb = (a.H + 63) / 64;
+    const int p1d_chunks = (a.n_lines + kP1dChunk - 1) / kP1dChunk;
+    hipLaunchKernelGGL(p3d_p1d_kernel, dim3(p1d_kzb * p1d_chunks), dim3(256), 0, st, a, p1d_kzb);
+    hipLaunchKernelGGL(p3d_p1d_sum_kernel, dim3((a.H + 255) / 256), dim3(256), 0, st, a,
+                       p1d_chunks);
+    const int n_kzb = (a.H + 63) / 64;
+    hipLaunchKernelGGL(p3d_x_kernel, dim3(a.n_rows * n_kzb), dim3(kXThreads), 0, st, a, n_kzb);
+    hipLaunchKernelGGL(p3d_y_kernel<false>, dim3(grid), dim3(kYThreads),
+                       sizeof(double2) * (size_t)(n << lgC) + 2 * sizeof(double) * (size_t)nb,
+                       st, a, lgC, n_chunks, nb);
+  }
+  hipLaunchKernelGGL(p3d_bin_kernel, dim3((a.n_bins + kBinShells - 1) / kBinShells),
                      dim3(kBinThreads), 0, st, a, nb, grid);
   return hipGetLastError();
 }

@@ -141,3 +141,36 @@ def test_full_size_workload_properties():
           f"vs {want_true:.6e}", flush=True)
     assert abs(tot_box / want_box - 1) <= 1e-11
     assert abs(tot_true - want_true) <= 1e-10 * tot_box
+
+
+@pytest.mark.parametrize("rows", [(13,), (14,), (15, 1, 14), (30, 30, 2), (31,), (14,) * 65,
+                                  (112,) * 64], ids=lambda r: f"{len(r)}x{max(r)}")
+def test_row_sizes_around_the_register_slots(rows):
+    """Rows at and past the 14 sight-lines that a thread of the fused kernel
+    holds, at and past the 16 more that it reads from memory (31 in one row, and
+    a plane of 7168, go through the stored intermediate), with weights."""
+    n = 128 if len(rows) > 64 else 64
+    rng = np.random.default_rng(sum(rows))
+    sy = np.repeat(rng.permutation(n)[:len(rows)], rows)
+    _check(n, 0, seed=len(rows), weights=True, p_noise=0.3,
+           cols=(rng.integers(0, n, sy.size), sy))
+
+
+@pytest.mark.parametrize("S", [40, 9000])
+def test_largest_grid_totals(S):
+    """n = 2048 (two butterflies per thread; 9000 sight-lines do not fit the
+    fused kernel's slots): Parseval for the total box power and the total of
+    P_true, to the bars of the 1024 workload."""
+    n, L = 2048, 500.0
+    rng = np.random.default_rng(S)
+    c = rng.choice(n * n, S, replace=False)
+    F = _flux(S, n, S)
+    nb = int(math.floor(math.sqrt(3) * n / 2)) + 1
+    print(f"power3d: n={n} S={S}", flush=True)
+    cnt, _, pt, pb = _run(F, 0.7, c // n, c % n, n, L, nb, p_noise=0.4)
+    assert cnt.sum() == n ** 3
+    delta = F.astype(np.float64) / 0.7 - 1.0
+    want = L ** 3 / n ** 3 * float(np.sum(delta * delta))
+    tot = float(np.sum(cnt * pb))
+    assert abs(tot / want - 1) <= 1e-11
+    assert abs(float(np.sum(cnt * pt)) + L ** 2 * S * 0.4 / n) <= 1e-10 * tot
