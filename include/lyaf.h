@@ -313,7 +313,9 @@ typedef struct {
  *   delta_b, v_z: DEVICE float [n_lines][n], written (sight-line s at s*n).
  * The library keeps a workspace of 16 R n (n/2+1) + 32 n_lines (n/2+1) bytes,
  * R the number of distinct sy values (about 8.6 GB at n = 1024 with every
- * row in use).  Errors: EINVAL (host checks above), EDEVICE, ENOMEM. */
+ * row in use), or on grids of 512 and of 1024 (from 320 sight-lines on) with at
+ * most 6656 sight-lines about 213,000 (n/2 + 1) + 27,000 n bytes (0.14 GB).
+ * Errors: EINVAL (host checks above), EDEVICE, ENOMEM. */
 int lyaf_field_skewers(const lyaf_field_params *fp, const void *modes, const double *pk,
                        int64_t n_lines, const int32_t *sx, const int32_t *sy, float *delta_b,
                        float *v_z, void *stream);
@@ -423,7 +425,8 @@ int lyaf_status_read(void *stream, uint32_t *device_status);
  *                the kernel); "tau_plain" the plain full-sum kernels
  *   "normalise", "normalise_backward", "tau_adjoint", "instrument",
  *   "instrument_backward", "flux_pdf", "flux_power",
- *   "field_ky", "field_kx", "field_z" (the three kernels of lyaf_field_skewers),
+ *   "field_planes", "field_z" (lyaf_field_skewers on grids of 512 and 1024),
+ *   "field_ky", "field_kx", "field_z" (its three kernels otherwise),
  *   "flux_power_3d" (every kernel of lyaf_flux_power_3d).
  * Launches under stream capture (plans, caller graphs) are not recorded, and
  * recording stops after 65536 launches.  lyaf_kernel_timing(0) stops and

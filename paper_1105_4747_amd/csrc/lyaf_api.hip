@@ -427,11 +427,12 @@ struct HostFieldPlan {
   int *h_row_of_y = nullptr, *d_row_of_y = nullptr;  // [n]: row of y, -1 if none
   int64_t h_row_of_y_cap = 0, d_row_of_y_cap = 0;
   int64_t d_rows_cap = 0, d_groups_cap = 0, d_lines_cap = 0, d_first_cap = 0;
-  // the fused mode kernel's slots (power3d only, built on its first use of the
-  // plan): 0 not built, 1 built, -1 these sight-lines do not fit
-  int slots = 0;
-  int *h_slots = nullptr, *d_slots = nullptr;
-  int64_t h_slots_cap = 0, d_slots_cap = 0;
+  // the fused kernels' slots, [0] of the 3D power's mode kernel, [1] of the field
+  // planes, each built on its first use of the plan: 0 not built, 1 built, -1
+  // these sight-lines do not fit
+  int slots[2] = {0, 0};
+  int *h_slots[2] = {nullptr, nullptr}, *d_slots[2] = {nullptr, nullptr};
+  int64_t h_slots_cap[2] = {0, 0}, d_slots_cap[2] = {0, 0};
 };
 std::map<Workspace *, HostFieldPlan> g_field_plans;
 
@@ -446,7 +447,7 @@ int ensure_field_plan(Workspace *ws, int64_t n, int64_t S, const int32_t *sx, co
   hipError_t e;
   if ((e = hipStreamSynchronize(ws->stream)) != hipSuccess) return map_err(e);
   hp.n = 0;
-  hp.slots = 0;
+  hp.slots[0] = hp.slots[1] = 0;
   // sight-lines ordered by row, then by their index
   std::vector<int32_t> order((size_t)S);
   std::iota(order.begin(), order.end(), 0);
@@ -504,24 +505,37 @@ int ensure_field_plan(Workspace *ws, int64_t n, int64_t S, const int32_t *sx, co
   return LYAF_OK;
 }
 
-// Distribution of the sight-lines over the fused mode kernel's threads: whole
-// rows, largest first, each to the thread with the fewest slots so far (the
-// rows without sight-lines take one slot, which stores their zero), threads
-// ordered by their first row so that a wave's rows end at about the same slot.
-// A row larger than the slots gets a thread of its own and spills.  Sight-lines
-// that do not fit (a crowded plane, or a row far above the others) leave
-// hp->slots = -1.  Layout of the upload, in int32: words, lines, first spill of
-// each thread, a pad to 8 bytes, the spill's (line, x) pairs.
-int ensure_power3d_slots(Workspace *ws, HostFieldPlan *hp, int n) {
-  if (hp->slots != 0) return LYAF_OK;
-  constexpr int T = kP3dModeThreads, K = kP3dModeSlots;
-  std::vector<int> order((size_t)n), load(T, 0), lead(T, -1);
-  std::vector<std::vector<int>> rows_of(T);
+// Distribution of the sight-lines over the threads of a fused kernel, whose
+// threads hold K of them each: rows, largest first, each to the thread with the
+// fewest slots so far; threads ordered by their first row, so that a wave's
+// rows end at about the same slot.
+//   3D power (planes = false): a row stays whole (its sum is one thread's), a
+//   row larger than K gets a thread of its own and spills, and the rows without
+//   sight-lines take one slot, which stores their zero.  A crowded plane, or a
+//   row far above the others, does not fit: slots[0] = -1.
+//   field planes (planes = true): the sums are per sight-line, so a row is cut
+//   where its thread is full, at the average that all threads get.
+// Layout of the upload, in int32: words (x | last of row << 11 | y << 12),
+// sight-lines, first spill of each thread, a pad to 8 bytes, the spill's
+// (sight-line, x) pairs.
+int ensure_slots(Workspace *ws, HostFieldPlan *hp, int n, bool planes) {
+  const int kind = planes ? 1 : 0;
+  if (hp->slots[kind] != 0) return LYAF_OK;
+  static_assert(kP3dModeThreads == kFieldThreads, "one table layout");
+  constexpr int T = kFieldThreads;
+  const int K = planes ? kFieldSlots : kP3dModeSlots;
+  const int S = (int)hp->sx.size();
+  const int cap = planes ? std::min(K, (S + T - 1) / T) : K;
+  struct Piece {
+    int y, from, count, slots;
+  };
   const auto first = [&](int y) { return hp->h_first[hp->h_row_of_y[y]]; };
   const auto count = [&](int y) {
     const int r = hp->h_row_of_y[y];
     return r < 0 ? 0 : hp->h_first[r + 1] - hp->h_first[r];
   };
+  std::vector<int> order((size_t)n), lead(T, 0);
+  std::vector<std::vector<Piece>> pieces(T);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return count(a) > count(b); });
   typedef std::pair<int, int> LoadOf;  // (slots used, thread): the least first
@@ -530,18 +544,25 @@ int ensure_power3d_slots(Workspace *ws, HostFieldPlan *hp, int n) {
   const auto later = [](const LoadOf &a, const LoadOf &b) { return a > b; };
   int n_spill = 0;
   for (const int y : order) {
-    std::pop_heap(heap.begin(), heap.end(), later);
-    LoadOf &h = heap.back();
-    const int c = std::max(count(y), 1), take = std::min(c, K);
-    if (h.first + take > K || c - take > kP3dMaxSpill) {
-      hp->slots = -1;
-      return LYAF_OK;
+    const int c = count(y);
+    if (planes && c == 0) break;
+    for (int from = 0; from < std::max(c, 1);) {
+      std::pop_heap(heap.begin(), heap.end(), later);
+      LoadOf &h = heap.back();
+      const int room = cap - h.first;
+      int take = std::min(std::max(c, 1) - from, planes ? room : K);
+      if (take > room || take <= 0 || (!planes && c - take > kP3dMaxSpill)) {
+        hp->slots[kind] = -1;
+        return LYAF_OK;
+      }
+      const int whole = planes ? take : c;  // sight-lines of this piece, spill included
+      pieces[(size_t)h.second].push_back({y, from, whole, take});
+      if (h.first == 0) lead[(size_t)h.second] = take;
+      n_spill += std::max(whole - take, 0);
+      h.first += take;
+      from += std::max(whole, 1);
+      std::push_heap(heap.begin(), heap.end(), later);
     }
-    rows_of[(size_t)h.second].push_back(y);
-    if (lead[(size_t)h.second] < 0) lead[(size_t)h.second] = c;
-    n_spill += c - take;
-    h.first += take;
-    std::push_heap(heap.begin(), heap.end(), later);
   }
   std::vector<int> threads(T);
   std::iota(threads.begin(), threads.end(), 0);
@@ -550,38 +571,37 @@ int ensure_power3d_slots(Workspace *ws, HostFieldPlan *hp, int n) {
   const int64_t pad = ((int64_t)2 * K * T + T + 2) & ~int64_t(1);
   const int64_t words = pad + 2 * (int64_t)n_spill;
   hipError_t e;
-  if ((e = grow_host(hp->h_slots, hp->h_slots_cap, words)) != hipSuccess ||
-      (e = grow_dev(hp->d_slots, hp->d_slots_cap, words)) != hipSuccess)
+  if ((e = grow_host(hp->h_slots[kind], hp->h_slots_cap[kind], words)) != hipSuccess ||
+      (e = grow_dev(hp->d_slots[kind], hp->d_slots_cap[kind], words)) != hipSuccess)
     return map_err(e);
-  int *w = hp->h_slots, *l = w + K * T, *sf = l + K * T, *sp = w + pad;
+  int *w = hp->h_slots[kind], *l = w + K * T, *sf = l + K * T, *sp = w + pad;
   std::fill(w, w + K * T, 0);
-  std::fill(l, l + K * T, kP3dSlotUnused);
+  std::fill(l, l + K * T, kSlotUnused);
   int ns = 0;
   for (int t = 0; t < T; ++t) {
     sf[t] = ns;
     int k = 0;
-    for (const int y : rows_of[(size_t)threads[(size_t)t]]) {
-      const int c = count(y);
-      for (int j = 0; j < std::max(c, 1); ++j) {
-        const int2 line = c > 0 ? hp->h_lines[first(y) + j] : make_int2(kP3dSlotZero, 0);
-        if (j >= K) {  // a row of its own thread
+    for (const Piece &p : pieces[(size_t)threads[(size_t)t]]) {
+      for (int j = 0; j < std::max(p.count, 1); ++j) {
+        const int2 line =
+            p.count > 0 ? hp->h_lines[first(p.y) + p.from + j] : make_int2(kP3dSlotZero, 0);
+        if (j >= p.slots) {
           sp[2 * ns] = line.x;
           sp[2 * ns + 1] = line.y;
           ++ns;
           continue;
         }
-        const bool last = j + 1 == std::min(std::max(c, 1), K);
-        w[k * T + t] = line.y | (last ? 0x800 : 0) | (y << 12);
+        w[k * T + t] = line.y | (j + 1 == p.slots ? 0x800 : 0) | (p.y << 12);
         l[k * T + t] = line.x;
         ++k;
       }
     }
   }
   sf[T] = ns;
-  if ((e = hipMemcpyAsync(hp->d_slots, hp->h_slots, sizeof(int) * (size_t)words,
+  if ((e = hipMemcpyAsync(hp->d_slots[kind], hp->h_slots[kind], sizeof(int) * (size_t)words,
                           hipMemcpyHostToDevice, ws->stream)) != hipSuccess)
     return map_err(e);
-  hp->slots = 1;
+  hp->slots[kind] = 1;
   return LYAF_OK;
 }
 
@@ -875,12 +895,24 @@ int lyaf_field_skewers(const lyaf_field_params *fp, const void *modes, const dou
   if ((rc = ensure_twiddles(ws, st))) return rc;
   const int64_t H = N / 2 + 1;
   hipError_t e;
-  int ky_resident = 0;
-  if ((e = field_kernel_attributes(&ky_resident)) != hipSuccess ||
-      (e = grow_dev(ws->field_T, ws->field_T_cap, 2 * (int64_t)hp->n_rows * N * H)) !=
-          hipSuccess ||
-      (e = grow_dev(ws->field_C, ws->field_C_cap, 2 * n_lines * H)) != hipSuccess)
-    return map_err(e);
+  int resident = 0;
+  bool planes = field_planes_fit((int)N, n_lines);
+  if (planes) {
+    if ((rc = ensure_slots(ws, hp, (int)N, true))) return rc;
+    planes = hp->slots[1] > 0;
+  }
+  const int64_t n_planes = planes ? H * 2 * kFieldSlotSum : 0;
+  if (planes) {
+    if ((e = field_planes_attributes((int)N, &resident)) != hipSuccess) return map_err(e);
+    e = grow_dev(ws->field_C, ws->field_C_cap,
+                 n_planes + (int64_t)field_last_parts((int)N, resident) * 2 * kFieldSlotSum);
+  } else {
+    if ((e = field_kernel_attributes(&resident)) == hipSuccess &&
+        (e = grow_dev(ws->field_T, ws->field_T_cap, 2 * (int64_t)hp->n_rows * N * H)) ==
+            hipSuccess)
+      e = grow_dev(ws->field_C, ws->field_C_cap, 2 * n_lines * H);
+  }
+  if (e != hipSuccess) return map_err(e);
   FieldArgs a;
   a.modes = static_cast<const float2 *>(modes);
   a.pk = pk;
@@ -898,14 +930,31 @@ int lyaf_field_skewers(const lyaf_field_params *fp, const void *modes, const dou
   a.rows = hp->d_rows;
   a.groups = hp->d_groups;
   a.lines = hp->d_lines;
-  a.Tb = ws->field_T;
-  a.Tv = ws->field_T + (int64_t)hp->n_rows * N * H;
-  a.Cb = ws->field_C;
-  a.Cv = ws->field_C + n_lines * H;
+  a.Tb = a.Tv = nullptr;
+  a.Cb = a.Cv = a.planes = a.last_parts = nullptr;
+  a.slot_words = nullptr;
+  a.slot_lines = nullptr;
+  if (planes) {
+    a.slot_words = reinterpret_cast<const uint32_t *>(hp->d_slots[1]);
+    a.slot_lines = hp->d_slots[1] + kFieldSlotSum;
+    a.planes = ws->field_C;
+    a.last_parts = ws->field_C + n_planes;
+  } else {
+    a.Tb = ws->field_T;
+    a.Tv = ws->field_T + (int64_t)hp->n_rows * N * H;
+    a.Cb = ws->field_C;
+    a.Cv = ws->field_C + n_lines * H;
+  }
   a.delta_b = delta_b;
   a.v_z = v_z;
   a.twiddle = ws->ps_twiddle;
-  if ((e = timed("field_ky", st, [&] { return launch_field_ky(a, ky_resident, st); })) !=
+  if (planes) {
+    if ((e = timed("field_planes", st, [&] { return launch_field_planes(a, resident, st); })) !=
+        hipSuccess)
+      return map_err(e);
+    return map_err(timed("field_z", st, [&] { return launch_field_z_planes(a, st); }));
+  }
+  if ((e = timed("field_ky", st, [&] { return launch_field_ky(a, resident, st); })) !=
           hipSuccess ||
       (e = timed("field_kx", st, [&] { return launch_field_kx(a, hp->n_groups, st); })) !=
           hipSuccess)
@@ -936,10 +985,10 @@ int lyaf_flux_power_3d(const lyaf_power3d_params *pp, int64_t n_lines, const flo
   HostFieldPlan *hp = nullptr;
   if ((rc = ensure_field_plan(ws, n, n_lines, sx, sy, &hp))) return rc;
   if ((rc = ensure_twiddles(ws, st))) return rc;
-  if ((rc = ensure_power3d_slots(ws, hp, (int)n))) return rc;
+  if ((rc = ensure_slots(ws, hp, (int)n, false))) return rc;
   // the fused kernel whenever the sight-lines fit its registers; a crowded
   // plane (over about 7000 sight-lines, or one very long row) goes through D1
-  const bool modes = hp->slots > 0;
+  const bool modes = hp->slots[0] > 0;
   const int64_t H = n / 2 + 1;
   const int nb = p3d_shell_bins((int)n, (int)pp->n_bins);
   int geom_grid = 0, grid = 0;
@@ -980,7 +1029,7 @@ int lyaf_flux_power_3d(const lyaf_power3d_params *pp, int64_t n_lines, const flo
   a.geom_part = a.shells + n_shells;
   a.p1d_part = a.geom_part + (int64_t)geom_grid * 2 * nb;
   constexpr int kSlotInts = kP3dModeSlots * kP3dModeThreads;
-  const int *slots = modes ? hp->d_slots : nullptr;
+  const int *slots = modes ? hp->d_slots[0] : nullptr;
   a.slot_words = reinterpret_cast<const uint32_t *>(slots);
   a.slot_lines = modes ? slots + kSlotInts : nullptr;
   a.spill_first = modes ? slots + 2 * kSlotInts : nullptr;

@@ -153,6 +153,147 @@ __device__ void fft_pass(V *buf, const double2 *__restrict__ T, int N, int lgC, 
   lds_barrier();
 }
 
+// ---------------------------------------------------------------------------
+// One transform of N = 64 E points (E = 8 or 16) per wave, without workgroup
+// barriers: radix E in each lane's registers, then the 64-point transforms as
+// two radix-8 steps, with two exchanges through the wave's own N elements of LDS
+// (a batch in passes of radix 8, 8, 8, 2 at N = 1024 exchanges four times, each
+// between two barriers).  Lane l holds x[r] = element l + 64 r on entry.  The
+// result, element k = k1 + E (k2 + 8 k3), is left in LDS at wave_fft_pos(k); the
+// XOR of the indices keeps every access to distinct banks.  Twiddles come from
+// LDS, one rounding of the FP64 table each: tw1[(k1 - 1) 64 + l] = e^{-2 pi i l
+// k1/N}, tw2[(k2 - 1) 8 + a] = e^{-2 pi i a k2/64}.
+__device__ inline int wave_fft_at(int k1, int b, int a) {
+  return (k1 << 6) + ((b ^ (k1 & 7)) << 3) + (a ^ b);
+}
+template <int E>
+__device__ inline int wave_fft_pos(int k) {
+  return wave_fft_at(k & (E - 1), (k / E) & 7, (k / E) >> 3);
+}
+template <int E>
+constexpr int kWaveTw1 = (E - 1) * 64;
+constexpr int kWaveTw2 = 7 * 8;
+
+// The entries t of both tables for a thread of the workgroup that fills them.
+template <int E, typename V>
+__device__ inline void wave_fft_tables(V *tw1, V *tw2, const double2 *__restrict__ T, int tid,
+                                       int threads) {
+  const auto root = [&](int t, int n) {  // e^{-2 pi i t / n}, 0 <= t < n
+    const int u = t * (kFftTableLen / n);
+    return twiddle_as<V>(u < kFftTableLen / 2 ? T[u]
+                                              : make_double2(-T[u - kFftTableLen / 2].x,
+                                                             -T[u - kFftTableLen / 2].y));
+  };
+  for (int i = tid; i < kWaveTw1<E>; i += threads)
+    tw1[i] = root((i & 63) * ((i >> 6) + 1), 64 * E);  // below 64 (E - 1) < 64 E
+  for (int i = tid; i < kWaveTw2; i += threads) tw2[i] = root((i & 7) * ((i >> 3) + 1), 64);
+}
+
+// Length-8 DFT in registers (as the radix-8 pass).
+template <typename V>
+__device__ inline void dft8(V (&x)[8]) {
+  using S = decltype(V{}.x);
+  constexpr S h = (S)0.70710678118654752440;  // sqrt(1/2)
+  const V b0 = csub(x[0], x[4]);
+  const V t1 = csub(x[1], x[5]);
+  const V b2 = mul_mi(csub(x[2], x[6]));
+  const V t3 = csub(x[3], x[7]);
+  V b1, b3;
+  b1.x = h * (t1.x + t1.y);
+  b1.y = h * (t1.y - t1.x);
+  b3.x = h * (t3.y - t3.x);
+  b3.y = -h * (t3.x + t3.y);
+  V y[8];
+  dft4(cadd(x[0], x[4]), cadd(x[1], x[5]), cadd(x[2], x[6]), cadd(x[3], x[7]), y[0], y[2], y[4],
+       y[6]);
+  dft4(b0, b1, b2, b3, y[1], y[3], y[5], y[7]);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) x[k] = y[k];
+}
+
+// Length-16 DFT in registers: length-4 DFTs over r = j, j + 4, j + 8, j + 12,
+// twiddles e^{-2 pi i j k/16}, length-4 DFTs over j.
+template <typename V>
+__device__ inline void dft16(V (&x)[16]) {
+  using S = decltype(V{}.x);
+  constexpr S c1 = (S)0.92387953251128675613, s1 = (S)0.38268343236508977173;  // pi/8
+  constexpr S h = (S)0.70710678118654752440;
+  V t[4][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    dft4(x[j], x[j + 4], x[j + 8], x[j + 12], t[j][0], t[j][1], t[j][2], t[j][3]);
+  const auto rot = [](V a, S c, S s) {  // a (c - i s)
+    V o;
+    o.x = a.x * c + a.y * s;
+    o.y = a.y * c - a.x * s;
+    return o;
+  };
+  const auto rot8 = [&](V a) {  // a e^{-i pi/4}
+    V o;
+    o.x = h * (a.x + a.y);
+    o.y = h * (a.y - a.x);
+    return o;
+  };
+  t[1][1] = rot(t[1][1], c1, s1);
+  t[1][2] = rot8(t[1][2]);
+  t[1][3] = rot(t[1][3], s1, c1);
+  t[2][1] = rot8(t[2][1]);
+  t[2][2] = mul_mi(t[2][2]);
+  t[2][3] = mul_mi(rot8(t[2][3]));
+  t[3][1] = rot(t[3][1], s1, c1);
+  t[3][2] = mul_mi(rot8(t[3][2]));
+  t[3][3] = rot(t[3][3], -c1, -s1);
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    dft4(t[0][k], t[1][k], t[2][k], t[3][k], x[k], x[k + 4], x[k + 8], x[k + 12]);
+}
+
+template <int E, typename V>
+__device__ inline void wave_fft(V (&x)[E], V *col, const V *tw1, const V *tw2, int lane) {
+  static_assert(E == 8 || E == 16, "64 E points");
+  if constexpr (E == 16)
+    dft16(x);
+  else
+    dft8(x);
+  const int lo = lane & 7, hi = lane >> 3;
+  {
+    const int in = lo ^ hi;  // position of a = lo within the eight of b = hi
+#pragma unroll
+    for (int k1 = 0; k1 < E; ++k1) {
+      col[(k1 << 6) + ((hi ^ (k1 & 7)) << 3) + in] =
+          k1 == 0 ? x[0] : cmul(x[k1], tw1[(k1 - 1) * 64 + lane]);
+      if ((k1 & 3) == 3) asm volatile("" ::: "memory");  // four twiddles in flight
+    }
+  }
+  // LDS accesses of one wave are performed in order: the reads below see the
+  // other lanes' writes without a wait; the compiler must keep that order
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int u = 0; u < E / 8; ++u) {  // radix 8 over b: lane (a = lo, k1 = hi + 8u)
+    V *c = col + ((hi + 8 * u) << 6);
+    V y[8];
+#pragma unroll
+    for (int b = 0; b < 8; ++b) y[b] = c[((b ^ hi) << 3) + (lo ^ b)];
+    dft8(y);
+#pragma unroll
+    for (int k2 = 0; k2 < 8; ++k2)
+      c[((k2 ^ hi) << 3) + (lo ^ k2)] = k2 == 0 ? y[0] : cmul(y[k2], tw2[(k2 - 1) * 8 + lo]);
+    asm volatile("" ::: "memory");  // one butterfly's elements at a time
+  }
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int u = 0; u < E / 8; ++u) {  // radix 8 over a: lane (k2 = lo, k1 = hi + 8u)
+    V *c = col + ((hi + 8 * u) << 6) + ((lo ^ hi) << 3);
+    V y[8];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) y[a] = c[a ^ lo];
+    dft8(y);
+#pragma unroll
+    for (int k3 = 0; k3 < 8; ++k3) c[k3 ^ lo] = y[k3];
+    asm volatile("" ::: "memory");
+  }
+}
+
 // The whole forward transform of the batch (N >= 1; N = 1 is the identity).
 // The caller has published buf with a barrier; the last pass ends with one
 // (LDS only: global loads issued before the transform may still be in flight).

@@ -15,7 +15,10 @@
 //   C_s(mz) = sum_mx e^{2 pi i mx x_s / N} T(mx, y_s, mz),
 //   T(mx, y, mz) = sum_my e^{2 pi i my y / N} F(mx, my, mz).
 //
-// Three kernels, all reading their inputs once:
+// Grids of 512 and 1024 with enough sight-lines go through field_planes_kernel,
+// which does both transforms across (kx, ky) one mz at a time without an
+// intermediate, and field_z_planes_kernel.  Otherwise three kernels, all reading
+// their inputs once:
 //   field_ky_kernel  persistent workgroups over (mx, run of C consecutive mz)
 //                    items, the next item's modes read ahead: reads the
 //                    N x C modes (C consecutive mz are contiguous), forms both
@@ -220,6 +223,244 @@ __global__ __launch_bounds__(kKxThreads) void field_kx_kernel(FieldArgs a, int n
   }
 }
 
+// The planes of one mz at a time, straight from the modes to the sight-lines'
+// sums over mx: T is neither written nor read.  A workgroup keeps FP64 sums of
+// both fields for up to kFieldSlots sight-lines per thread in registers, and
+// takes four pairs mx = p, -p per round (p = 0 stands for the pair 0, N/2): each
+// wave reads one mx column of modes (the next round's while the sight-lines are
+// summed), forms both fields' spectra, and transforms them along my by itself
+// (wave_fft, no workgroup barriers); then every thread adds the eight columns to
+// its sight-lines,
+//   C += cos (T(p) + T(-p)) + i sin (T(p) - T(-p)),
+// four FP64 FMAs per pair and field for both signs of mx, with the sums and
+// differences formed once per row.  Sight-lines of a row are consecutive slots
+// of a thread.  The modes of one mz lie 8 bytes in each row of the grid, so the
+// workgroups of an XCD hold consecutive mz and run in step: a line of the
+// modes serves 16 of them from one L2.  At n = 1024 and 6250 sight-lines the
+// kernel takes 6.3 ms, the my and mx kernels through T 6.7 + 5.3; without its
+// reads of modes it takes 3.9 (contiguous reads of the same bytes: 4.1), so the
+// gather bounds it.  Measured and not kept: reads of two mz at once with the odd
+// one's modes kept in memory for its own turn (6.2 ms for 2 GB), the reads
+// started before the transforms (6.5), the waves' reads in rotated order (6.3).
+// Workgroup g of G takes planes mz = g, g + G, .. below N/2; the last plane
+// N/2, which would leave most of a round idle, is split over the workgroups by
+// mx, its parts added by field_last_kernel in a fixed order.
+template <int E>
+struct FieldPlanesLds {
+  static constexpr int N = 64 * E;
+  float2 col[8][2][N];   // by wave: mx = +-(4 r + wave / 2); both fields
+  double2 tw[N];         // e^{-2 pi i t / N}
+  float2 tw1[kWaveTw1<E>], tw2[kWaveTw2];
+};
+
+template <int E, int K>
+__global__ __launch_bounds__(kFieldThreads) __attribute__((amdgpu_waves_per_eu(2))) void
+field_planes_kernel(FieldArgs a) {
+  constexpr int N = 64 * E, HALF = N / 2;
+  constexpr int ROUNDS = HALF / 4;
+  extern __shared__ double2 lds_planes[];
+  FieldPlanesLds<E> &sh = *reinterpret_cast<FieldPlanesLds<E> *>(lds_planes);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int t = tid; t < N; t += kFieldThreads) sh.tw[t] = conj(root_of_unity(a.twiddle, t, N));
+  wave_fft_tables<E>(sh.tw1, sh.tw2, a.twiddle, tid, kFieldThreads);
+
+  // this thread's slots: x | last-of-row flag << 11 | LDS position of y << 12
+  uint32_t word[K];
+  double br[K], bi[K], vr[K], vi[K];  // conjugates of the sums, both fields
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const uint32_t w = a.slot_words[k * kFieldThreads + tid];
+    word[k] = (w & 0xFFFu) | ((uint32_t)wave_fft_pos<E>((int)(w >> 12)) << 12);
+    br[k] = bi[k] = vr[k] = vi[k] = 0.0;
+  }
+
+  const int G = (int)gridDim.x;
+  const int g = (G & 7) == 0 ? ((int)blockIdx.x & 7) * (G >> 3) + ((int)blockIdx.x >> 3)
+                             : (int)blockIdx.x;
+  const int n_planes = g < HALF ? (HALF - g + G - 1) / G : 0;
+  const int n_last = g < ROUNDS ? (ROUNDS - g + G - 1) / G : 0;
+  const int n_steps = n_planes * ROUNDS + n_last;
+  // step i: (mz, round)
+  const auto step_of = [&](int i, int &mz, int &r) {
+    const int pl = i / ROUNDS;
+    mz = pl < n_planes ? g + pl * G : HALF;
+    r = pl < n_planes ? i - pl * ROUNDS : g + (i - n_planes * ROUNDS) * G;
+  };
+  const int pair = wave >> 1;
+  const bool minus = (wave & 1) != 0;
+  float2 gm[E];  // modes of this wave's column, elements lane + 64 r
+  const auto fetch = [&](int i) {
+    int mz, r;
+    step_of(i, mz, r);
+    const int p = 4 * r + pair;
+    const int kx = p == 0 ? (minus ? HALF : 0) : (minus ? N - p : p);
+    int ln = lane;
+    asm volatile("" : "+v"(ln));  // addresses per step, not held across the steps
+    const float2 *src = a.modes + ((size_t)kx * N + ln) * a.H + mz;
+#pragma unroll
+    for (int e = 0; e < E; ++e) gm[e] = src[(size_t)(64 * e) * a.H];
+  };
+  float2 *colb = sh.col[wave][0], *colv = sh.col[wave][1];
+  if (n_steps > 0) fetch(0);
+  __syncthreads();  // the tables
+  for (int i = 0; i < n_steps; ++i) {
+    int mz, r;
+    step_of(i, mz, r);
+    {
+      const int p = 4 * r + pair;
+      const int mx = p == 0 ? (minus ? HALF : 0) : p;  // |mx|: the factors hold its square
+      // factors of |my| = 0 .. N/2, each formed once per column: element y uses
+      // |my| = y below N/2 and N - y above, which another lane holds
+      float2 *fac = colb;
+      int ln = lane;
+      asm volatile("" : "+v"(ln));  // addresses per step, not held across the steps
+#pragma unroll
+      for (int j = 0; j <= E / 2; ++j) {
+        const int my = j < E / 2 ? ln + 64 * j : HALF;
+        float fb, fv;
+        field_factors(a, mx, my, mz, fb, fv);
+        if (j < E / 2 || ln == 0) fac[my] = make_float2(fb, fv);
+        asm volatile("" ::: "memory");  // one factor at a time
+      }
+      asm volatile("" ::: "memory");
+      float2 x[E];
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int y = ln + 64 * e;
+        const float2 f = fac[e < E / 2 ? y : N - y];
+        // conjugated on the way in: the inverse transform is conj(FFT(conj))
+        x[e] = make_float2(gm[e].x * f.x, -gm[e].y * f.x);
+        colv[y] = make_float2(-gm[e].y * f.y, -gm[e].x * f.y);  // conj(i fv g), kept in LDS
+        if ((e & 3) == 3) asm volatile("" ::: "memory");
+      }
+      wave_fft<E>(x, colb, sh.tw1, sh.tw2, ln);
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int e = 0; e < E; ++e) x[e] = colv[ln + 64 * e];
+      asm volatile("" ::: "memory");
+      wave_fft<E>(x, colv, sh.tw1, sh.tw2, ln);
+    }
+    lds_barrier();
+    if (i + 1 < n_steps) fetch(i + 1);  // in flight during the sums
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+      const int p = 4 * r + q;
+      // p = 0, columns 0 and N/2: T(0) + (-1)^x T(N/2).  The same sums give it
+      // with (cos, sin) = (1, 0) or (0, 1) by the parity of x, from the table's
+      // entries 0 and 3 N/4, and the row's differences turned by a quarter
+      const int pm = p == 0 ? 3 * N / 4 : p;
+      const uint32_t xm = p == 0 ? 1u : 0x7FFu;
+      const float2 *cq = sh.col[2 * q][0];
+      double bux, buy, bdx, bdy, vux, vuy, vdx, vdy;  // T(p) +- T(-p) of a row, conjugated
+      const auto row = [&](uint32_t w) {
+        asm volatile("" : "+v"(w));  // decoded here, not held decoded across the steps
+        const float2 *c = cq + (w >> 12);
+        const float2 bp = c[0], vp = c[N], bm = c[2 * N], vm = c[3 * N];
+        bux = (double)bp.x + (double)bm.x;
+        bdx = (double)bp.x - (double)bm.x;
+        buy = (double)bp.y + (double)bm.y;
+        bdy = (double)bp.y - (double)bm.y;
+        vux = (double)vp.x + (double)vm.x;
+        vdx = (double)vp.x - (double)vm.x;
+        vuy = (double)vp.y + (double)vm.y;
+        vdy = (double)vp.y - (double)vm.y;
+        if (p == 0) {
+          double t = bdx;
+          bdx = bdy;
+          bdy = -t;
+          t = vdx;
+          vdx = vdy;
+          vdy = -t;
+        }
+      };
+      const auto root = [&](uint32_t w) {
+        asm volatile("" : "+v"(w));
+        return sh.tw[(pm * (int)(w & xm)) & (N - 1)];
+      };
+      row(word[0]);
+      double2 e = root(word[0]);
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const double2 e1 = k + 1 < K ? root(word[k + 1 < K ? k + 1 : k]) : e;
+        br[k] = __builtin_fma(e.x, bux, __builtin_fma(-e.y, bdy, br[k]));
+        bi[k] = __builtin_fma(e.x, buy, __builtin_fma(e.y, bdx, bi[k]));
+        vr[k] = __builtin_fma(e.x, vux, __builtin_fma(-e.y, vdy, vr[k]));
+        vi[k] = __builtin_fma(e.x, vuy, __builtin_fma(e.y, vdx, vi[k]));
+        if (k + 1 < K) {
+          // the sums above are done with this row before the next one replaces it
+          asm volatile("" : "+v"(br[k]), "+v"(bi[k]), "+v"(vr[k]), "+v"(vi[k]));
+          if (word[k] & 0x800u) row(word[k + 1 < K ? k + 1 : k]);
+        }
+        e = e1;
+      }
+    }
+    const bool end = i + 1 == n_steps || (mz < HALF && r == ROUNDS - 1);
+    if (end) {
+      double2 *out = mz < HALF ? a.planes + (size_t)mz * 2 * kFieldSlotSum
+                               : a.last_parts + (size_t)g * 2 * kFieldSlotSum;
+      int t = tid;
+      asm volatile("" : "+v"(t));
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        out[k * kFieldThreads + t] = make_double2(br[k], -bi[k]);
+        out[kFieldSlotSum + k * kFieldThreads + t] = make_double2(vr[k], -vi[k]);
+        br[k] = bi[k] = vr[k] = vi[k] = 0.0;
+      }
+    }
+    lds_barrier();  // the next round overwrites the columns
+  }
+}
+
+// The last plane mz = N/2: the workgroups' parts added in order.
+__global__ __launch_bounds__(256) void field_last_kernel(FieldArgs a, int parts) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= 2 * kFieldSlotSum) return;
+  double2 s = make_double2(0.0, 0.0);
+#pragma unroll 16
+  for (int p = 0; p < parts; ++p) s = cadd(s, a.last_parts[(size_t)p * 2 * kFieldSlotSum + i]);
+  a.planes[(size_t)(a.N / 2) * 2 * kFieldSlotSum + i] = s;
+}
+
+// The transform along z from the plane sums, four neighbouring slots per
+// workgroup (64 contiguous bytes of every plane), as field_z_kernel.
+constexpr int kZPThreads = 512;
+__global__ __launch_bounds__(kZPThreads) void field_z_planes_kernel(FieldArgs a) {
+  extern __shared__ double2 lds_zp[];  // [N][4]
+  const int N = a.N, half = N / 2;
+  const int c = threadIdx.x & 3;
+  const int slot = 4 * (int)blockIdx.x + c;
+  const int line = a.slot_lines[slot];
+  if (!__syncthreads_or(line >= 0)) return;
+  for (int k = threadIdx.x >> 2; k <= half; k += kZPThreads / 4) {
+    const double2 *pl = a.planes + (size_t)k * 2 * kFieldSlotSum + slot;
+    double2 b = make_double2(0.0, 0.0), v = b;
+    if (line >= 0) {
+      b = pl[0];
+      v = pl[kFieldSlotSum];
+    }
+    // conjugates of C_b + i C_v and, at N - k, of conj(C_b) + i conj(C_v); the
+    // imaginary parts of planes 0 and N/2 drop out of Re[]
+    if (k == 0 || k == half) {
+      lds_zp[4 * k + c] = make_double2(b.x, -v.x);
+    } else {
+      lds_zp[4 * k + c] = make_double2(b.x - v.y, -(b.y + v.x));
+      lds_zp[4 * (N - k) + c] = make_double2(b.x + v.y, b.y - v.x);
+    }
+  }
+  __syncthreads();
+  fft_batch<kZPThreads, 4096>(lds_zp, a.twiddle, N, 2);
+  if (line < 0) return;
+  const double scale = a.inv_n3;
+  float *ob = a.delta_b + (size_t)line * N;
+  float *ov = a.v_z + (size_t)line * N;
+  for (int t = threadIdx.x >> 2; t < N; t += kZPThreads / 4) {
+    const double2 z = lds_zp[4 * t + c];  // conj of the inverse transform: f_b - i f_v
+    ob[t] = (float)(z.x * scale);
+    ov[t] = (float)(-z.y * scale);
+  }
+}
+
 __global__ __launch_bounds__(kZThreads) void field_z_kernel(FieldArgs a) {
   extern __shared__ double2 lds_z[];  // [N]
   const int s = blockIdx.x;
@@ -287,6 +528,64 @@ hipError_t field_kernel_attributes(int *ky_resident) {
   g_attr_set[dev] = true;
   *ky_resident = g_ky_resident[dev];
   return hipSuccess;
+}
+
+bool field_planes_fit(int N, int64_t n_lines) {
+  // 512 and 1024 are the sizes of wave_fft; the slots hold 6656 sight-lines.  A
+  // call at N = 512 takes 0.83, 0.89, 0.99 and 1.27 ms with 16, 400, 1500 and
+  // 6250 sight-lines against 0.92, 1.26, 1.55 and 2.46 through T; at N = 1024
+  // the gathered modes set the time, 5.97, 5.99 and 6.90 ms with 16, 256 and
+  // 6250, and T costs little while few rows are kept: 5.28, 5.92 and 12.37.
+  if (n_lines > kFieldSlotSum) return false;
+  return N == 512 || (N == 1024 && n_lines >= 320);
+}
+
+int field_last_parts(int N, int resident) { return std::min(N / 8, resident); }
+
+hipError_t field_planes_attributes(int N, int *resident) {
+  static int known[64][2] = {{0}};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  int &r = known[dev][N == 1024 ? 1 : 0];
+  if (r == 0) {
+    const void *f = N == 1024 ? (const void *)field_planes_kernel<16, kFieldSlots>
+                              : (const void *)field_planes_kernel<8, kFieldSlots>;
+    const size_t lds = N == 1024 ? sizeof(FieldPlanesLds<16>) : sizeof(FieldPlanesLds<8>);
+    int per_cu = 0, cus = 0;
+    if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) !=
+            hipSuccess ||
+        (e = hipFuncSetAttribute((const void *)field_z_planes_kernel,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)(4 * 1024 * sizeof(double2)))) != hipSuccess ||
+        (e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, kFieldThreads, lds)) !=
+            hipSuccess ||
+        (e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) !=
+            hipSuccess)
+      return e;
+    r = std::max(1, per_cu) * cus;
+  }
+  *resident = r;
+  return hipSuccess;
+}
+
+hipError_t launch_field_planes(const FieldArgs &a, int resident, hipStream_t st) {
+  if (a.N == 1024)
+    hipLaunchKernelGGL((field_planes_kernel<16, kFieldSlots>), dim3(resident), dim3(kFieldThreads),
+                       sizeof(FieldPlanesLds<16>), st, a);
+  else
+    hipLaunchKernelGGL((field_planes_kernel<8, kFieldSlots>), dim3(resident), dim3(kFieldThreads),
+                       sizeof(FieldPlanesLds<8>), st, a);
+  hipLaunchKernelGGL(field_last_kernel, dim3((2 * kFieldSlotSum + 255) / 256), dim3(256), 0, st,
+                     a, field_last_parts(a.N, resident));
+  return hipGetLastError();
+}
+
+hipError_t launch_field_z_planes(const FieldArgs &a, hipStream_t st) {
+  hipLaunchKernelGGL(field_z_planes_kernel, dim3(kFieldSlotSum / 4), dim3(kZPThreads),
+                     4 * sizeof(double2) * (size_t)a.N, st, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_field_ky(const FieldArgs &a, int resident, hipStream_t st) {

@@ -203,7 +203,24 @@ struct FieldArgs {
   double2 *Cb, *Cv;      // device [S][H] after the mx transform
   float *delta_b, *v_z;  // device [S][N] outputs
   const double2 *twiddle;  // the shared FFT table (kFftTableLen / 2 entries)
+  // the fused plane kernel: its slots (as P3dArgs), its sums [H][2][kFieldSlotSum]
+  // (both fields; the last plane from field_last) and the workgroups' parts of
+  // the last plane [parts][2][kFieldSlotSum]
+  const uint32_t *slot_words;
+  const int *slot_lines;
+  double2 *planes, *last_parts;
 };
+// Slots of the fused plane kernel: sight-lines that each of its threads holds.
+constexpr int kFieldThreads = 512;
+constexpr int kFieldSlots = 13;
+constexpr int kFieldSlotSum = kFieldThreads * kFieldSlots;
+constexpr int kSlotUnused = -2;
+// Whether the fused plane kernel takes n_lines sight-lines of a grid of side N.
+bool field_planes_fit(int N, int64_t n_lines);
+int field_last_parts(int N, int resident);  // workgroups with a part of the last plane
+hipError_t field_planes_attributes(int N, int *resident);
+hipError_t launch_field_planes(const FieldArgs &a, int resident, hipStream_t st);
+hipError_t launch_field_z_planes(const FieldArgs &a, hipStream_t st);
 int field_ky_columns(int N);  // mz values per field_ky work item
 // Sets the kernels' LDS limits once per device; *ky_resident: resident
 // workgroups of the persistent my-transform kernel.
@@ -223,7 +240,6 @@ constexpr int kP3dModeThreads = 512;
 constexpr int kP3dModeSlots = 14;
 constexpr int kP3dMaxSpill = 16;
 constexpr int kP3dSlotZero = -1;        // a row without sight-lines
-constexpr int kP3dSlotUnused = -2;
 struct P3dArgs {
   const float *F;         // device [S][n] flux
   const double *w;        // device [S] weights or null (all 1)

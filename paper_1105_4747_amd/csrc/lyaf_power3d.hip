@@ -400,7 +400,7 @@ p3d_modes_kernel(P3dArgs a, int nb) {
 #pragma unroll
   for (int k = 0; k < kModeSlots; ++k) {
     slot[k] = a.slot_words[k * kModeThreads + tid];
-    if (a.slot_lines[k * kModeThreads + tid] != kP3dSlotUnused) used = k + 1;
+    if (a.slot_lines[k * kModeThreads + tid] != kSlotUnused) used = k + 1;
     g[k] = make_double2(0.0, 0.0);
   }
   for (int m = 32; m >= 1; m >>= 1) used = max(used, __shfl_xor(used, m));

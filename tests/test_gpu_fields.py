@@ -146,3 +146,35 @@ def test_full_size_workload_sampled():
                                      w.sx[pick], w.sy[pick])
     _assert_close("delta_b (sampled)", b[pick], rb)
     _assert_close("v_z (sampled)", v[pick], rv)
+
+
+def test_fused_planes_at_512():
+    """The fused plane kernel at N = 512 with one sight-line, one per thread, one
+    past that, and its most (13 per thread), 40 of them in one row: three
+    sight-lines against the oracle on the same modes, and all 6656 against the
+    three-kernel path, which takes 6657 (each is within the bar of the truth)."""
+    from synth import fields
+    N, most = 512, 13 * 512
+    rng = np.random.default_rng(12)
+    sx, sy = rng.integers(0, N, most + 1), rng.integers(0, N, most + 1)
+    sy[:40] = 77
+    L, kF, Ep, amp = 120.0, 6.5, 73.0, 1.3
+    pk, dk = _table(N, L, n=900)
+    modes = fields.field_modes_white(N, 5, "cuda:0")
+    pick = [0, 1, most - 1]
+    rb, rv = FS.skewer_fields_planes(modes.cpu().numpy(), pk, dk, amp, L, kF, Ep, sx[pick],
+                                     sy[pick])
+    ref = {}
+    for S in (most + 1, most, 513, 512, 1):
+        print(f"field synthesis: N={N} S={S}", flush=True)
+        b, v = _run(modes, pk, dk, amp, L, kF, Ep, sx[:S], sy[:S])
+        have = [i for i, k in enumerate(pick) if k < S]
+        at = [pick[i] for i in have]
+        _assert_close("delta_b (sampled)", b[at], rb[have])
+        _assert_close("v_z (sampled)", v[at], rv[have])
+        if S == most + 1:
+            ref = {"b": b, "v": v}
+            continue
+        for name, got in (("b", b), ("v", v)):
+            full = ref[name][:S]
+            assert np.max(np.abs(got - full)) <= 2 * FIELD_TOL * np.sqrt(np.mean(full * full))
