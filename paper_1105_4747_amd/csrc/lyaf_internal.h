@@ -54,11 +54,16 @@ struct NormState {
   double step;       // |A_new - A_old| / A_new of the last step
   int32_t iter, done, status;
   int32_t phase;     // kNormPhaseFP32, kNormPhaseExact
-  int32_t pending;   // no moments at A yet (the next full pass computes them)
-  int32_t buf;       // partial buffer (0 or 1) holding the last moments
-  int32_t nparts;    // workgroups that wrote them
 };
 constexpr int32_t kNormPhaseFP32 = 1, kNormPhaseExact = 2;
+
+constexpr int kNormPasses = 3;  // full root-find passes after the sample
+// The states after the sample and each pass, and the counts by which a kernel
+// finds its last workgroup (zero before the first call).
+struct NormScratch {
+  NormState st[kNormPasses + 1];
+  uint32_t ticket, arrived;
+};
 
 // Per-(device, stream) workspace.
 struct Workspace {
@@ -66,7 +71,7 @@ struct Workspace {
   hipStream_t stream = nullptr;
   uint32_t *status = nullptr;       // sticky LYAF_STATUS_* bits
   double *partials = nullptr;       // [kPartialsDoubles]
-  NormState *norm = nullptr;        // [kNormPasses + 2]
+  NormScratch *norm = nullptr;
   double *ratio = nullptr;          // backward-normalise scalar
   // growable buffers (the work lists of the entry points live in the API's
   // per-(workspace, tile) records; a plan keeps its offsets here)
@@ -91,7 +96,6 @@ struct Workspace {
 };
 constexpr int kMaxPartialBlocks = 512;  // workgroups of a root-find pass
 constexpr int kPartStride = 8;          // doubles per workgroup partial
-constexpr int kNormPasses = 3;          // full root-find passes after the sample
 constexpr int kSampleN = 8192;          // pixels the root-find samples first
 constexpr int kSampleCap = 16384;       // room for the sample in the partials allocation
 // The partials allocation also holds the sample (up to kSampleCap floats)

@@ -4,39 +4,38 @@
 //
 // The root-find runs on the device without host synchronisation, as a short
 // fixed sequence of kernels (each kernel boundary costs a few microseconds,
-// so there are few):
-//   norm_gather    8192 pixels spread evenly over the batch (all of them if
-//                  fewer) into a contiguous buffer;
-//   norm_sample    one workgroup keeps the sample in registers and iterates
-//                  to convergence on it, starting from the Jensen
-//                  lower bound A0 = -ln F / <tau> (g(A0) >= 0 for the convex,
-//                  decreasing g(A) = <exp(-A tau)> - F); FP32 exponentials,
-//                  FP64 sums.  The sample's root is within a few 1e-2 of the
-//                  batch's (the sampling error of g is a few 1e-3).
+// so there are few).  Up to kSmallPixels pixels one workgroup does everything
+// (norm_small); beyond:
+//   norm_sample    8192 pixels spread evenly over the batch, gathered by eight
+//                  workgroups; the last to finish iterates to convergence on
+//                  them, starting from the Jensen lower bound
+//                  A0 = -ln F / <tau> (g(A0) >= 0 for the convex, decreasing
+//                  g(A) = <exp(-A tau)> - F); FP32 exponentials, FP64 sums.
+//                  The sample's root is within a few 1e-2 of the batch's (the
+//                  sampling error of g is a few 1e-3).
 //   norm_pass x3   S_k = sum tau^k exp(-A tau) over every pixel, in FP64 per
 //                  workgroup, with the counts of zero and invalid values.
 //                  After a settled sample the passes are exact from the
-//                  first: FP64 exponentials (to 2e-13), k = 0 .. 5.  Each
-//                  pass begins with every workgroup summing the previous
-//                  pass's partials in the same fixed order and taking the
-//                  same step: the root of the degree-5 Taylor series of g
-//                  about A (the scaled moments M_k = A^k S_k / P are its
-//                  coefficients up to sign and k!), accepted at once when it
-//                  is below 0.1 of A and the degree-4 series' root agrees
-//                  with it to 1e-8; otherwise a safeguarded Halley step
-//                  (Newton, then bisection, as fallbacks) inside the bracket,
-//                  accepted below 1e-5 of A.  A sample without a settled root
-//                  starts the passes with FP32 exponentials and k = 0 .. 2
-//                  until a Halley step is below 3e-2 of A.  A kernel
-//                  boundary, not a device-scope fence, publishes the
-//                  partials: on a multi-XCD part a fence per workgroup
-//                  writes back and invalidates L2 and serialises the pass.
-//   norm_finalise  the last step, then tau' = A tau and F = exp(-tau').
-// From a sample root a few 1e-2 off, the degree-5 series' root is within
-// ~1e-11 of the batch's root and the degree-4 one within ~1e-9 (lognormal-
-// field tau), so one exact pass usually suffices: the second pass takes the
-// step and returns, and the third (a reserve for the Halley iteration) and the
-// finalisation find nothing left to do.  Results are bitwise reproducible.
+//                  first: FP64 exponentials (to 2e-13), k = 0 .. 5.  The last
+//                  workgroup to finish sums the workgroups' partials in a
+//                  fixed order and takes the step: the root of the degree-5
+//                  Taylor series of g about A (the scaled moments
+//                  M_k = A^k S_k / P are its coefficients up to sign and k!),
+//                  accepted at once when it is below 0.1 of A and the degree-4
+//                  series' root agrees with it to 1e-8; otherwise a safeguarded
+//                  Halley step (Newton, then bisection, as fallbacks) inside
+//                  the bracket, accepted below 1e-5 of A.  A sample without a
+//                  settled root starts the passes with FP32 exponentials and
+//                  k = 0 .. 2 until a Halley step is below 3e-2 of A.
+//   norm_finalise  tau' = A tau and F = exp(-tau').
+// What a last workgroup reads of the others is written and read with
+// device-scope atomic accesses, which go past the L2 of each die, and the writer
+// waits for their completion before it counts itself in.  A device-scope fence
+// instead writes back and invalidates that L2 for every workgroup and
+// serialised the pass (1 ms).  From a sample root a few 1e-2 off, the degree-5
+// series' root is within ~1e-11 of the batch's root and the degree-4 one within
+// ~1e-9 (lognormal-field tau), so one exact pass usually suffices: the other two
+// find nothing left to do.  Results are bitwise reproducible.
 #include <math.h>
 
 #include <mutex>
@@ -100,41 +99,55 @@ __device__ __forceinline__ double exp_neg_tab(double x, const double *tab) {
   return tab[ni & 255] * p * __hiloint2double(ex << 20, 0);
 }
 
-// Sum of N values over a workgroup of NW waves (fixed order), in every
-// thread.  For many values thread q < N adds up quantity q's NW wave sums, so
-// that no thread holds all N NW of them in registers at once (an extra
-// barrier); few are added up by every thread.  sh holds N (NW + 1) doubles.
-constexpr int block_sum_lds(int N, int NW) { return N * (NW + 1); }
+// 1 / x to about 1e-15 relative (the hardware's estimate and two Newton steps):
+// the steps of a converging iteration, whose fixed point it does not move.  The
+// full division is a chain of a dozen FP64 operations more.
+__device__ __forceinline__ double step_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
+
+// Sum over the 16 lanes of a row (DPP), in every lane of it.
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row_sum(double x) {
+  x += dpp_d<0xB1>(x);   // quad_perm [1,0,3,2]
+  x += dpp_d<0x4E>(x);   // quad_perm [2,3,0,1]
+  x += dpp_d<0x141>(x);  // lane i <-> 7-i within each 8 lanes
+  x += dpp_d<0x140>(x);  // lane i <-> 15-i within each 16 lanes
+  return x;
+}
+
+// Sum of N values over a workgroup of NW waves (fixed order), in every thread:
+// DPP sums of each row of 16 lanes, then one wave per quantity adds the rows (an
+// all-shuffle reduction of eight FP64 values costs 96 LDS operations per wave).
+// sh holds N (4 NW + 1) doubles.
+constexpr int block_sum_lds(int N, int NW) { return N * (4 * NW + 1); }
 template <int N, int NW>
 __device__ __forceinline__ void block_sum(double (&v)[N], double *sh) {
+  constexpr int ROWS = 4 * NW;
+  static_assert(ROWS <= 64, "one lane per row");
 #pragma unroll
-  for (int q = 0; q < N; ++q)
-    for (int m = 32; m >= 1; m >>= 1) v[q] += __shfl_xor(v[q], m);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
+  for (int q = 0; q < N; ++q) v[q] = row_sum(v[q]);
+  if ((threadIdx.x & 15) == 0)
 #pragma unroll
-    for (int q = 0; q < N; ++q) sh[q * NW + w] = v[q];
+    for (int q = 0; q < N; ++q) sh[q * ROWS + (threadIdx.x >> 4)] = v[q];
   __syncthreads();
-  if constexpr (N * NW <= 16) {
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-      double t = sh[q * NW];
-#pragma unroll
-      for (int k = 1; k < NW; ++k) t += sh[q * NW + k];
-      v[q] = t;
-    }
-  } else {
-    if (threadIdx.x < N) {
-      const double *r = sh + threadIdx.x * NW;
-      double t = r[0];
-#pragma unroll
-      for (int k = 1; k < NW; ++k) t += r[k];
-      sh[N * NW + threadIdx.x] = t;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < N; ++q) v[q] = sh[N * NW + q];
+  const int lane = threadIdx.x & 63;
+  for (int q = threadIdx.x >> 6; q < N; q += NW) {
+    double t = row_sum(lane < ROWS ? sh[q * ROWS + lane] : 0.0);
+    if (ROWS > 16) t += __shfl_xor(t, 16);
+    if (ROWS > 32) t += __shfl_xor(t, 32);
+    if (lane == 0) sh[N * ROWS + q] = t;
   }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < N; ++q) v[q] = sh[N * ROWS + q];
   __syncthreads();
 }
 
@@ -150,6 +163,18 @@ __device__ __forceinline__ void reduce_partials(const double *partials, int nblo
   block_sum<NQ, NW>(tot, sh);
 }
 
+// Device-scope accesses of data that another workgroup of the same kernel reads.
+template <typename T>
+__device__ __forceinline__ void put_shared(T *p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T get_shared(const T *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// This wave's stores have reached the device's point of coherence.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 constexpr int kNormThreads = 256;  // backward kernels and finalise
 constexpr int kNormWaves = kNormThreads / kWave;
 constexpr int kPassThreads = 512;  // full root-find passes
@@ -159,10 +184,19 @@ constexpr int kPassBatch = 4;    // float4 reads in flight per thread in a pass
 constexpr int kNormQ = 8;
 constexpr int kQZero = 6, kQBad = 7;
 static_assert(kNormQ <= kPartStride, "a workgroup's partials fit its slot");
+// One wave per SIMD: the iteration is a chain of FP64 sums and divisions that
+// every wave takes, 1.8 us a step with 16 waves.
 constexpr int kSampleThreads = 256;
 constexpr int kSampleWaves = kSampleThreads / kWave;
-constexpr int kGatherThreads = 256;
+constexpr int kSampleGroups = kSampleN / kSampleThreads;  // one gathered pixel per thread
 constexpr int kSampleIters = 32;
+constexpr int kSmallPixels = 16384;  // most pixels of norm_small
+// The second and third pass usually find nothing to do, but cost 4.6 us each as
+// kernels: up to kAlonePixels (16 MB for one workgroup to pass over, when it has to)
+// the first pass's last workgroup makes them, 2e6 pixels 33.7 -> 29.0 us; beyond,
+// 128 workgroups keep their launch short.
+constexpr int kReserveBlocks = 128;
+constexpr int64_t kAlonePixels = int64_t(1) << 22;
 // the sample iteration stops at this step: its root is only ~1e-2 from the
 // batch's, which the first full pass's series step corrects
 constexpr double kSampleTol = 1e-3;
@@ -181,104 +215,16 @@ __device__ __forceinline__ void halley(NormState &s, double g, double g1, double
   if (g != 0.0) {
     if (g > 0.0) s.lo = s.A; else s.hi = s.A;
     const double den = 2.0 * g1 * g1 - g * g2;
-    const double hal = (den != 0.0) ? s.A - 2.0 * g * g1 / den : NAN;
-    const double newton = (g1 < 0.0) ? s.A - g / g1 : NAN;
+    const double hal = (den != 0.0) ? s.A - 2.0 * g * g1 * step_rcp(den) : NAN;
+    const double newton = (g1 < 0.0) ? s.A - g * step_rcp(g1) : NAN;
     if (hal > s.lo && hal < s.hi) An = hal;
     else if (newton > s.lo && newton < s.hi) An = newton;
     else if (isfinite(s.hi)) An = 0.5 * (s.lo + s.hi);
     else An = 2.0 * s.A;
   }
-  s.step = (g == 0.0) ? 0.0 : fabs(An - s.A) / An;
+  s.step = (g == 0.0) ? 0.0 : fabs(An - s.A) * step_rcp(An);
   s.A = An;
   s.iter += 1;
-}
-
-// The sample: pixel floor(k P / N) for k < N = min(P, kSampleN), gathered by
-// many workgroups into a contiguous buffer (one workgroup pulling thousands of
-// scattered cache lines alone would take tens of microseconds).
-__global__ __launch_bounds__(kGatherThreads) void norm_gather_kernel(
-    const float *__restrict__ tau, int64_t P, float *__restrict__ sample) {
-  const int64_t N = P < kSampleN ? P : kSampleN;
-  const int64_t k = (int64_t)blockIdx.x * kGatherThreads + threadIdx.x;
-  if (k < N) sample[k] = tau[(k * P) / N];
-}
-
-// Root of the sample's g: one workgroup of four waves, the sample in LDS.
-// Leaves the state for the full passes (FP32 phase, open bracket, no moments
-// yet).
-__global__ __launch_bounds__(kSampleThreads) void norm_sample_kernel(
-    const float *__restrict__ sample, int64_t P, double target, NormState *st_out) {
-  __shared__ double sh[block_sum_lds(3, kSampleWaves)];
-  __shared__ float4 xs[kSampleN / 4];
-  const int64_t N = P < kSampleN ? P : kSampleN;
-  double v[3] = {0.0, 0.0, 0.0};  // sum tau, #zeros, #invalid over the sample
-  constexpr int R = kSampleN / 4 / kSampleThreads;  // float4 per thread
-  float4 q[R];
-#pragma unroll
-  for (int j = 0; j < R; ++j)  // every read in flight at once
-    q[j] = reinterpret_cast<const float4 *>(sample)[threadIdx.x + j * kSampleThreads];
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    const int k4 = threadIdx.x + j * kSampleThreads;
-    float t[4] = {q[j].x, q[j].y, q[j].z, q[j].w};
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const bool in = 4 * (int64_t)k4 + c < N;  // slots past N hold tau = 0
-      const bool bad = in && (!(t[c] >= 0.f) || !isfinite(t[c]));
-      t[c] = (in && !bad) ? t[c] : 0.f;
-      v[0] += (double)t[c];
-      v[1] += (in && !bad && t[c] == 0.f) ? 1.0 : 0.0;
-      v[2] += bad ? 1.0 : 0.0;
-    }
-    xs[k4] = make_float4(t[0], t[1], t[2], t[3]);
-  }
-  block_sum<3, kSampleWaves>(v, sh);  // its barriers publish xs
-  NormState s;
-  s.P = (double)P;
-  s.Ps = (double)N;
-  s.target = target;
-  s.step = INFINITY;
-  s.iter = 0;
-  s.done = 0;
-  s.status = 0;
-  s.phase = kNormPhaseFP32;
-  s.pending = 1;
-  s.buf = 0;
-  s.nparts = 0;
-  s.lo = 0.0;
-  s.hi = INFINITY;
-  const double mean = v[0] / s.Ps;
-  s.A = (mean > 0.0) ? -log(target) / mean : 1.0;
-  // iterate only if the sample is valid and has a root; otherwise the full
-  // passes start from A0 and settle the status
-  if (v[2] == 0.0 && v[1] / s.Ps < target && mean > 0.0) {
-    const double pad = (double)(kSampleN - N);
-    for (int it = 0; it < kSampleIters; ++it) {
-      const float Al = (float)(s.A * kLog2e);
-      float e0 = 0.f, e1 = 0.f, e2 = 0.f;
-      for (int k4 = threadIdx.x; k4 < kSampleN / 4; k4 += kSampleThreads) {
-        const float4 q = xs[k4];
-        const float t[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const float e = __builtin_amdgcn_exp2f(-(Al * t[c]));
-          e0 += e;
-          e1 = __builtin_fmaf(t[c], e, e1);
-          e2 = __builtin_fmaf(t[c] * t[c], e, e2);
-        }
-      }
-      double m[3] = {(double)e0, (double)e1, (double)e2};
-      block_sum<3, kSampleWaves>(m, sh);
-      const double g = (m[0] - pad) / s.Ps - target;
-      halley(s, g, -m[1] / s.Ps, m[2] / s.Ps);
-      if (s.step <= kSampleTol) break;
-    }
-    // a settled sample root is close enough for the exact phase's series step
-    if (s.step <= kSampleTol) s.phase = kNormPhaseExact;
-  }
-  s.lo = 0.0;
-  s.hi = INFINITY;
-  if (threadIdx.x == 0) *st_out = s;
 }
 
 // Root d of the degree-D Taylor model of g about A in the relative step
@@ -305,7 +251,7 @@ __device__ double taylor_root(const double (&M)[6], double target, double d0) {
       dp = fma(dp, d, (double)n * c[n]);
     }
     p = fma(p, d, c[0]);
-    const double dn = d - p / dp;
+    const double dn = d - p * step_rcp(dp);
     if (!isfinite(dn)) return NAN;
     if (fabs(dn - d) <= 4e-16 * fabs(dn) + 1e-300) return dn;  // settled to rounding
     d = dn;
@@ -363,43 +309,215 @@ __device__ NormState norm_step(NormState s, const double (&tot)[kNormQ]) {
   return s;
 }
 
-// A full pass.  Every workgroup reads the state the previous kernel left,
-// sums the previous pass's partials in the same fixed order and takes the
-// same step; workgroup 0 records the result.  Then S0..S2 at the new A (FP32
-// or FP64 exponentials by phase) and the counts, per workgroup.
-__global__ __launch_bounds__(kPassThreads) void norm_pass_kernel(
-    const float *__restrict__ tau, int64_t P, double *partials, const NormState *st_prev,
-    NormState *st_out, uint32_t *status) {
-  __shared__ double sh[block_sum_lds(kNormQ, kPassWaves)];
-  __shared__ NormState shs;
-  if (threadIdx.x == 0) shs = *st_prev;
-  __syncthreads();
-  NormState s = shs;
-  if (s.done) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *st_out = s;
-    return;
-  }
-  if (!s.pending) {
-    double tot[kNormQ];
-    reduce_partials<kNormQ, kPassWaves>(partials + s.buf * kPartStride * kMaxPartialBlocks,
-                                        s.nparts, tot, sh);
-    if (threadIdx.x == 0) shs = norm_step(s, tot);
+// The state a root-find starts from, given the mean of the pixels it has seen.
+__device__ __forceinline__ NormState norm_start(int64_t P, double seen, double target,
+                                                double mean) {
+  NormState s;
+  s.P = (double)P;
+  s.Ps = seen;
+  s.target = target;
+  s.step = INFINITY;
+  s.iter = 0;
+  s.done = 0;
+  s.status = 0;
+  s.phase = kNormPhaseFP32;
+  s.lo = 0.0;
+  s.hi = INFINITY;
+  s.A = (mean > 0.0) ? -log(target) / mean : 1.0;
+  return s;
+}
+
+// Halley's iteration on the R pixels that each thread holds (FP32 exponentials,
+// FP64 sums over the workgroup) to a step of kSampleTol; s.phase becomes exact
+// when it settles.  Values past the seen ones are tau = 0 and number `pad`.
+template <int R, int NW>
+__device__ __forceinline__ void norm_iterate(NormState &s, const float (&t)[R], double pad,
+                                             double *sh) {
+  constexpr int ROWS = 4 * NW;
+  const double inv = 1.0 / s.Ps;
+  const int lane = threadIdx.x & 63;
+  for (int it = 0; it < kSampleIters; ++it) {
+    const float Al = (float)(s.A * kLog2e);
+    float e0 = 0.f, e1 = 0.f, e2 = 0.f;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const float e = __builtin_amdgcn_exp2f(-(Al * t[k]));
+      e0 += e;
+      e1 = __builtin_fmaf(t[k], e, e1);
+      e2 = __builtin_fmaf(t[k] * t[k], e, e2);
+    }
+    // sums over the workgroup with one barrier: every wave adds the row sums
+    // itself, and takes the same step; alternate iterations use the two halves
+    // of sh
+    double m[3] = {row_sum((double)e0), row_sum((double)e1), row_sum((double)e2)};
+    double *buf = sh + (it & 1) * 3 * ROWS;
+    if ((threadIdx.x & 15) == 0)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) buf[q * ROWS + (threadIdx.x >> 4)] = m[q];
     __syncthreads();
-    s = shs;
-    if (s.done) {
-      if (blockIdx.x == 0 && threadIdx.x == 0) {
-        *st_out = s;
-        if (s.status) atomicOr(status, (uint32_t)s.status);
-      }
-      return;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      m[q] = row_sum(lane < ROWS ? buf[q * ROWS + lane] : 0.0);
+      m[q] += __shfl_xor(m[q], 16);  // rows past ROWS / 16 hold 0: every lane
+      m[q] += __shfl_xor(m[q], 32);  // gets the sum
+    }
+    const double g = (m[0] - pad) * inv - s.target;
+    halley(s, g, -m[1] * inv, m[2] * inv);
+    if (s.step <= kSampleTol) break;
+  }
+  // a settled root is close enough for the exact phase's series step
+  if (s.step <= kSampleTol) s.phase = kNormPhaseExact;
+  s.lo = 0.0;
+  s.hi = INFINITY;
+  __syncthreads();  // sh is free again
+}
+
+// The sample: pixel floor(k P / N), k < N = kSampleN, one per thread of
+// kSampleGroups workgroups (one workgroup pulling thousands of scattered cache
+// lines alone would take tens of microseconds).  The last workgroup to finish
+// finds the root of the sample's g and leaves the state for the full passes.
+__global__ __launch_bounds__(kSampleThreads) void norm_sample_kernel(
+    const float *__restrict__ tau, int64_t P, double target, float *sample, NormScratch *ns) {
+  __shared__ double sh[2 * block_sum_lds(3, kSampleWaves)];
+  __shared__ int last;
+  const int64_t k = (int64_t)blockIdx.x * kSampleThreads + threadIdx.x;
+  put_shared(sample + k, tau[(k * P) / kSampleN]);
+  stores_done();
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    // the ticket only counts up, kSampleGroups per call: nothing to reset
+    const uint32_t t = __hip_atomic_fetch_add(&ns->ticket, 1u, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+    last = (t % kSampleGroups) == kSampleGroups - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  if (threadIdx.x == 0) put_shared(&ns->arrived, 0u);
+  constexpr int R = kSampleN / kSampleThreads;
+  float t[R];
+  {
+    const uint64_t *s8 = reinterpret_cast<const uint64_t *>(sample);
+    uint64_t w[R / 2];  // every read in flight at once
+#pragma unroll
+    for (int j = 0; j < R / 2; ++j) w[j] = get_shared(s8 + threadIdx.x + j * kSampleThreads);
+#pragma unroll
+    for (int j = 0; j < R / 2; ++j) {
+      t[2 * j] = __uint_as_float((uint32_t)w[j]);
+      t[2 * j + 1] = __uint_as_float((uint32_t)(w[j] >> 32));
     }
   }
-  const int out_buf = 1 - s.buf;
+  double v[3] = {0.0, 0.0, 0.0};  // sum tau, #zeros, #invalid over the sample
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const bool bad = !(t[j] >= 0.f) || !isfinite(t[j]);
+    t[j] = bad ? 0.f : t[j];
+    v[0] += (double)t[j];
+    v[1] += (!bad && t[j] == 0.f) ? 1.0 : 0.0;
+    v[2] += bad ? 1.0 : 0.0;
+  }
+  block_sum<3, kSampleWaves>(v, sh);
+  NormState s = norm_start(P, (double)kSampleN, target, v[0] / (double)kSampleN);
+  // iterate only if the sample is valid and has a root; otherwise the full
+  // passes start from A0 and settle the status
+  if (v[2] == 0.0 && v[1] / s.Ps < target && v[0] > 0.0)
+    norm_iterate<R, kSampleWaves>(s, t, 0.0, sh);
+  if (threadIdx.x == 0) ns->st[0] = s;
+}
+
+// A small batch (at most R pixels per thread of the one workgroup): the
+// iteration on all of them, exact passes until a step is accepted, tau' and F,
+// with tau in registers throughout.  A chain of kernels costs its launches and
+// latencies whatever its work: 23-27 us for the six kernels of the earlier form
+// and 21 us for today's three; this one takes 7.8 us at 512 pixels, 9.5 at 4096,
+// 11.5 at 8192 and 16.2 at 16384, where its one compute unit is already busy with
+// FP64 arithmetic.
+constexpr int kSmallPasses = 8;
+template <int R, int THREADS>
+__global__ __launch_bounds__(THREADS) void norm_small_kernel(float *__restrict__ tau,
+                                                             float *__restrict__ F, int P,
+                                                             double target, double *A_dev,
+                                                             uint32_t *status) {
+  constexpr int NW = THREADS / kWave;
+  __shared__ double sh[block_sum_lds(kNormQ, NW)];  // more than the iteration's 24 NW
+  __shared__ double tab[256];  // 2^(-j/256)
+  __shared__ NormState shs;
+  const int tid = threadIdx.x;
+  float t[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const int p = tid + j * THREADS;
+    t[j] = p < P ? tau[p] : 0.f;
+  }
+  for (int j = tid; j < 256; j += THREADS) tab[j] = exp_neg(j * (kLn2 / 256.0));
+  double v[3] = {0.0, 0.0, 0.0};  // sum tau, #zeros, #invalid
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const bool in = tid + j * THREADS < P;
+    const bool bad = !(t[j] >= 0.f) || !isfinite(t[j]);
+    v[0] += bad ? 0.0 : (double)t[j];
+    v[1] += (in && t[j] == 0.f) ? 1.0 : 0.0;
+    v[2] += bad ? 1.0 : 0.0;
+  }
+  block_sum<3, NW>(v, sh);  // its barriers publish the table
+  const double pad = (double)(R * THREADS - P);
+  NormState s = norm_start(P, (double)P, target, v[0] / (double)P);
+  if (v[2] > 0.0) {
+    s.status = LYAF_STATUS_DOMAIN;
+  } else if (!(v[1] / s.P < target)) {
+    s.status = LYAF_STATUS_NOROOT;
+  } else {
+    norm_iterate<R, NW>(s, t, pad, sh);
+    s.phase = kNormPhaseExact;
+    for (int pass = 0; pass < kSmallPasses && !s.done; ++pass) {
+      double m[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        if (tid + j * THREADS < P) {
+          const double x = (double)t[j];
+          double te = exp_neg_tab(s.A * x, tab);
+          m[0] += te;
+#pragma unroll
+          for (int n = 1; n < 6; ++n) {
+            te *= x;
+            m[n] += te;
+          }
+        }
+      }
+      block_sum<6, NW>(m, sh);
+      if (tid == 0) {
+        const double tot[kNormQ] = {m[0], m[1], m[2], m[3], m[4], m[5], v[1], 0.0};
+        shs = norm_step(s, tot);
+      }
+      __syncthreads();
+      s = shs;
+      __syncthreads();
+    }
+    if (!s.done) s.status = LYAF_STATUS_NOCONV;
+  }
+  if (tid == 0) {
+    *A_dev = s.A;
+    if (s.status) atomicOr(status, (uint32_t)s.status);
+  }
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const int p = tid + j * THREADS;
+    if (p < P) {
+      const float ts = (float)(s.A * (double)t[j]);
+      tau[p] = ts;
+      if (F) F[p] = expf(-ts);
+    }
+  }
+}
+
+// S0..S5 (or, in the FP32 phase, S0..S2) at s.A and the counts, over this
+// thread's share of the pixels (thread gtid of nthr).
+__device__ __forceinline__ void norm_moments(const NormState &s, const float *__restrict__ tau,
+                                             int64_t P, int64_t gtid, int64_t nthr,
+                                             const double *tab, double (&m)[kNormQ]) {
   const bool aligned = (reinterpret_cast<uintptr_t>(tau) & 15) == 0;
-  const int64_t nthr = (int64_t)gridDim.x * blockDim.x;
-  const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t P4 = P >> 2;  // whole groups of four pixels; the tail below
-  double m[kNormQ] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < kNormQ; ++q) m[q] = 0.0;
   int nz = 0, nbad = 0;
   auto counts = [&](float t) {
     nz += (t == 0.f);
@@ -452,10 +570,6 @@ __global__ __launch_bounds__(kPassThreads) void norm_pass_kernel(
       m[2] += (double)e2;
     }
   } else {
-    __shared__ double tab[256];  // 2^(-j/256)
-    static_assert(kPassThreads >= 256, "one table entry per thread");
-    if (threadIdx.x < 256) tab[threadIdx.x] = exp_neg(threadIdx.x * (kLn2 / 256.0));
-    __syncthreads();
     const double A = s.A;
     auto px = [&](float tf, double (&acc)[6]) {  // tau^n exp(-A tau), n = 0 .. 5
       const double t = (double)tf;
@@ -482,57 +596,82 @@ __global__ __launch_bounds__(kPassThreads) void norm_pass_kernel(
   }
   m[kQZero] = (double)nz;
   m[kQBad] = (double)nbad;
-  block_sum<kNormQ, kPassWaves>(m, sh);
-  double *out = partials + out_buf * kPartStride * kMaxPartialBlocks;
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int k = 0; k < kNormQ; ++k) out[blockIdx.x * kPartStride + k] = m[k];
+}
+
+// A full pass from the state st_prev: the moments at its A, per workgroup; the
+// last workgroup to finish adds them up in a fixed order and leaves the state
+// after the step in st_out.  With alone != 0 (a batch small enough that no
+// further pass kernels follow) it makes the later passes itself, if any is
+// needed.
+__global__ __launch_bounds__(kPassThreads) void norm_pass_kernel(
+    const float *__restrict__ tau, int64_t P, double *partials, const NormState *st_prev,
+    NormState *st_out, uint32_t *arrived, uint32_t *status, int alone) {
+  __shared__ double sh[block_sum_lds(kNormQ, kPassWaves)];
+  __shared__ double tab[256];  // 2^(-j/256)
+  __shared__ NormState shs;
+  __shared__ int last;
+  if (threadIdx.x == 0) shs = *st_prev;
+  __syncthreads();
+  if (shs.done) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *st_out = shs;
+    return;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    // from LDS: the state is not held in registers across the pass
-    NormState o = shs;
-    o.pending = 0;
-    o.buf = out_buf;
-    o.nparts = gridDim.x;
-    *st_out = o;
+  static_assert(kPassThreads >= 256, "one table entry per thread");
+  if (threadIdx.x < 256) tab[threadIdx.x] = exp_neg(threadIdx.x * (kLn2 / 256.0));
+  __syncthreads();
+  double m[kNormQ];
+  norm_moments(shs, tau, P, (int64_t)blockIdx.x * kPassThreads + threadIdx.x,
+               (int64_t)gridDim.x * kPassThreads, tab, m);
+  block_sum<kNormQ, kPassWaves>(m, sh);
+  if (threadIdx.x < kWave) {  // one wave stores, waits and counts the workgroup in
+#pragma unroll
+    for (int k = 0; k < kNormQ; ++k)
+      if (threadIdx.x == k) put_shared(partials + blockIdx.x * kPartStride + k, m[k]);
+    stores_done();
+    if (threadIdx.x == 0)
+      last = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+             gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+#pragma unroll
+  for (int q = 0; q < kNormQ; ++q) m[q] = 0.0;
+  static_assert(kPassThreads >= kMaxPartialBlocks, "one partial per thread");
+  if (threadIdx.x < gridDim.x) {
+#pragma unroll
+    for (int q = 0; q < kNormQ; ++q)
+      m[q] = get_shared(partials + threadIdx.x * kPartStride + q);
+  }
+  block_sum<kNormQ, kPassWaves>(m, sh);
+  if (threadIdx.x == 0) {
+    put_shared(arrived, 0u);  // for the next pass
+    shs = norm_step(shs, m);
+  }
+  __syncthreads();
+  for (int pass = 1; alone && pass < kNormPasses && !shs.done; ++pass) {
+    norm_moments(shs, tau, P, threadIdx.x, kPassThreads, tab, m);
+    block_sum<kNormQ, kPassWaves>(m, sh);
+    if (threadIdx.x == 0) shs = norm_step(shs, m);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    *st_out = shs;
+    if (shs.status) atomicOr(status, (uint32_t)shs.status);
   }
 }
 
-// Last step (from the last pass's moments unless already converged), then
 // tau' = A tau and F = exp(-tau').
 __global__ __launch_bounds__(kNormThreads) void norm_finalise_kernel(
-    float *__restrict__ tau, float *__restrict__ F, int64_t P, const double *partials,
-    const NormState *st_prev, NormState *st_out, double *A_dev, uint32_t *status) {
-  __shared__ double sh[block_sum_lds(kNormQ, kNormWaves)];
+    float *__restrict__ tau, float *__restrict__ F, int64_t P, const NormState *st_prev,
+    double *A_dev, uint32_t *status) {
   __shared__ NormState shs;
   if (threadIdx.x == 0) shs = *st_prev;
   __syncthreads();
-  if (!shs.done) {
-    if (shs.pending) {  // no moments at A: the cap on passes was hit
-      if (threadIdx.x == 0) {
-        shs.done = 1;
-        shs.status |= LYAF_STATUS_NOCONV;
-      }
-    } else {  // one more step from the last pass's moments
-      double tot[kNormQ];
-      reduce_partials<kNormQ, kNormWaves>(partials + shs.buf * kPartStride * kMaxPartialBlocks,
-                                          shs.nparts, tot, sh);
-      if (threadIdx.x == 0) {
-        NormState s = norm_step(shs, tot);
-        // accepted: converged in the exact phase, or a domain / no-root
-        // verdict, or an FP32-phase step as small as the exact acceptance
-        const bool accepted = s.done || s.step <= kNormAcceptStep;
-        s.done = 1;
-        if (!accepted) s.status |= LYAF_STATUS_NOCONV;
-        shs = s;
-      }
-    }
-    __syncthreads();
-  }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    *st_out = shs;
     *A_dev = shs.A;
-    if (shs.status) atomicOr(status, (uint32_t)shs.status);
+    // accepted: converged in the exact phase, or a domain / no-root verdict, or
+    // an FP32-phase step as small as the exact acceptance
+    if (!shs.done && !(shs.step <= kNormAcceptStep)) atomicOr(status, LYAF_STATUS_NOCONV);
   }
   const double A = shs.A;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -572,22 +711,39 @@ static int norm_grid(int64_t pixels) {  // backward reductions
 }
 
 hipError_t launch_norm_buffers(int64_t n_pix, float *tau, float *F, double target_F,
-                               double *A_dev, double *partials, NormState *norm,
+                               double *A_dev, double *partials, NormScratch *ns,
                                uint32_t *status, hipStream_t st) {
+  // one workgroup while it is faster than the chain (16.2 against 21 us at 16384
+  // pixels, 26 by its growth at 32768), with as few waves as hold the pixels
+  if (n_pix <= 4096) {
+    hipLaunchKernelGGL((norm_small_kernel<16, 256>), dim3(1), dim3(256), 0, st, tau, F,
+                       (int)n_pix, target_F, A_dev, status);
+    return hipGetLastError();
+  }
+  if (n_pix <= 8192) {
+    hipLaunchKernelGGL((norm_small_kernel<16, 512>), dim3(1), dim3(512), 0, st, tau, F,
+                       (int)n_pix, target_F, A_dev, status);
+    return hipGetLastError();
+  }
+  if (n_pix <= kSmallPixels) {
+    hipLaunchKernelGGL((norm_small_kernel<32, 512>), dim3(1), dim3(512), 0, st, tau, F,
+                       (int)n_pix, target_F, A_dev, status);
+    return hipGetLastError();
+  }
   int64_t g = (n_pix + kPassThreads * 16 - 1) / (kPassThreads * 16);
   const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(g, kMaxPartialBlocks));
   float *sample = reinterpret_cast<float *>(partials + 2 * kPartStride * kMaxPartialBlocks);
-  hipLaunchKernelGGL(norm_gather_kernel, dim3(kSampleN / kGatherThreads), dim3(kGatherThreads),
-                     0, st, tau, n_pix, sample);
-  hipLaunchKernelGGL(norm_sample_kernel, dim3(1), dim3(kSampleThreads), 0, st, sample, n_pix,
-                     target_F, norm);
-  for (int k = 0; k < kNormPasses; ++k)
-    hipLaunchKernelGGL(norm_pass_kernel, dim3(grid), dim3(kPassThreads), 0, st, tau, n_pix,
-                       partials, norm + k, norm + k + 1, status);
+  hipLaunchKernelGGL(norm_sample_kernel, dim3(kSampleGroups), dim3(kSampleThreads), 0, st, tau,
+                     n_pix, target_F, sample, ns);
+  const bool alone = n_pix <= kAlonePixels;
+  const int passes = alone ? 1 : kNormPasses;
+  for (int k = 0; k < passes; ++k)
+    hipLaunchKernelGGL(norm_pass_kernel, dim3(k == 0 ? grid : std::min(grid, kReserveBlocks)),
+                       dim3(kPassThreads), 0, st, tau, n_pix, partials, ns->st + k,
+                       ns->st + k + 1, &ns->arrived, status, alone ? 1 : 0);
   const int fgrid = (int)std::min<int64_t>((n_pix + 4095) / 4096, 2048);
   hipLaunchKernelGGL(norm_finalise_kernel, dim3(std::max(fgrid, 1)), dim3(kNormThreads), 0, st,
-                     tau, F, n_pix, partials, norm + kNormPasses, norm + kNormPasses + 1, A_dev,
-                     status);
+                     tau, F, n_pix, ns->st + passes, A_dev, status);
   return hipGetLastError();
 }
 
@@ -609,7 +765,7 @@ hipError_t launch_norm(int64_t n_pix, float *tau, float *F, double target_F, dou
 constexpr size_t kNoAllocPartialsBytes = sizeof(double) * (size_t)kPartialsDoubles;
 constexpr size_t kNoAllocStatesOffset = (kNoAllocPartialsBytes + 255) / 256 * 256;
 constexpr size_t kNoAllocStatusOffset =
-    (kNoAllocStatesOffset + sizeof(NormState) * (kNormPasses + 2) + 255) / 256 * 256;
+    (kNoAllocStatesOffset + sizeof(NormScratch) + 255) / 256 * 256;
 constexpr size_t kNoAllocScratchBytes = kNoAllocStatusOffset + 256;
 static_assert(kNoAllocScratchBytes == kNormNoAllocScratchBytes,
               "scratch size declared in lyaf_internal.h");
@@ -644,7 +800,7 @@ hipError_t launch_norm_noalloc(int64_t n_pix, float *tau, float *F, double targe
   if (e != hipSuccess) return e;
   unsigned char *b = static_cast<unsigned char *>(base);
   double *partials = reinterpret_cast<double *>(b);
-  NormState *norm = reinterpret_cast<NormState *>(b + kNoAllocStatesOffset);
+  NormScratch *norm = reinterpret_cast<NormScratch *>(b + kNoAllocStatesOffset);
   uint32_t *st_word = status ? status : reinterpret_cast<uint32_t *>(b + kNoAllocStatusOffset);
   return launch_norm_buffers(n_pix, tau, F, target_F, A_dev, partials, norm, st_word, st);
 }

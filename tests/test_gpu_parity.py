@@ -225,6 +225,52 @@ def test_normalise_from_a_biased_sample(other):
     assert np.allclose(ts.cpu().numpy(), float(A.cpu()) * raw, rtol=1e-7, atol=0)
 
 
+@pytest.mark.parametrize("P", [1, 3, 255, 4096, 4097, 8192, 8193, 16384, 16385, (1 << 22) + 1])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_normalise_at_the_edges_of_its_kernels(P, offset):
+    """The largest and smallest batches of the one-workgroup kernels (4096, 8192
+    and 16384 pixels), of the chain whose first pass makes every pass (2^22), and
+    past it, on aligned and unaligned arrays: A against the oracle's root, tau' and
+    F from it."""
+    import torch
+    from paper_1105_4747_amd import lyaf as L
+    rng = np.random.default_rng(P)
+    raw = (np.exp(rng.normal(-0.5, 1.2, P)) + 1e-3).astype(np.float32)
+    t = torch.empty(P + offset, device="cuda:0")[offset:]
+    F = torch.full((P + offset,), float("nan"), device="cuda:0")[offset:]
+    A = torch.zeros((), device="cuda:0", dtype=torch.float64)
+    t.copy_(torch.from_numpy(raw))
+    L.status_read()
+    L.normalise_mean_flux(t, F, 0.7, A)
+    assert L.status_read() == 0
+    A_ref, _ = O.mean_flux_A(raw.astype(np.float64), 0.7)
+    a = float(A.cpu())
+    assert abs(a / A_ref - 1) <= A_REL
+    want = (a * raw.astype(np.float64)).astype(np.float32)
+    assert np.array_equal(t.cpu().numpy(), want)
+    assert np.max(np.abs(F.cpu().numpy() - np.exp(-want.astype(np.float64)))) <= 1e-6
+
+
+def test_normalise_one_workgroup_from_a_far_start():
+    """Two levels of tau four decades apart in one workgroup's batch: the iteration
+    starts far from the root and takes many steps (and the verdicts of a batch of
+    that size: no root, an invalid value)."""
+    import torch
+    from paper_1105_4747_amd import lyaf as L
+    raw = np.where(np.arange(5000) % 3 == 0, 1e-2, 1e2).astype(np.float32)
+    L.status_read()
+    ts, F, A = gpu_normalise(torch.from_numpy(raw).to("cuda:0"), 0.3)
+    assert L.status_read() == 0
+    A_ref, _ = O.mean_flux_A(raw.astype(np.float64), 0.3)
+    assert abs(float(A.cpu()) / A_ref - 1) <= A_REL
+    raw[:4000] = 0.0
+    gpu_normalise(torch.from_numpy(raw).to("cuda:0"), 0.3)
+    assert L.status_read() == L.STATUS_NOROOT
+    raw[7] = np.nan
+    gpu_normalise(torch.from_numpy(raw).to("cuda:0"), 0.3)
+    assert L.status_read() == L.STATUS_DOMAIN
+
+
 def test_normalise_root_and_domain_checks_cover_unsampled_pixels():
     """No root, or an invalid value, that only the pixels outside the sample
     reveal: the full passes report it."""
