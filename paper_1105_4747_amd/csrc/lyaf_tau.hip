@@ -87,7 +87,12 @@ __device__ __forceinline__ T block_reduce_max(T v, T *sh) {
 }
 
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void reach_kernel(Batch b) {
+// Four waves read, the fifth forms the constants (logarithms and exponentials in
+// FP64, as long a chain as the reads) meanwhile.  4096 x 4096 pixels: 19.0 us with
+// the constants in every thread by pow, 14.4 us so (67 MB, 4.7 TB/s: the reads).
+constexpr double kTempRef07 = 630.95734448019325;  // (1e4 K)^0.7
+constexpr int kReachReaders = 256;
+__global__ __launch_bounds__(kReachReaders + kWave) void reach_kernel(Batch b) {
   __shared__ float shm[8];
   __shared__ int shbad[1];
   const int64_t s = blockIdx.x;
@@ -97,80 +102,87 @@ __global__ __launch_bounds__(256) void reach_kernel(Batch b) {
   int bad = !(dv > 0.f) || !isfinite(dv) || !(T0 > 0.f) || !isfinite(T0) || !isfinite(gm);
   if (threadIdx.x == 0) shbad[0] = 0;
   __syncthreads();
-  // per-skewer constants, FP64, rounded once
+  // what every thread needs of the per-skewer constants (FP64, rounded once)
   SkewerConst K;
-  {
-    const double T0d = bad ? 1e4 : (double)T0, dvd = bad ? 1.0 : (double)dv;
-    const double sq = sqrt(T0d);
-    const double R = kSqrtLog2e / (kBeta * sq);
+  const double T0d = bad ? 1e4 : (double)T0, dvd = bad ? 1.0 : (double)dv;
+  K.B = (float)(kBeta * sqrt(T0d));
+  K.gm1 = bad ? 0.f : gm - 1.f;
+  K.inv_dv = (float)(1.0 / dvd);
+  const bool reader = threadIdx.x < kReachReaders;
+  float b_piv = 0.f;  // the Doppler parameter at the pivot
+  if (!reader) {
+    const double R = kSqrtLog2e / (kBeta * sqrt(T0d));
     K.R = (float)R;
     // a line's integral over the pixels goes as w / r, so W is rounded
     // together with the rounding of R: W / R is then off by one rounding
-    K.W = (float)((double)b.tau_ref * pow(1e4, 0.7) * dvd / (kSqrtPi * kBeta) *
-                  pow(T0d, -1.2) * ((double)K.R / R));
-    K.B = (float)(kBeta * sq);
-    K.gm1 = bad ? 0.f : gm - 1.f;
+    K.W = (float)((double)b.tau_ref * kTempRef07 * dvd / (kSqrtPi * kBeta) *
+                  exp2(-1.2 * log2(T0d)) * ((double)K.R / R));
     K.dv = (float)dvd;
-    K.inv_dv = (float)(1.0 / dvd);
     K.n = n;
+    if (isfinite(b.pivot))
+      b_piv = (float)(kBeta * sqrt(T0d) * exp2(0.5 * (double)K.gm1 * log2((double)b.pivot)) *
+                      (1.0 + 1e-6));
   }
   float mr = 0.f;
+  bool by_v = true;  // mr is the largest |v|, else the largest reach in pixels
   if (!bad && K.gm1 >= 0.f && isfinite(b.pivot)) {
-    // T rises with Delta up to the pivot, so b <= beta sqrt(T0 pivot^(gamma-1))
-    // for every source: only the velocities are read.  The kernels that stage
-    // the sources check Delta.
-    const float b_piv =
-        (float)(kBeta * sqrt((double)T0 * pow((double)b.pivot, (double)K.gm1)) * (1.0 + 1e-6));
-    float mv = 0.f;
-    const float *vp = b.vpec + off;
-    auto one = [&](const float v) {
-      mv = fmaxf(mv, fabsf(v));
-      if (!isfinite(v)) bad = 1;
-    };
-    // float4 reads from the first 16-byte boundary, four in flight per thread
-    // (a 4096-pixel skewer in one round); the few values before and after
-    // are read one by one
-    const int head =
-        (int)min<int64_t>(n, (int64_t)(((16u - (reinterpret_cast<uintptr_t>(vp) & 15u)) & 15u) >> 2));
-    const int n4 = (n - head) >> 2;
-    const float4 *v4 = reinterpret_cast<const float4 *>(vp + head);
-    const int bd = (int)blockDim.x;
-    int j = threadIdx.x;
-    for (; j + 3 * bd < n4; j += 4 * bd) {
-      float4 q[4];
+    if (reader) {
+      // T rises with Delta up to the pivot, so b <= beta sqrt(T0 pivot^(gamma-1))
+      // for every source: only the velocities are read.  The kernels that stage
+      // the sources check Delta.
+      float &mv = mr;  // the largest |v| until the reduction
+      const float *vp = b.vpec + off;
+      auto one = [&](const float v) {
+        mv = fmaxf(mv, fabsf(v));
+        if (!isfinite(v)) bad = 1;
+      };
+      // float4 reads from the first 16-byte boundary, four in flight per thread
+      // (a 4096-pixel skewer in one round); the few values before and after
+      // are read one by one
+      const int head =
+          (int)min<int64_t>(n, (int64_t)(((16u - (reinterpret_cast<uintptr_t>(vp) & 15u)) & 15u) >> 2));
+      const int n4 = (n - head) >> 2;
+      const float4 *v4 = reinterpret_cast<const float4 *>(vp + head);
+      constexpr int bd = kReachReaders;
+      int j = threadIdx.x;
+      for (; j + 3 * bd < n4; j += 4 * bd) {
+        float4 q[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) q[u] = v4[j + u * bd];
+        for (int u = 0; u < 4; ++u) q[u] = v4[j + u * bd];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        one(q[u].x);
-        one(q[u].y);
-        one(q[u].z);
-        one(q[u].w);
+        for (int u = 0; u < 4; ++u) {
+          one(q[u].x);
+          one(q[u].y);
+          one(q[u].z);
+          one(q[u].w);
+        }
       }
+      for (; j < n4; j += bd) {
+        const float4 q = v4[j];
+        one(q.x);
+        one(q.y);
+        one(q.z);
+        one(q.w);
+      }
+      if ((int)threadIdx.x < head) one(vp[threadIdx.x]);
+      for (int t = head + 4 * n4 + (int)threadIdx.x; t < n; t += bd) one(vp[t]);
     }
-    for (; j < n4; j += bd) {
-      const float4 q = v4[j];
-      one(q.x);
-      one(q.y);
-      one(q.z);
-      one(q.w);
-    }
-    if ((int)threadIdx.x < head) one(vp[threadIdx.x]);
-    for (int t = head + 4 * n4 + (int)threadIdx.x; t < n; t += bd) one(vp[t]);
-    if (n > 0) mr = (mv + b.window_k * b_piv) * K.inv_dv;
   } else {
-    for (int j = threadIdx.x; j < n; j += blockDim.x) {
+    by_v = false;
+    for (int j = threadIdx.x; reader && j < n; j += kReachReaders) {
       const float d = b.delta[off + j], v = b.vpec[off + j];
       if (!(d >= 0.f) || !isfinite(d) || !isfinite(v)) bad = 1;
       if (d > 0.f) {
-        const Src o = source_of(d, K, b.pivot);
-        mr = fmaxf(mr, (fabsf(v) + b.window_k * o.b) * K.inv_dv);
+        const float D = fmaxf(fminf(d, b.pivot), 1e-30f);
+        const float bj = K.B * fexp2(0.5f * (K.gm1 * flog2(D)));
+        mr = fmaxf(mr, (fabsf(v) + b.window_k * bj) * K.inv_dv);
       }
     }
   }
   if (bad) atomicOr(shbad, 1);
   mr = block_reduce_max(mr, shm);
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == kReachReaders) {
+    if (by_v && n > 0) mr = (mr + b.window_k * b_piv) * K.inv_dv;
     int R = n;
     if (b.window_k > 0.f && mr < 1e8f) R = min(n, (int)ceilf(mr) + 2);
     K.reach = R;
@@ -181,7 +193,8 @@ __global__ __launch_bounds__(256) void reach_kernel(Batch b) {
 
 hipError_t launch_reach(const Batch &b, hipStream_t st) {
   if (b.n_skewers == 0) return hipSuccess;
-  hipLaunchKernelGGL(reach_kernel, dim3((unsigned)b.n_skewers), dim3(256), 0, st, b);
+  hipLaunchKernelGGL(reach_kernel, dim3((unsigned)b.n_skewers), dim3(kReachReaders + kWave), 0,
+                     st, b);
   return hipGetLastError();
 }
 
