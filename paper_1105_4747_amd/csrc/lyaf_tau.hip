@@ -512,16 +512,7 @@ constexpr int kSkewFold = 16;              // terms per block sum of a run
 constexpr int kSkewPart = 8;               // block sums per partial sum
 constexpr int kSkewMargin = 12;            // staged sources beyond the reach
 constexpr int kSkewGroup = 4;              // sources per window-bounds group
-// Target-minus-source offsets as exact floats, read from LDS four at a time
-// (one broadcast read per block of four steps instead of a VALU decrement per
-// step): entry k holds kFdTop - k.  A lane run covers offsets H4 .. H4 - NS + 1
-// with H4 <= RH <= 476 and NS <= H4 + RH + M (M <= 8 targets per lane), plus
-// one block read ahead.
-constexpr int kSkewMaxRH = 476;  // staged margin limit of the windowed path
-constexpr int kFdTop = 480;
-constexpr int kFdN = 976;
-static_assert(kFdTop >= kSkewMaxRH + 4 && kFdN >= kFdTop + kSkewMaxRH + 12 && kFdN % 4 == 0,
-              "offset table covers every lane run");
+constexpr int kSkewMaxRH = 476;            // staged margin limit of the windowed path
 
 template <int NWAVES, int M = kSkewM>
 struct SkewShape {
@@ -532,21 +523,36 @@ struct SkewShape {
   static constexpr int kTile = NWAVES * kSpan;
   // staged sources: tile + 2 RH with RH <= kMaxRH, so that four 4-wave
   // workgroups fit in the 160 KiB of LDS of a compute unit (tiles reaching
-  // further take the full-sum path).  With 2048 targets the margin is smaller,
-  // the window bounds are kept per 8 sources instead of 4, and the offsets
-  // of a block of steps come from the VALU instead of a table in LDS.
+  // further take the full-sum path).  With 2048 targets the margin is smaller
+  // and the window bounds are kept per 8 sources instead of 4.
   static constexpr int kMaxRH = M == 8 ? 200 : kSkewMaxRH;
   static constexpr int kChunkS =
       kTile + 2 * kMaxRH > kChunk ? kTile + 2 * kMaxRH : kChunk;
   static constexpr int kPlane = kChunkS / 4;
   static constexpr int kGroup = M == 8 ? 8 : kSkewGroup;  // sources per window-bounds group
   static constexpr int kGroups = kChunkS / kGroup;
-  static constexpr bool kFdTable = M != 8;
-  static constexpr int kFdEntries = kFdTable ? kFdN / 4 : 1;
   static_assert(kChunkS >= kChunk, "the full-sum path stages kChunk sources");
-  static_assert((kChunkS + 4) * 16 + kGroups * 4 + kFdEntries * 16 + 16 <= 160 * 1024 / 4,
+  static_assert((kChunkS + 4) * 16 + kGroups * 4 + 16 <= 160 * 1024 / 4,
                 "four workgroups per compute unit");
 };
+
+// Highest of both 16-bit halves over the G lanes of a window-bounds group.
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_max16(uint32_t x) {
+  const uint32_t y = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(uint32_t,
+                            __builtin_elementwise_max(__builtin_bit_cast(ushort2v, x),
+                                                      __builtin_bit_cast(ushort2v, y)));
+}
+template <int G>
+__device__ __forceinline__ uint32_t group_max(uint32_t x) {
+  static_assert(G == 4 || G == 8, "a group is 4 or 8 positions");
+  x = dpp_max16<kDppXor1>(x);
+  x = dpp_max16<kDppXor2>(x);
+  if (G == 8) x = dpp_max16<kDppHalfMirror>(x);
+  return x;
+}
 
 __device__ __forceinline__ int wave_max(int x) {
 #pragma unroll
@@ -558,24 +564,31 @@ __device__ __forceinline__ int wave_max(int x) {
 // t_k = t_0 + k a (a = dv r), t_k^2 - t_(k-1)^2 = a (2 t_(k-1) + a), so
 // E_k = exp2(-t_k^2) = E_(k-1) G_(k-1) with G_0 = exp2(-a (2 t_0 + a)) and
 // G_k = G_(k-1) C, C = exp2(-2 a^2) per source: two exp2 per source and lane
-// instead of four.  These records hold (w, a, v r, C), so that
-// t_0 = (fd dv - v) r = fd a - v r is one FMA on the exact offset fd; a and
-// v r are rounded once each, which adds about u (|fd a| + |v r|) to t_0 (on the
+// instead of four.  These records hold (w, a, v r + p a, C), p = 0 .. 3 the
+// source's plane: the four steps of a block have offsets fd = F, F - 1, F - 2,
+// F - 3, so t_0 = (fd dv - v) r = F a - (v r + p a) is one FMA on the block's
+// exact offset F, which takes one subtraction per block.  a and the third entry
+// are rounded once each, which adds about u (|fd a| + |v r|) to t_0 (on the
 // 4096 x 4096 workload's fields, 1e-7 of tau at most).  The chain starts
 // at the lane's first target; it is exact to rounding unless E_0 underflows
 // while a later E_k matters, which needs a > 1.16 (|t_0| > 11.2 and
 // |t_0 + 3a| < 7.75), so a tile with any source of a > kRecMaxA (unresolved
 // lines) takes the direct form.  G_0 is clamped at 2^64, reached only where
-// E_0 = 0 (t_0 < -32 for a <= 1), so that no product is 0 * inf.
+// E_0 = 0 (t_0 < -32 for a <= 1), so that no product is 0 * inf; in a tile whose
+// largest a and reach keep every exponent below kRecMaxExp the clamp is left out.
 // With 8 targets per lane the chain reaches 7a past its start: it is exact
 // unless a > 0.49 (|t_0| > 11.2 and |t_0 + 7a| < 7.75).
 constexpr float kRecMaxA = 1.0f;
 constexpr float kRecMaxA8 = 0.45f;
+// |a (2 t_0 + a)| <= 2 a^2 (|fd - v/dv| + 1/2), |fd| <= RH + 8 and |v|/dv <= RH:
+// below 2^120, and the M - 1 factors C <= 1 only lower it
+constexpr float kRecMaxExp = 120.f;
+
+constexpr int kWalkDirect = 0, kWalkChain = 1, kWalkClamp = 2;
 
 template <int NWAVES, bool REC = false, int M = kSkewM>
 __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
-                                              float *__restrict__ tau, float4 *rec,
-                                              int *gwin, const float4 *fdt) {
+                                              float *__restrict__ tau, float4 *rec, int *gwin) {
   using SH = SkewShape<NWAVES, M>;
   constexpr int TILE = SH::kTile, NT = SH::kThreads, PL = SH::kPlane;
   const int64_t s = item.x;
@@ -594,66 +607,91 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
   }
 
   // ---- stage extended indices e_lo .. i_end + RH - 1 (position c = e - e_lo).
-  // A thread issues its global reads in rounds of 8 ahead of the arithmetic
-  // of the round.  The
-  // window bounds of every group of 4 positions (lowest ceil(lo), highest
-  // floor(hi)) meet in a DPP reduction over the 4 lanes that hold them.
+  // A thread issues its global reads in rounds of SIT ahead of the arithmetic of
+  // the round.  The window bounds of every group of positions (highest last and
+  // lowest first pixel, kept as biased 16-bit highest values) meet in a DPP
+  // reduction over the lanes that hold them.  About 45 operations a position, a
+  // tile staging 1.2 (M = 8) to 1.3 positions per target, beside the walk's 29 a
+  // step (M = 8; 32 with a subtraction per step and the clamp): with 100, by
+  // branches and IEEE minima, a plan of 4096 x 4096 pixels took 360 us, now 329,
+  // the ragged 20000-skewer one 1.78 ms, now 1.72, the 512 x 512 x 4096 box 19.6,
+  // now 18.8.
   constexpr int SIT = 8;  // positions per thread per round of reads
+  constexpr int G = SH::kGroup;
   const int e_lo = i0 - RH;
   const int cnt = (i_end - i0) + 2 * RH;
-  const float pivot = b.pivot, wk = b.window_k;
+  const float pivot = b.pivot;
+  const char *const dbase = reinterpret_cast<const char *>(b.delta + off);
+  const char *const vbase = reinterpret_cast<const char *>(b.vpec + off);
+  const bool inside = e_lo >= 0 && e_lo + cnt <= n;  // no periodic image in the tile
+  // half window in pixels: k b / dv = (k sqrt(log2 e) / dv) / r, widened by 0.01
+  // so that the rounding of the bounds drops no source at the window's edge
+  const float hk = b.window_k * (float)kSqrtLog2e * K.inv_dv;
   bool bad = false;
-  int unsafe = 0;  // REC: a source of a > kRecMaxA
-  // CHAIN_LAYOUT: records (w, a, v r, C) for the recurrence, else (w, r, v, a)
+  float a_max = 0.f;  // largest a of a line
+  // chain_layout: records (w, a, v r + p a, C) for the recurrence, else (w, r, v, a)
   auto stage = [&](const bool chain_layout) {
+    const float pf = (float)(threadIdx.x & 3);  // the plane p: c mod 4, alike for every round
+    float4 *const slot = rec + (threadIdx.x & 3) * PL + (threadIdx.x >> 2);
+    int *const gslot = gwin + threadIdx.x / G;
     for (int c0 = 0; c0 < cnt; c0 += SIT * NT) {
       float dd[SIT], vv[SIT];
 #pragma unroll
       for (int u = 0; u < SIT; ++u) {
-        const int c = c0 + threadIdx.x + u * NT;
+        const int c = c0 + (int)threadIdx.x + u * NT;
         dd[u] = 0.f;
         vv[u] = 0.f;
         if (c < cnt) {
-          const int e = e_lo + c;  // -n <= e < 2n: RH <= n/2 and i_end <= n
-          const int j = e < 0 ? e + n : (e >= n ? e - n : e);
-          dd[u] = b.delta[off + j];
-          vv[u] = b.vpec[off + j];
+          int j = e_lo + c;  // -n <= e < 2n: RH <= n/2 and i_end <= n
+          if (!inside) j = j < 0 ? j + n : (j >= n ? j - n : j);
+          const uint32_t at = (uint32_t)j << 2;  // n <= 2^24
+          dd[u] = *reinterpret_cast<const float *>(dbase + at);
+          vv[u] = *reinterpret_cast<const float *>(vbase + at);
         }
       }
 #pragma unroll
       for (int u = 0; u < SIT; ++u) {
         if (c0 + u * NT >= cnt) break;
-        const int c = c0 + threadIdx.x + u * NT;
-        bad |= (c < cnt) && bad_delta(dd[u]);
-        const Src o = source_of(dd[u], K, pivot);
-        float flo = 8191.f, fhi = -8192.f;  // no window: meets no target
+        const int c = c0 + (int)threadIdx.x + u * NT;
+        const float d = dd[u], v = vv[u];
+        bad |= bad_delta(d);  // the positions past cnt hold 0
+        // w = W Delta^2 D^(-1.2 (gamma-1)), r = R D^(-(gamma-1)/2), as source_of
+        const float x = K.gm1 * flog2(__builtin_amdgcn_fmed3f(d, 1e-30f, pivot));
+        const float w = K.W * d * d * fexp2(kTempExpW * x);
+        const float r = K.R * fexp2(kTempExpR * x);
+        const float a = K.dv * r;
+        // an empty pixel (0 or NaN here) has no line: w = 0, E = G = 1 whatever its v
+        const bool line = w > 0.f;
+        // bias so that the bounds are positive: |v / dv| + h <= RH < 2^9, c < 2^12
+        const float cc = __builtin_fmaf(v, K.inv_dv, (float)c + 4096.f);
+        const float h = __builtin_fmaf(hk, __builtin_amdgcn_rcpf(r), 0.01f);
+        const uint32_t hi = (uint32_t)(cc + h), nlo = (uint32_t)((8192.f - cc) + h);
+        uint32_t win = line ? (hi | (nlo << 16)) : 0u;
         if (c < cnt) {
-          if (o.w > 0.f) {
-            const float cc = __builtin_fmaf(vv[u], K.inv_dv, (float)c);  // line centre
-            const float h = wk * o.b * K.inv_dv;                         // half window
-            flo = fminf(fmaxf(ceilf(cc - h), -8192.f), 8191.f);
-            fhi = fminf(fmaxf(floorf(cc + h), -8192.f), 8191.f);
-          }
-          const float a = K.dv * o.r;
           if (chain_layout) {
-            unsafe |= (o.w > 0.f) && !(a <= (M == 8 ? kRecMaxA8 : kRecMaxA));
-            // (w, a = dv r, v r, C): t_0 = fd a - v r takes one FMA in the walk
-            rec[(c & 3) * PL + (c >> 2)] = make_float4(o.w, a, vv[u] * o.r, fexp2(-2.f * a * a));
+            const float C = fexp2(-2.f * a * a);
+            a_max = fmaxf(a_max, line ? a : 0.f);
+            slot[(c0 >> 2) + u * (NT / 4)] =
+                make_float4(line ? w : 0.f, line ? a : 0.f,
+                            line ? __builtin_fmaf(pf, a, v * r) : 0.f, line ? C : 1.f);
           } else {
-            rec[(c & 3) * PL + (c >> 2)] = make_float4(o.w, o.r, vv[u], a);
+            slot[(c0 >> 2) + u * (NT / 4)] = make_float4(line ? w : 0.f, r, v, a);
           }
+        } else {
+          win = 0u;
         }
-        flo = stream_min<SH::kGroup>(flo);
-        fhi = stream_max<SH::kGroup>(fhi);
-        if ((threadIdx.x & (SH::kGroup - 1)) == 0 && c < cnt)
-          gwin[c / SH::kGroup] =
-              (int)(((uint32_t)(int)fhi & 0xFFFFu) | ((uint32_t)(int)flo << 16));
+        win = group_max<G>(win);
+        if ((threadIdx.x & (G - 1)) == 0 && c < cnt) gslot[(c0 + u * NT) / G] = (int)win;
       }
     }
   };
   stage(REC);
   flag_bad_delta(b, bad);
-  const bool chain = REC ? __syncthreads_or(unsafe) == 0 : false;
+  const bool chain =
+      REC ? __syncthreads_or(!(a_max <= (M == 8 ? kRecMaxA8 : kRecMaxA))) == 0 : false;
+  const bool clamp =
+      REC ? __syncthreads_or(!(2.f * a_max * a_max * (float)(2 * RH + 9) <= kRecMaxExp)) != 0
+          : false;
   if (!REC) __syncthreads();
   if (REC && !chain) {
     // the direct form keeps the exact offset d_0 = fd dv - v (one rounding)
@@ -676,13 +714,12 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
   // above, its last position (source - lane start)
   int Hm = -(1 << 20), Em = -(1 << 20);
   {
-    constexpr int G = SH::kGroup;
     const int g_beg = (T0r - RH) / G;
     const int g_end = min((cnt + G - 1) / G, (T0r + SH::kSpan + RH + G - 1) / G);
     for (int g = g_beg + lane; g < g_end; g += kWave) {
       const int x = gwin[g];
-      const int fh = (int)(int16_t)(x & 0xFFFF) - T0r;  // floor(hi) - T0r
-      const int fl = (x >> 16) - (M - 1) - T0r;
+      const int fh = (x & 0xFFFF) - 4096 - T0r;                  // floor(hi) - T0r
+      const int fl = 4096 - (int)((uint32_t)x >> 16) - (M - 1) - T0r;  // ceil(lo) - (M - 1) - T0r
       const int lhi = min(fh >> SH::kLgM, last_lane);  // last lane whose targets the windows meet
       const int llo = max((fl + M - 1) >> SH::kLgM, 0);  // first such lane
       if (llo <= lhi) {
@@ -721,12 +758,15 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
         acc[k] = first ? q.x * e : __builtin_fmaf(q.x, e, acc[k]);
       }
     };
-    // one source against the lane's kSkewM targets by the recurrence
-    auto pair_chain = [&](const float4 q, const float fd, const bool first) {
-      const float tt0 = __builtin_fmaf(fd, q.y, -q.z);
+    // one source against the lane's kSkewM targets by the recurrence; F is the
+    // exact offset of the block's first step (the record holds the step's share)
+    auto pair_chain = [&](auto cl, const float4 q, const float F, const bool first) {
+      const float tt0 = __builtin_fmaf(F, q.y, -q.z);
       const float a = q.y;
       float E = fexp2(-(tt0 * tt0));
-      float G = fexp2(fminf(-(__builtin_fmaf(2.f, tt0, a) * a), 64.f));
+      float g = -(__builtin_fmaf(2.f, tt0, a) * a);
+      if (decltype(cl)::value) g = fminf(g, 64.f);
+      float G = fexp2(g);
 #pragma unroll
       for (int k = 0; k < M; ++k) {
         if (k > 0) {
@@ -736,14 +776,16 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
         acc[k] = first ? q.x * E : __builtin_fmaf(q.x, E, acc[k]);
       }
     };
-    // CH: the recurrence (decided per tile, so the whole walk takes one form
-    // and its sums stay in the same registers from block to block)
-    auto block = [&](auto ch, const float4 (&q)[5], const bool first) {
-      if constexpr (decltype(ch)::value) {
-        pair_chain(q[0], q[4].x, first);
-        pair_chain(q[1], q[4].y, false);
-        pair_chain(q[2], q[4].z, false);
-        pair_chain(q[3], q[4].w, false);
+    // WALK: the direct form, the recurrence, or the recurrence without the clamp
+    // (decided per tile, so the whole walk takes one form and its sums stay in
+    // the same registers from block to block)
+    auto block = [&](auto wk, const float4 (&q)[4], const float F, const bool first) {
+      if constexpr (decltype(wk)::value != kWalkDirect) {
+        const std::integral_constant<bool, decltype(wk)::value == kWalkClamp> cl;
+        pair_chain(cl, q[0], F, first);
+        pair_chain(cl, q[1], F, false);
+        pair_chain(cl, q[2], F, false);
+        pair_chain(cl, q[3], F, false);
         // the block's 8 exps, one per 7 (M = 4) or 18 (M = 8: the last ones
         // early, measured best) other VALU instructions
 #pragma unroll
@@ -753,10 +795,10 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
         }
         return;
       } else {
-        pair_step(q[0], q[4].x, first);
-        pair_step(q[1], q[4].y, false);
-        pair_step(q[2], q[4].z, false);
-        pair_step(q[3], q[4].w, false);
+        pair_step(q[0], F, first);
+        pair_step(q[1], F - 1.f, false);
+        pair_step(q[2], F - 2.f, false);
+        pair_step(q[3], F - 3.f, false);
         // the transcendental unit runs beside the other VALU work: the
         // block's 4 M exps are spread one per four other VALU instructions,
         // so that they do not queue behind one another
@@ -783,66 +825,57 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
     // column of the run's first source in every plane; a block is 4 steps
     // (one record from each plane), a run of kSkewFold steps is 4 blocks
     const float4 *p = rec + ((T0r - H4) >> 2) + lane * (M / 4);
-    const float4 *pf = fdt + ((kFdTop - H4) >> 2);  // offsets H4 - 4 blk - (0..3)
-    auto load = [&](float4 (&q)[5], const int blk) {
+    auto load = [&](float4 (&q)[4], const int blk) {
       q[0] = p[blk];
       q[1] = p[blk + PL];
       q[2] = p[blk + 2 * PL];
       q[3] = p[blk + 3 * PL];
-      if constexpr (SH::kFdTable) {
-        q[4] = pf[blk];
-      } else {
-        const float f = (float)(H4 - 4 * blk);
-        q[4] = make_float4(f, f - 1.f, f - 2.f, f - 3.f);
-      }
     };
     const int nblk = NS >> 2;
     static_assert(kSkewFold == 4 * 4, "the walk folds after four blocks of four steps");
     // the next block's records are read while this one is evaluated; the read
     // past the last block stays inside the staged array
-    auto walk = [&](auto ch) {
-      float4 qa[5], qb[5];
+    auto walk = [&](auto wk) {
+      float4 qa[4], qb[4];
+      float F = (float)H4;  // target minus source at the block's first step, exact
       load(qa, 0);
       int blk = 0;
       for (; blk + 4 <= nblk; blk += 4) {
         load(qb, blk + 1);
-        block(ch, qa, true);
+        block(wk, qa, F, true);
         load(qa, blk + 2);
-        block(ch, qb, false);
+        block(wk, qb, F - 4.f, false);
         load(qb, blk + 3);
-        block(ch, qa, false);
+        block(wk, qa, F - 8.f, false);
         load(qa, blk + 4);
-        block(ch, qb, false);
+        block(wk, qb, F - 12.f, false);
+        F -= 16.f;
         fold();
       }
       for (; blk < nblk; ++blk) {
         load(qb, blk + 1);
-        block(ch, qa, true);
+        block(wk, qa, F, true);
+        F -= 4.f;
         fold();
 #pragma unroll
-        for (int k = 0; k < 5; ++k) qa[k] = qb[k];
+        for (int k = 0; k < 4; ++k) qa[k] = qb[k];
       }
     };
     if constexpr (REC) {
-      if (chain)
-        walk(std::true_type{});
+      if (!chain)
+        walk(std::integral_constant<int, kWalkDirect>{});
+      else if (clamp)
+        walk(std::integral_constant<int, kWalkClamp>{});
       else
-        walk(std::false_type{});
+        walk(std::integral_constant<int, kWalkChain>{});
     } else {
-      walk(std::false_type{});
+      walk(std::integral_constant<int, kWalkDirect>{});
     }
   }
 #pragma unroll
   for (int k = 0; k < M; ++k) {
     const int i = i_l + k;
     if (i < i_end) tau[off + i] = sum[k] + part[k];
-  }
-}
-
-__device__ __forceinline__ void fill_offset_table(float4 *fdt) {
-  for (int k = threadIdx.x; k < kFdN / 4; k += blockDim.x) {
-    const float t = (float)(kFdTop - 4 * k);
-    fdt[k] = make_float4(t, t - 1.f, t - 2.f, t - 3.f);
   }
 }
 
@@ -853,9 +886,7 @@ __global__ __launch_bounds__(NWAVES * kWave) void tau_skew_kernel(Batch b,
   using SH = SkewShape<NWAVES, M>;
   __shared__ float4 rec[SH::kChunkS + 4];
   __shared__ int gwin[SH::kGroups];
-  __shared__ float4 fdt[SH::kFdEntries];
-  if (SH::kFdTable) fill_offset_table(fdt);  // published by the barrier after staging
-  tau_skew_tile<NWAVES, REC, M>(b, items[blockIdx.x], tau, rec, gwin, fdt);
+  tau_skew_tile<NWAVES, REC, M>(b, items[blockIdx.x], tau, rec, gwin);
 }
 
 // 4-wave form: at most 128 VGPRs, so that four waves share a SIMD as in the
@@ -868,9 +899,7 @@ __attribute__((amdgpu_waves_per_eu(NWAVES == 4 ? 4 : 3))) void tau_skew_persiste
   using SH = SkewShape<NWAVES, M>;
   __shared__ float4 rec[SH::kChunkS + 4];
   __shared__ int gwin[SH::kGroups];
-  __shared__ float4 fdt[SH::kFdEntries];
   __shared__ int next;
-  if (SH::kFdTable) fill_offset_table(fdt);
   for (;;) {
     __syncthreads();  // the previous item is done with LDS and `next`
     if (threadIdx.x == 0) next = (int)atomicAdd(queue, (unsigned)kQueueGrab);
@@ -880,7 +909,7 @@ __attribute__((amdgpu_waves_per_eu(NWAVES == 4 ? 4 : 3))) void tau_skew_persiste
     const int last = min(first + kQueueGrab, n_items);
     for (int idx = first; idx < last; ++idx) {
       if (idx > first) __syncthreads();  // the previous item is done with LDS
-      tau_skew_tile<NWAVES, REC, M>(b, items[idx], tau, rec, gwin, fdt);
+      tau_skew_tile<NWAVES, REC, M>(b, items[idx], tau, rec, gwin);
     }
   }
 }

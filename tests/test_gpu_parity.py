@@ -118,6 +118,40 @@ def test_tau_recurrence_shape_near_and_past_its_limit(shape):
     assert_tau_close(got, oracle_tau(w), f"narrow lines shape {shape}")
 
 
+@pytest.mark.parametrize("shape,v_max,a", [(4, 400.0, (0.45, 0.47, 0.48, 0.5, 0.7)),
+                                           (5, 500.0, (0.37, 0.38, 0.39, 0.40, 0.44))])
+def test_tau_recurrence_with_and_without_its_clamp(shape, v_max, a):
+    """Large velocities at narrow lines: the first two skewers' exponents stay below
+    2^120 (2 a^2 (2 RH + 9) with the staged margin RH), so their tiles leave the
+    clamp of G_0 out; the others' do not."""
+    from paper_1105_4747_amd import lyaf as L
+    w = fields.small_workload(n_skewers=5, n_pix=6000, seed=43, dv=4.0, sigma_lnD=1.2)
+    w.gamma[:] = 1.0
+    b = 4.0 * np.sqrt(np.log2(np.e)) / np.array(a)
+    w.T0[:] = ((b / 0.12845065404917816) ** 2).astype(np.float32)
+    w.vpec *= v_max / np.abs(w.vpec).max()
+    print(f"case: clamp shape={shape} v_max={v_max}", flush=True)
+    got = gpu_tau(w, flags=L.FLAG_SHAPE(shape)).cpu().numpy()
+    assert_tau_close(got, oracle_tau(w), f"clamp shape {shape}")
+
+
+@pytest.mark.parametrize("shape", [0, 4, 5])
+def test_tau_empty_pixels_of_any_velocity(shape):
+    """Empty pixels (Delta = 0) contribute nothing whatever their velocity, which
+    the reach of a gamma < 1 skewer does not cover; single and adjacent ones, at
+    the skewer's ends, next to strong lines."""
+    from paper_1105_4747_amd import lyaf as L
+    w = fields.small_workload(n_skewers=2, n_pix=5000, seed=44, gamma=0.9)
+    empty = np.r_[0:3, 70, 1023:1026, 2000:2300, 4999]
+    for s in range(2):
+        w.delta[s * 5000 + empty] = 0.0
+        w.vpec[s * 5000 + empty] = 3e5
+    print(f"case: empty pixels shape={shape}", flush=True)
+    got = gpu_tau(w, flags=L.FLAG_SHAPE(shape)).cpu().numpy()
+    assert L.status_read() == 0
+    assert_tau_close(got, oracle_tau(w), f"empty pixels shape {shape}")
+
+
 def test_tau_is_linear_in_tau_ref_and_deterministic(c1):
     a = gpu_tau(c1).cpu().numpy()
     b = gpu_tau(c1).cpu().numpy()
