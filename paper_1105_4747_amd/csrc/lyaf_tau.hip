@@ -92,6 +92,8 @@ __device__ __forceinline__ T block_reduce_max(T v, T *sh) {
 // the constants in every thread by pow, 14.4 us so (67 MB, 4.7 TB/s: the reads).
 constexpr double kTempRef07 = 630.95734448019325;  // (1e4 K)^0.7
 constexpr int kReachReaders = 256;
+constexpr int kSkewMargin = 12;            // staged sources beyond the reach
+
 __global__ __launch_bounds__(kReachReaders + kWave) void reach_kernel(Batch b) {
   __shared__ float shm[8];
   __shared__ int shbad[1];
@@ -124,16 +126,16 @@ __global__ __launch_bounds__(kReachReaders + kWave) void reach_kernel(Batch b) {
                       (1.0 + 1e-6));
   }
   float mr = 0.f;
-  bool by_v = true;  // mr is the largest |v|, else the largest reach in pixels
+  float mv = 0.f, mb = 0.f;  // largest |v| and b
+  bool by_v = true;          // mr is the largest |v|, else the largest reach in pixels
   if (!bad && K.gm1 >= 0.f && isfinite(b.pivot)) {
     if (reader) {
       // T rises with Delta up to the pivot, so b <= beta sqrt(T0 pivot^(gamma-1))
       // for every source: only the velocities are read.  The kernels that stage
       // the sources check Delta.
-      float &mv = mr;  // the largest |v| until the reduction
       const float *vp = b.vpec + off;
       auto one = [&](const float v) {
-        mv = fmaxf(mv, fabsf(v));
+        mr = fmaxf(mr, fabsf(v));
         if (!isfinite(v)) bad = 1;
       };
       // float4 reads from the first 16-byte boundary, four in flight per thread
@@ -176,16 +178,32 @@ __global__ __launch_bounds__(kReachReaders + kWave) void reach_kernel(Batch b) {
         const float D = fmaxf(fminf(d, b.pivot), 1e-30f);
         const float bj = K.B * fexp2(0.5f * (K.gm1 * flog2(D)));
         mr = fmaxf(mr, (fabsf(v) + b.window_k * bj) * K.inv_dv);
+        mv = fmaxf(mv, fabsf(v));
+        mb = fmaxf(mb, bj);
       }
     }
   }
   if (bad) atomicOr(shbad, 1);
   mr = block_reduce_max(mr, shm);
+  if (!by_v) {
+    __syncthreads();  // shm is free again
+    mv = block_reduce_max(mv, shm);
+    __syncthreads();
+    mb = block_reduce_max(mb, shm);
+  }
   if (threadIdx.x == kReachReaders) {
-    if (by_v && n > 0) mr = (mr + b.window_k * b_piv) * K.inv_dv;
-    int R = n;
-    if (b.window_k > 0.f && mr < 1e8f) R = min(n, (int)ceilf(mr) + 2);
-    K.reach = R;
+    if (by_v) {
+      mv = mr;
+      mb = b_piv;
+      if (n > 0) mr = (mr + b.window_k * b_piv) * K.inv_dv;
+    }
+    const auto pixels = [&](float x) { return x < 1e8f ? min(n, (int)ceilf(x) + 2) : n; };
+    K.reach = b.window_k > 0.f ? pixels(mr) : n;
+    // a window of less than 6 b ends where the terms matter: such boxes are windowed
+    // only where the reach allows it, and summed whole at window_k = 0
+    K.half = b.window_k >= 6.f ? pixels(b.window_k * mb * K.inv_dv)
+                               : (b.window_k > 0.f ? min(n, K.reach + kSkewMargin + 3) : n);
+    K.vpx = pixels(mv * K.inv_dv);
     b.skc[s] = K;
     if (shbad[0]) atomicOr(b.status, LYAF_STATUS_DOMAIN);
   }
@@ -510,7 +528,6 @@ __global__ void reset_queue_kernel(unsigned int *queue) { *queue = 0u; }
 constexpr int kSkewM = 4;                  // targets per lane
 constexpr int kSkewFold = 16;              // terms per block sum of a run
 constexpr int kSkewPart = 8;               // block sums per partial sum
-constexpr int kSkewMargin = 12;            // staged sources beyond the reach
 constexpr int kSkewGroup = 4;              // sources per window-bounds group
 constexpr int kSkewMaxRH = 476;            // staged margin limit of the windowed path
 
@@ -600,8 +617,12 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
   // staged margin on each side, a multiple of 4 so that lane runs start on a
   // plane-0 column
   const int RH = (K.reach + kSkewMargin + 3) & ~3;
-  if (TILE + 2 * RH > SH::kChunkS || RH > SH::kMaxRH || 2 * RH + 8 > n) {
-    // the window covers the box, or reaches beyond the staged margin
+  if (TILE + 2 * RH > SH::kChunkS || RH > SH::kMaxRH || 2 * K.half + 8 > n || K.reach >= n) {
+    // the window covers the box, or reaches beyond the staged margin.  A box of at
+    // least two half windows of 6 b or more takes the windowed path if its velocities
+    // reach less than the box: a source staged together with its images counts once, as
+    // the images are then more than 6 b from any target its own window meets (their
+    // terms are below exp(-36)).
     for (int q = i0; q < i_end; q += NT) full_sum_tile<true>(b, K, off, q, tau, rec);
     return;
   }
@@ -642,8 +663,11 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
         dd[u] = 0.f;
         vv[u] = 0.f;
         if (c < cnt) {
-          int j = e_lo + c;  // -n <= e < 2n: RH <= n/2 and i_end <= n
-          if (!inside) j = j < 0 ? j + n : (j >= n ? j - n : j);
+          int j = e_lo + c;
+          if (!inside) {
+            while (j < 0) j += n;
+            while (j >= n) j -= n;
+          }
           const uint32_t at = (uint32_t)j << 2;  // n <= 2^24
           dd[u] = *reinterpret_cast<const float *>(dbase + at);
           vv[u] = *reinterpret_cast<const float *>(vbase + at);

@@ -152,6 +152,26 @@ def test_tau_empty_pixels_of_any_velocity(shape):
     assert_tau_close(got, oracle_tau(w), f"empty pixels shape {shape}")
 
 
+@pytest.mark.parametrize("shape", [0, 4, 5])
+@pytest.mark.parametrize("window_k", [6.0, 9.0])
+def test_tau_short_boxes_of_large_velocities(shape, window_k):
+    """Boxes around two half windows (k b / dv, +- a few pixels) whose velocities
+    reach from a third of the box to several boxes: a source is staged beside its
+    own images, or the tile sums every source."""
+    from paper_1105_4747_amd import lyaf as L
+    dv, b, T0 = 4.0, 16.0, (16.0 / 0.12845065404917816) ** 2
+    half = int(np.ceil(window_k * b / dv)) + 2
+    for n in (2 * half + 7, 2 * half + 8, 2 * half + 9, 3 * half):
+        w = fields.small_workload(n_skewers=6, n_pix=n, seed=45, dv=dv, T0=T0, gamma=1.0,
+                                  window_k=window_k)
+        reach = np.array([0.3, 0.6, 0.98, 1.02, 2.5, 7.3]) * n * dv
+        v = w.vpec.reshape(6, n)
+        v *= (reach / np.abs(v).max(axis=1))[:, None].astype(np.float32)
+        print(f"case: short box n={n} shape={shape} k={window_k}", flush=True)
+        got = gpu_tau(w, flags=L.FLAG_SHAPE(shape)).cpu().numpy()
+        assert_tau_close(got, oracle_tau(w), f"short box n={n} shape {shape}")
+
+
 def test_tau_is_linear_in_tau_ref_and_deterministic(c1):
     a = gpu_tau(c1).cpu().numpy()
     b = gpu_tau(c1).cpu().numpy()
