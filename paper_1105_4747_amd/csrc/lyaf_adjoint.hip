@@ -10,18 +10,29 @@
 //   dL/dT0 = sum_j Q_j / T0,   dL/dgamma = sum_j Q_j ln D_j.
 // The 1.2 is the temperature exponent of w (n_HI ~ T^-0.7 over b ~ T^0.5).
 //
-// One workgroup per 256-source pass; the target gradients g_i within reach are
-// staged in LDS.  Each lane owns one source and walks its own run of targets,
-// four per step, shifted with its source: the run of lane l starts at j_l - H
-// and has NS targets, H and NS uniform over the wave (from the lanes' window
-// bounds), so target minus source is the same on every lane and the four
-// targets of a step share t_k = t_0 + k a (a = dv r).  Short or wide skewers
-// sum over every target with the minimal image chosen per pair.  The three
-// per-source sums are FP32 blocks of 16 terms folded with Kahan compensation
-// (S1 is a signed sum that cancels across the line centre), Q_j is formed in
-// FP64 from them, and the per-skewer T0/gamma terms are summed in FP64 per
-// workgroup and then per skewer in a fixed order.
+// One workgroup per 512 sources; the target gradients g_i within reach are staged
+// in LDS.  Each lane owns one source at a time and walks its own run of targets,
+// which starts at the target nearest its line centre less H, H uniform over the
+// wave (the lanes' largest half window): target less centre is the same integer
+// m on every lane, t = m a + t_c with a = dv r and |t_c| <= a / 2, and the run is
+// no longer than the widest of 64 neighbouring lines.  Per block of eight targets
+// the Gaussian follows a product recurrence outwards from the block's middle
+// (three exp2; the tau kernel's, from one end with two, put 1e-7 more on the
+// velocity gradients), and the sums are moments about that middle, B_n =
+// sum_k k^n g E, folded every 16 targets into FP64 moments in m, from which
+//   sum g E t = a M1 + t_c M0,  sum g E t^2 = a^2 M2 + 2 a t_c M1 + t_c^2 M0
+// (M1 is signed and cancels across the line centre).  A wave with a line too
+// narrow for the recurrence evaluates every exp2.  Short or wide skewers sum
+// over every target with the minimal image chosen per pair.  The per-skewer
+// T0/gamma terms are summed in FP64 per workgroup and then per skewer in a fixed
+// order.  Bound by VALU issue: 4096 skewers of 2048 pixels at 2 km/s 246 -> 220 us
+// (6.9 operations a visited pair, where the Kahan-folded direct form took 9), 37
+// ragged ones of up to 8192 31 -> 21 us.  w and r are rounded once, from FP64: the
+// gradients' errors against 64 bits stay at or below the direct form's (velocity
+// 1.75e-7 -> 1.67e-7, density 1.15e-7 -> 1.15e-7 at 2 km/s).
 #include <math.h>
+
+#include <type_traits>
 
 #include "lyaf_internal.h"
 
@@ -31,181 +42,266 @@ __device__ __forceinline__ float aexp2(float x) { return __builtin_amdgcn_exp2f(
 __device__ __forceinline__ float alog2(float x) { return __builtin_amdgcn_logf(x); }
 
 constexpr int kAdjThreads = 256;
-constexpr int kAdjTile = 256;  // sources per pass of the workgroup (one per thread)
-constexpr int kAdjMargin = 12; // staged targets beyond the reach
-
-// Compensated sum of FP32 blocks: sum + comp carries the running total.
-struct KahanSum {
-  float sum = 0.f, comp = 0.f;
-  __device__ __forceinline__ void add(const float blk) {
-    const float y = blk - comp;
-    const float t = sum + y;
-    comp = (t - sum) - y;
-    sum = t;
-  }
-  __device__ __forceinline__ float value() const { return sum - comp; }
-};
+constexpr int kAdjPasses = kTauTile / kAdjThreads;  // sources per thread of an item
+constexpr int kAdjChunk = 2048;                     // targets staged in LDS at once
+constexpr int kAdjMargin = 12;                      // staged targets beyond the reach
+constexpr float kAdjMaxA = 0.25f;                   // coarsest grid of the recurrence
+constexpr float kAdjMaxExp = 120.f;                 // exponent of the recurrence's ratio
 
 __device__ __forceinline__ int adj_wave_max(int x) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) x = max(x, __shfl_xor(x, m));
   return x;
 }
-static_assert(kTauTile % kAdjTile == 0, "work items hold whole adjoint passes");
+static_assert(kTauTile % kAdjThreads == 0, "work items hold whole adjoint passes");
 
-// One pass: sources j0 .. j0+255 of skewer s (one per thread).  Adds this
-// thread's Q_j and Q_j ln D_j to q_T0 and q_gam.
-__device__ void adjoint_pass(const Batch &b, const SkewerConst &K, int64_t off, int j0,
-                             const float *__restrict__ g, float *__restrict__ gdelta,
-                             float *__restrict__ gvpec, float *gl, double &q_T0,
-                             double &q_gam) {
-  const int n = K.n;
-  const int R = K.reach;
-  const int j = j0 + (int)threadIdx.x;
-  const bool valid = j < n;
+// 1 / x to about 1e-15 relative, x normal (the hardware's estimate and two Newton
+// steps).
+__device__ __forceinline__ double adj_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
 
-  // this lane's source
-  float delta = 0.f, v = 0.f, w = 0.f, r = K.R, bj = 0.f, l2D = 0.f;
-  if (valid) {
-    delta = b.delta[off + j];
-    v = b.vpec[off + j];
-    if (delta > 0.f) {
-      const float D = fmaxf(fminf(delta, b.pivot), 1e-30f);
-      l2D = alog2(D);
-      const float x = K.gm1 * l2D;
-      w = K.W * delta * delta * aexp2(kTempExpW * x);
-      r = K.R * aexp2(kTempExpR * x);
-      bj = K.B * aexp2(0.5f * x);
-    }
+// A source: w, r, a = dv r, its gradient of tau's three sums.
+__device__ __forceinline__ double adj_scaled_exp2(float c, double y) {
+  const float yh = (float)y;
+  const double e = (double)c * (double)aexp2(yh);
+  return fma(e, kLn2 * (y - (double)yh), e);
+}
+struct AdjSource {
+  float delta, v, w, r, l2D;
+};
+__device__ __forceinline__ AdjSource adj_source(const SkewerConst &K, float pivot, float delta,
+                                                float v) {
+  AdjSource s = {delta, v, 0.f, K.R, 0.f};
+  if (delta > 0.f) {
+    const float D = fmaxf(fminf(delta, pivot), 1e-30f);
+    s.l2D = alog2(D);
+    const double x = (double)K.gm1 * (double)s.l2D;
+    s.w = (float)((double)delta * (double)delta * adj_scaled_exp2(K.W, kTempExpW * x));
+    s.r = (float)adj_scaled_exp2(K.R, kTempExpR * x);
   }
-  // an invalid density sets the sticky domain bit (the reach pass may not
-  // have read Delta)
-  if (__any(valid && (!(delta >= 0.f) || !isfinite(delta))) && (threadIdx.x & 63) == 0)
-    atomicOr(b.status, LYAF_STATUS_DOMAIN);
-  const float dv = K.dv;
-  // sums of g E, g E t, g E t^2: blocks of 16 terms folded into Kahan sums
-  float S0 = 0.f, S1 = 0.f, S2 = 0.f;
-  KahanSum K0, K1, K2;
-  auto fold = [&]() {
-    K0.add(S0);
-    K1.add(S1);
-    K2.add(S2);
-    S0 = S1 = S2 = 0.f;
-  };
+  return s;
+}
 
-  // staged margin beyond the reach (window bounds are rounded outwards)
-  const int RH = (R + kAdjMargin + 3) & ~3;
-  const int j_end = min(j0 + kAdjTile, n);
-  const int e_lo = j0 - RH;
-  const int cnt = (j_end - j0) + 2 * RH;
-  __syncthreads();  // gl is reused across passes
-  if (kAdjTile + 2 * RH + 8 <= kChunk && 2 * RH + 8 <= n) {
-    // windowed: targets e_lo .. e_lo + cnt - 1 (extended, periodic)
-    for (int c = threadIdx.x; c < cnt; c += kAdjThreads) {
-      const int e = e_lo + c;  // -n <= e < 2n
-      const int i = e < 0 ? e + n : (e >= n ? e - n : e);
-      gl[c] = g[off + i];
-    }
-    __syncthreads();
-    // this lane's window in targets: j - Hl .. j + El
-    int Hl = -(1 << 20), El = -(1 << 20);
-    if (w > 0.f) {
-      const float cc = __builtin_fmaf(v, K.inv_dv, (float)(j - j0));  // line centre
-      const float h = b.window_k * bj * K.inv_dv;
-      const float lo = fminf(fmaxf(ceilf(cc - h), -8192.f), 8191.f);
-      const float hi = fminf(fmaxf(floorf(cc + h), -8192.f), 8191.f);
-      Hl = (j - j0) - (int)lo;
-      El = (int)hi - (j - j0);
-    }
-    const int H = min(__builtin_amdgcn_readfirstlane(adj_wave_max(Hl)), RH);
-    const int E = __builtin_amdgcn_readfirstlane(adj_wave_max(El));
-    if (E >= -(1 << 19)) {
-      // NS <= H + RH - 8 keeps every read inside the staged targets
-      const int NS = min((H + E + 1 + 3) & ~3, H + RH - 8);
-      const float *gp = gl + (j - j0) + RH - H;  // run start of this lane
-      const float a = dv * r;
-      float fd = (float)(-H);  // target - source at the step's first target, exact
-      for (int st = 0; st < NS; st += 4) {
-        const float gi[4] = {gp[st], gp[st + 1], gp[st + 2], gp[st + 3]};
-        const float t0 = __builtin_fmaf(fd, dv, -v) * r;
+// Windowed sums of one source over the staged targets (gl[p] the gradient at the
+// target nearest its centre): S0, S1, S2 = sum g E t^n.  Blocks of eight targets
+// m = 8 i - 4 .. 8 i + 3, the line's centre in the block i = 0, whose moments are
+// then taken about the centre itself: a narrow line's M1 and M2 are not
+// differences of moments about a far target.
+__device__ __forceinline__ void adjoint_run(const float *gl, int p, int H, float a, float tc,
+                                            bool chain, double &S0, double &S1, double &S2) {
+  double M0 = 0.0, M1 = 0.0, M2 = 0.0;
+  const int left = (H + 3) >> 3, right = (H + 4) >> 3;  // blocks beside the central one
+  const float C = aexp2(-2.f * a * a);
+  float B0, B1, B2;  // moments about the first block's middle, up to two blocks
+  // the eight targets around m = 8 i, added to the moments about 8 (i - O)
+  const auto block = [&](auto form, auto O, int i) {
+    const float *g8 = gl + p + 8 * i - 4;
+    const float fi = (float)(8 * i);
+    float e[8];
+    if constexpr (decltype(form)::value) {
+      // outwards from the middle, so that no factor is raised far: E_(k+1) = E_k U_k
+      // and E_(k-1) = E_k D_k, both ratios falling by C per step
+      const float tm = __builtin_fmaf(fi, a, tc);
+      e[4] = aexp2(-(tm * tm));
+      float U = aexp2(-(__builtin_fmaf(2.f, tm, a) * a));
+      float D = aexp2(__builtin_fmaf(2.f, tm, -a) * a);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float t = (k == 0) ? t0 : __builtin_fmaf((float)k, a, t0);
-          const float tt = t * t;
-          const float gE = gi[k] * aexp2(-tt);
-          S0 += gE;
-          S1 = __builtin_fmaf(gE, t, S1);
-          S2 = __builtin_fmaf(gE, tt, S2);
-        }
-        fd += 4.f;
-        if ((st & 12) == 12) fold();  // every 4 steps (16 terms); st is wave-uniform
+      for (int k = 5; k < 8; ++k) {
+        e[k] = e[k - 1] * U;
+        if (k < 7) U *= C;
+      }
+#pragma unroll
+      for (int k = 3; k >= 0; --k) {
+        e[k] = e[k + 1] * D;
+        if (k > 0) D *= C;
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float t = __builtin_fmaf(fi + (float)(k - 4), a, tc);
+        e[k] = aexp2(-(t * t));
       }
     }
-  } else {
-    // every target, minimal image per pair
-    const float nf = (float)n;
-    const float invV = 1.f / (nf * dv);
-    for (int c0 = 0; c0 < n; c0 += kChunk) {
-      const int cn = min(kChunk, n - c0);
-      __syncthreads();
-      for (int c = threadIdx.x; c < cn; c += kAdjThreads) gl[c] = g[off + c0 + c];
-      __syncthreads();
-      float fd = (float)(c0 - j);
-      for (int c = 0; c < cn; ++c) {
-        const float gi = gl[c];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const float gE = g8[k] * e[k];
+      constexpr float o = 8.f * (float)decltype(O)::value - 4.f;
+      const float kk = o + (float)k;
+      if (decltype(O)::value == 0 && k == 0) {
+        B0 = gE;
+        B1 = kk * gE;
+        B2 = kk * kk * gE;
+      } else {
+        B0 += gE;
+        if (kk != 0.f) {
+          B1 = __builtin_fmaf(gE, kk, B1);
+          B2 = __builtin_fmaf(gE, kk * kk, B2);
+        }
+      }
+    }
+  };
+  const auto fold = [&](int i) {  // moments about 8 i, to moments about the centre
+    const double b0 = B0, b1 = B1, md = (double)(8 * i);
+    M0 += b0;
+    M1 += fma(md, b0, b1);
+    M2 += fma(md, fma(md, b0, 2.0 * b1), (double)B2);
+  };
+  const std::integral_constant<int, 0> first;
+  const std::integral_constant<int, 1> second;
+  const auto run = [&](auto form) {
+    int i = -left;
+    if (left & 1) {  // the central block is then the first of a pair
+      block(form, first, i);
+      fold(i);
+      ++i;
+    }
+    for (; i < right; i += 2) {
+      block(form, first, i);
+      block(form, second, i + 1);
+      fold(i);
+    }
+    if (i == right) {
+      block(form, first, i);
+      fold(i);
+    }
+  };
+  if (chain)
+    run(std::true_type{});
+  else
+    run(std::false_type{});
+  const double ad = a, td = tc;
+  S0 = M0;
+  S1 = fma(ad, M1, td * M0);
+  S2 = fma(ad * ad, M2, td * fma(2.0 * ad, M1, td * M0));
+}
+
+// The same over every target, the minimal image chosen per pair; gl is filled
+// chunk by chunk.
+__device__ void adjoint_full(const SkewerConst &K, const float *__restrict__ g, float *gl, int j,
+                             float v, float r, double &S0, double &S1, double &S2) {
+  const int n = K.n;
+  const float dv = K.dv, nf = (float)n;
+  const float invV = 1.f / (nf * dv);
+  S0 = S1 = S2 = 0.0;
+  for (int c0 = 0; c0 < n; c0 += kAdjChunk) {
+    const int cn = min(kAdjChunk, n - c0);
+    __syncthreads();
+    for (int c = threadIdx.x; c < cn; c += kAdjThreads) gl[c] = g[c0 + c];
+    __syncthreads();
+    for (int c16 = 0; c16 < cn; c16 += 16) {
+      float s0 = 0.f, s1 = 0.f, s2 = 0.f;
+      const float fj = (float)(c0 + c16 - j);
+      const auto pair = [&](int k) {
+        const float fd = fj + (float)k;
         const float d0 = __builtin_fmaf(fd, dv, -v);
         const float img = floorf(__builtin_fmaf(d0, invV, 0.5f));
         const float d = __builtin_fmaf(__builtin_fmaf(img, -nf, fd), dv, -v);
         const float t = d * r;
-        const float gE = gi * aexp2(-(t * t));
+        const float gE = gl[c16 + k] * aexp2(-(t * t));
         const float gEt = gE * t;
-        S0 += gE;
-        S1 += gEt;
-        S2 = __builtin_fmaf(gEt, t, S2);
-        fd += 1.f;
-        if ((c & 15) == 15) fold();
+        s0 += gE;
+        s1 += gEt;
+        s2 = __builtin_fmaf(gEt, t, s2);
+      };
+      if (c16 + 16 <= cn) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) pair(k);
+      } else {
+#pragma unroll 1
+        for (int k = 0; k < cn - c16; ++k) pair(k);
       }
-      fold();
+      S0 += (double)s0;
+      S1 += (double)s1;
+      S2 += (double)s2;
     }
-  }
-  fold();
-
-  // per-source outputs (t = x sqrt(log2 e): x = t / sqrt(log2 e))
-  if (valid) {
-    float gd = 0.f, gv = 0.f;
-    if (w > 0.f) {
-      const float inv_s = (float)(1.0 / kSqrtLog2e);
-      const float s0 = w * K0.value();
-      const float s1 = w * K1.value() * inv_s;
-      // Q = S2 - 1.2 S0 cancels where x^2 ~ 1.2: formed in FP64
-      const double Q =
-          (double)w * ((double)K2.value() * (1.0 / kLog2e) - 1.2 * (double)K0.value());
-      gv = 2.f * s1 / bj;
-      const float below = (delta <= b.pivot) ? 1.f : 0.f;
-      gd = (float)((2.0 * (double)s0 + (double)K.gm1 * below * Q) / (double)delta);
-      q_T0 += Q;
-      q_gam += Q * ((double)l2D * kLn2);  // Q ln D
-    }
-    gdelta[off + j] = gd;
-    gvpec[off + j] = gv;
   }
 }
 
 __global__ __launch_bounds__(kAdjThreads) void tau_adjoint_kernel(
     Batch b, const int2 *__restrict__ items, const float *__restrict__ g,
     float *__restrict__ gdelta, float *__restrict__ gvpec, double *__restrict__ gpart) {
-  __shared__ float gl[kChunk];
+  __shared__ float gl[kAdjChunk];
   __shared__ double shd[8];
   const int2 item = items[blockIdx.x];
-  const int64_t s = item.x;
-  const SkewerConst K = b.skc[s];
-  const int64_t off = b.offsets[s];
-  double q_T0 = 0.0, q_gam = 0.0;
-  for (int p = 0; p < kTauTile; p += kAdjTile) {
-    const int j0 = item.y * kTauTile + p;
-    if (j0 >= K.n) break;
-    adjoint_pass(b, K, off, j0, g, gdelta, gvpec, gl, q_T0, q_gam);
+  const SkewerConst K = b.skc[item.x];
+  const int64_t off = b.offsets[item.x];
+  const int n = K.n;
+  const int j0 = item.y * kTauTile;
+  const int j_end = min(j0 + kTauTile, n);
+  float dd[kAdjPasses], vv[kAdjPasses];
+  bool bad = false;
+#pragma unroll
+  for (int p = 0; p < kAdjPasses; ++p) {
+    const int j = j0 + p * kAdjThreads + (int)threadIdx.x;
+    dd[p] = j < j_end ? b.delta[off + j] : 0.f;
+    vv[p] = j < j_end ? b.vpec[off + j] : 0.f;
   }
+  // staged margin: a run reaches at most vpx + half from its source, and its outer
+  // blocks up to 8 more.  A box of at least two half windows of 6 b or more holds
+  // one image of every pair that matters (the others' terms are below exp(-36)), if
+  // the velocities reach less than the box.
+  const int RH = K.vpx + K.half + kAdjMargin;
+  const bool windowed =
+      kTauTile + 2 * RH <= kAdjChunk && 2 * K.half + 8 <= n && K.vpx < n;
+  if (windowed) {
+    const int cnt = (j_end - j0) + 2 * RH;
+    const float *gs = g + off;
+    for (int c = threadIdx.x; c < cnt; c += kAdjThreads) {
+      int i = j0 - RH + c;
+      while (i < 0) i += n;
+      while (i >= n) i -= n;
+      gl[c] = gs[i];
+    }
+  }
+  __syncthreads();
+  double q_T0 = 0.0, q_gam = 0.0;
+#pragma unroll 1
+  for (int p = 0; p < kAdjPasses; ++p) {
+    const int j = j0 + p * kAdjThreads + (int)threadIdx.x;
+    if (j0 + p * kAdjThreads >= j_end) break;
+    const float delta = p == 0 ? dd[0] : dd[kAdjPasses - 1], v = p == 0 ? vv[0] : vv[kAdjPasses - 1];
+    static_assert(kAdjPasses <= 2, "a source each from dd and vv");
+    // an invalid density sets the sticky domain bit (the reach pass may not
+    // have read Delta)
+    bad |= !(delta >= 0.f) || !isfinite(delta);
+    const AdjSource s = adj_source(K, b.pivot, delta, v);
+    double S0, S1, S2;
+    if (windowed) {
+      const bool line = s.w > 0.f;
+      const float a = line ? K.dv * s.r : 0.f;
+      // the target nearest the centre, and the centre's distance from it: exact to
+      // one rounding of a value below dv
+      const float vs = line ? fminf(fmaxf(rintf(v * K.inv_dv), (float)-K.vpx), (float)K.vpx) : 0.f;
+      const float tc = line ? __builtin_fmaf(vs, K.dv, -v) * s.r : 0.f;
+      const float h = b.window_k * (float)kSqrtLog2e * K.inv_dv / s.r;  // k b / dv
+      const int Hl = line ? (int)fminf(h + 1.51f, (float)K.half) : 0;
+      const int H = __builtin_amdgcn_readfirstlane(adj_wave_max(Hl));
+      const bool wide = !(a <= kAdjMaxA) || !(2.f * a * a * ((float)H + 10.f) <= kAdjMaxExp);
+      adjoint_run(gl, (j - j0) + RH + (int)vs, H, a, tc, !__any(wide), S0, S1, S2);
+    } else {
+      adjoint_full(K, g + off, gl, j, v, s.r, S0, S1, S2);
+    }
+    if (j < j_end) {
+      float gd = 0.f, gv = 0.f;
+      if (s.w > 0.f) {
+        // t = x sqrt(log2 e) and 1/b = r / sqrt(log2 e); Q = S2 - 1.2 S0 cancels
+        // where x^2 ~ 1.2: formed in FP64
+        const double w = s.w;
+        const double Q = w * (S2 * (1.0 / kLog2e) - 1.2 * S0);
+        gv = (float)(2.0 * w * S1 * (double)s.r * (1.0 / kLog2e));
+        const double below = (delta <= b.pivot) ? (double)K.gm1 : 0.0;
+        gd = (float)(fma(below, Q, 2.0 * w * S0) * adj_rcp((double)delta));
+        q_T0 += Q;
+        q_gam += Q * ((double)s.l2D * kLn2);  // Q ln D
+      }
+      gdelta[off + j] = gd;
+      gvpec[off + j] = gv;
+    }
+  }
+  if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(b.status, LYAF_STATUS_DOMAIN);
   // FP64 workgroup sums of Q (for dL/dT0 after division by T0) and Q ln D
   double a0 = q_T0, a1 = q_gam;
   for (int m = 32; m >= 1; m >>= 1) {

@@ -62,6 +62,39 @@ def test_tau_backward_full_box_path(n_pix, dv):
     assert_per_skewer_close(gg.cpu().numpy(), rg, "dL/dgamma")
 
 
+@pytest.mark.parametrize("n_pix,dv,v_max", [
+    (92, 4.0, 250.0),     # two half windows, sources beside their own images
+    (92, 4.0, 380.0),     # velocities beyond the box: every target
+    (511, 2.0, 300.0), (512, 2.0, 300.0), (513, 2.0, 300.0), (1500, 2.0, 300.0),
+    (2100, 1.0, 600.0),   # reach beyond the staged targets
+    (700, 9.0, 300.0),    # lines too narrow for the recurrence
+])
+def test_tau_backward_windows(n_pix, dv, v_max):
+    import torch
+    from paper_1105_4747_amd import lyaf as L
+    w = fields.small_workload(n_skewers=2, n_pix=n_pix, seed=46, dv=dv, gamma=1.2,
+                              T0=1.0e4)
+    w.vpec *= np.float32(v_max / np.abs(w.vpec).max())
+    w.delta[[0, n_pix // 2, n_pix, 2 * n_pix - 1]] = 0.0
+    d = OnDevice(w)
+    g = np.random.default_rng(4).normal(size=w.n_pix).astype(np.float32)
+    gd, gv = torch.empty_like(d.delta), torch.empty_like(d.vpec)
+    gT = torch.empty(2, device="cuda:0", dtype=torch.float64)
+    gg = torch.empty_like(gT)
+    print(f"case: adjoint window n={n_pix} dv={dv} v_max={v_max}", flush=True)
+    L.tau_backward(d.delta, d.vpec, d.dv, d.T0, d.gamma, d.offsets, to_dev(g), gd, gv, gT, gg)
+    torch.cuda.synchronize()
+    rd, rv, rT, rg = O.tau_grad(w.delta, w.vpec, w.dv, w.T0, w.gamma, g.astype(np.float64),
+                                offsets=w.offsets)
+    for got, ref, what in ((gd, rd, "dL/dDelta"), (gv, rv, "dL/dv")):
+        got = got.cpu().numpy()
+        ok = w.delta > 0
+        assert (got[~ok] == 0).all()
+        assert_grad_close(got[ok], ref[ok], what)
+    assert_per_skewer_close(gT.cpu().numpy(), rT, "dL/dT0")
+    assert_per_skewer_close(gg.cpu().numpy(), rg, "dL/dgamma")
+
+
 def test_normalise_backward_against_oracle():
     import torch
     from paper_1105_4747_amd import lyaf as L
