@@ -265,6 +265,7 @@ struct HostInsPlan {
   int64_t n_items = 0;
   int64_t n_sk = 0;   // backward: skewers for the per-skewer kernel (after the items)
   int max_bins = 0;   // the most bins of those skewers
+  int64_t max_n = 0;  // the longest skewer
   int64_t *h_off = nullptr, *h_oo = nullptr;
   int2 *h_items = nullptr;
   int64_t h_off_cap = 0, h_oo_cap = 0, h_items_cap = 0;
@@ -315,10 +316,11 @@ int ensure_ins_plan(Workspace *ws, int64_t S, const int64_t *offsets, const int6
   // the pinned staging buffers may still feed an earlier copy on this stream
   if ((e = hipStreamSynchronize(ws->stream)) != hipSuccess) return map_err(e);
   hp.offsets.clear();
-  int64_t ni = 0, nf = 0, max_bins = 0;
+  int64_t ni = 0, nf = 0, max_bins = 0, max_n = 0;
   for (int64_t s = 0; s < S; ++s) {
     const int64_t n = offsets[s + 1] - offsets[s], no = out_offsets[s + 1] - out_offsets[s];
     ni += ins_items_per_skewer(n, no, backward);
+    max_n = std::max(max_n, n);
     if (backward && ins_bwd_skewer_item(n, no)) {
       ++nf;
       max_bins = std::max(max_bins, no);
@@ -357,6 +359,7 @@ int ensure_ins_plan(Workspace *ws, int64_t S, const int64_t *offsets, const int6
   hp.n_items = ni;
   hp.n_sk = nf;
   hp.max_bins = (int)max_bins;
+  hp.max_n = max_n;
   return LYAF_OK;
 }
 
@@ -807,7 +810,7 @@ int lyaf_instrument(int64_t n_skewers, const int64_t *offsets, const float *dv, 
   a.out = F_obs;
   a.noise = ip->noise_sigma > 0.0 ? noise : nullptr;
   return map_err(timed("instrument", st, [&] {
-    return launch_instrument(a, hp->d_items, hp->n_items, nullptr, 0, 0, false, st);
+    return launch_instrument(a, hp->d_items, hp->n_items, nullptr, 0, 0, hp->max_n, false, st);
   }));
 }
 
@@ -830,7 +833,7 @@ int lyaf_instrument_backward(int64_t n_skewers, const int64_t *offsets, const fl
   a.out = grad_F;
   return map_err(timed("instrument_backward", st, [&] {
     return launch_instrument(a, hp->d_items, hp->n_items, hp->d_items + hp->n_items, hp->n_sk,
-                             hp->max_bins, true, st);
+                             hp->max_bins, hp->max_n, true, st);
   }));
 }
 

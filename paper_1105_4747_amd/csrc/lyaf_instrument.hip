@@ -12,34 +12,35 @@
 //            pixel i = [(i - 1/2) dv, (i + 1/2) dv)
 //   Fobs_k = Fbin_k + sigma eps_k
 //
-// Kernel layout.  The forward takes one skewer per workgroup and walks its
-// tiles: tile c holds the bins whose lower edge lies in pixels [c W, (c+1) W)
-// from the first bin's edge, W = kInsWindow, and their pixel span (at most
-// W + dv_bin/dv + 2 <= kInsTile pixels) is convolved by the workgroup.  The
-// flux of a tile with its halo of M pixels on each side sits in LDS in 8 planes
-// by index mod 8 (lane l reads element 8l + j from plane j, so the reads of a
-// wave are consecutive); each lane owns 8 consecutive outputs and walks the
-// taps 16 at a time with two windows of registers used in turn, accumulating
-// in FP64 (on gfx950 an FP64 FMA issues at the rate of an unpacked FP32 one).
-// When the taps fit one block of kInsTapBlock, the skewer's taps are formed
-// once and the flux is staged as FP32 in two buffers: the next tile is copied
-// from memory straight into the other buffer (global_load_lds, one wave
-// instruction per plane and 64 rows) while this one is convolved.  Wider
-// line-spread functions stage FP64 values and the taps block by block for every
-// tile (the plane stride puts those 8 planes on different banks).  The
-// convolved span then becomes an FP64 prefix sum in LDS, and each bin is the
-// difference of that cumulative integral, linearly interpolated, at its two
-// edges, divided by its width.
+// Kernel layout.  Line-spread functions whose taps fit one block of kInsTapBlock (all
+// but those of several pixels' width) take a wave per part of a skewer, with no
+// barrier: it forms the taps once and walks pieces of 512 outputs, eight consecutive
+// ones to a lane.  The flux of a piece with its halo of M pixels on each side sits in
+// LDS as FP32 in 8 planes by index mod 8 (lane l reads element 8l + j from plane j, so
+// the reads of a wave are consecutive); the lane walks the taps with two windows of
+// registers used in turn, accumulating in FP64 (on gfx950 an FP64 FMA issues at the
+// rate of an unpacked FP32 one).  The convolved span then becomes an FP64 prefix sum
+// in LDS, and each bin is the difference of that cumulative integral, linearly
+// interpolated, at its two edges, divided by its width.  Wider line-spread functions
+// take a workgroup per skewer, which walks tiles of kInsTile pixels and stages FP64
+// values and the taps block by block.
 //
-// The backward is the transpose: each pixel gathers the gradients of the bins
-// it overlaps (times overlap / bin width), and the same convolution runs over
-// those values (the taps are even in m).  Skewers with at most kInsBwdBins
-// bins take one workgroup each, which forms the bins' FP64 prefix sums once in
-// LDS (a pixel's gathered gradient is then the difference of their linear
-// interpolation at its two edges) and walks the skewer's tiles, gathering a
-// row of 8 staged pixels per thread and the few rows past one per thread a
-// pixel per thread; skewers with more bins take one workgroup per tile and
-// gather by a merge walk over the bins in memory.
+// The backward is the transpose: each pixel gathers the gradients of the bins it
+// overlaps (times overlap / bin width), and the same convolution runs over those
+// values (the taps are even in m).  A wave per part again, where the bins over a
+// staged piece are few enough: their FP64 prefix sums go to LDS, and a pixel's
+// gathered gradient is the difference of their linear interpolation at its two edges.
+// Other skewers of at most kInsBwdBins bins (wide line-spread functions, bins finer
+// than pixels) take the workgroup, which sums all of the bins; skewers with more bins
+// one workgroup per tile, gathering by a merge walk over the bins in memory.
+//
+// 4096 skewers of 4096 pixels at 2 km/s (FWHM 7, bins of 3.08 km/s; 222 MB moved) and
+// at 18.3 km/s (FWHM 224, bins of 64 km/s), forward and backward together: 196 and
+// 199 -> 154 and 162 us, where a workgroup per skewer with tiles of 2048 waited at
+// five barriers per tile and left a third of its waves without outputs in the last
+// one.  Vector issue takes about half of that, the traffic a quarter; the FP64
+// windows hold the kernels to four waves per SIMD (at five they spill: 94 against 88
+// and 188 against 92 us), which do not hide the rest.
 #include <algorithm>
 
 #include "lyaf_internal.h"
@@ -173,36 +174,62 @@ __device__ double stage_taps(const InsArgs &a, const InsSkewer &k, int u0, int t
   return z_part;
 }
 
-// Eight taps u .. u+7 against the window lo (elements 8l + u .. 8l + u + 7) and
-// hi (the next 8).
-__device__ inline void conv_step(int u, const double (&lo)[8], const double (&hi)[8],
-                                 double (&acc)[kInsPerLane], const double *taps) {
+// Four taps against the window lo (elements 8l + u .. 8l + u + 7) and hi (the next
+// 8), HALF of eight taps: taps u + 4 HALF .. u + 4 HALF + 3 reach elements up to
+// 4 HALF + 3 of hi.
+template <int HALF>
+__device__ __forceinline__ void conv_half(const double (&lo)[8], const double (&hi)[8],
+                                          const double (&t)[4], double (&acc)[kInsPerLane]) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const double h = taps[u + i];
+  for (int i = 0; i < 4; ++i) {
 #pragma unroll
-    for (int q = 0; q < kInsPerLane; ++q)
-      acc[q] = __builtin_fma(h, (q + i < 8) ? lo[q + i] : hi[q + i - 8], acc[q]);
+    for (int q = 0; q < kInsPerLane; ++q) {
+      const int e = q + i + 4 * HALF;
+      acc[q] = __builtin_fma(t[i], e < 8 ? lo[e] : hi[e - 8], acc[q]);
+    }
   }
 }
 
-// acc[q] += sum_{u < tbp} h_u s[8l + q + u] over the staged block (tbp a
-// multiple of 16): lane l owns outputs 8l .. 8l + 7; element 8l + 8b + j of the
-// staged block sits in plane j at row l + b.
-__device__ inline void conv_block(int tbp, double (&acc)[kInsPerLane], const InsShared &sh) {
-  const double *p = sh.s + threadIdx.x;
+// acc[q] += sum_{u < tbp} h_u s[8l + q + u] over a staged block (tbp a multiple of
+// 8): lane l owns outputs 8l .. 8l + 7; element 8l + 8b + j of the block sits in
+// plane j at row l + b, p is the lane's row of plane 0 and PLANE the planes' stride.
+// Half a window is read ahead of the four taps that need it and no more (the
+// schedule is held to that, or the taps' reads take the registers).
+template <int PLANE, class E>
+__device__ __forceinline__ void conv_walk(int tbp, double (&acc)[kInsPerLane], const E *p,
+                                          const double *taps) {
   double wa[8], wb[8];
+  E f[4], g[4];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) wa[j] = p[j * kInsPlane];
-  for (int u = 0; u < tbp; u += 16) {
-    const int b = u >> 3;
+  for (int j = 0; j < 8; ++j) wa[j] = (double)p[j * PLANE];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) wb[j] = p[j * kInsPlane + b + 1];
-    conv_step(u, wa, wb, acc, sh.h);
+  for (int j = 0; j < 4; ++j) f[j] = p[j * PLANE + 1];
+  const auto step = [&](int u, const double(&lo)[8], double(&hi)[8]) {
+    const E *pb = p + (u >> 3);
+    double t[4];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) wa[j] = p[j * kInsPlane + b + 2];
-    conv_step(u + 8, wb, wa, acc, sh.h);
+    for (int i = 0; i < 4; ++i) t[i] = taps[u + i];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) g[j] = pb[(4 + j) * PLANE + 1];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) hi[j] = (double)f[j];
+    conv_half<0>(lo, hi, t, acc);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = taps[u + 4 + i];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[j] = pb[j * PLANE + 2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) hi[4 + j] = (double)g[j];
+    conv_half<1>(lo, hi, t, acc);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int u = 0;
+  for (; u + 16 <= tbp; u += 16) {
+    step(u, wa, wb);
+    step(u + 8, wb, wa);
   }
+  if (u < tbp) step(u, wa, wb);
 }
 
 // Convolution of a tile: acc[q] = sum_{u < T} h_u src(8l + q + u) for the lane's
@@ -227,7 +254,7 @@ __device__ double convolve_tile(const InsArgs &a, const InsSkewer &k, int span, 
     const int real = span + tb - 1;   // offsets carrying real taps
     for (int x = tid; x < need; x += kInsThreads) stage_store(sh, x, x < real ? src(u0 + x) : 0.0);
     __syncthreads();
-    if (wave_active) conv_block(tbp, acc, sh);
+    if (wave_active) conv_walk<kInsPlane>(tbp, acc, sh.s + threadIdx.x, sh.h);
   }
   return block_sum_d(z_part, sh.red);
 }
@@ -286,8 +313,6 @@ __device__ InsTile ins_tile(const InsArgs &a, const InsSkewer &k, int c, const I
   return t;
 }
 
-constexpr int kNzPre = 4;  // noise draws per thread read ahead
-
 // Staged offset x of a tile holds pixel (p0 - M + x) mod n; n <= 2^24, so 32
 // bits do.
 __device__ inline float tile_flux(const float *F, uint32_t n32, uint32_t base, int x) {
@@ -306,73 +331,14 @@ __device__ inline void bin_range(const InsTile &t, int &j0, int &cnt) {
   cnt = min(cb, nb - j0);
 }
 
-__device__ inline void noise_loads(const InsArgs &a, const InsSkewer &k, const InsTile &t,
-                                   float (&nz)[kNzPre]) {
-  int j0, cnt;
-  bin_range(t, j0, cnt);
-#pragma unroll
-  for (int r = 0; r < kNzPre; ++r)
-    nz[r] = (a.noise && r < cnt) ? a.noise[k.out_off + t.k_lo + j0 + r] : 0.0f;
-}
+constexpr int kTileRows = 320;  // rows of a plane of a staged FP32 tile, 5 blocks of 64
+static_assert(8 * kTileRows >= kInsTile + kInsTapBlock + 16, "a staged tile must fit");
 
-// LDS of the forward when the taps fit one block: two buffers of the raw flux
-// (FP32, 8 planes of kDmaRows rows: element x at plane x mod 8, row x / 8), the
-// prefix sums of the convolved tile, the taps.
-constexpr int kDmaRows = 320;  // 5 blocks of 64 rows
-static_assert(8 * kDmaRows >= kInsTile + kInsTapBlock + 16, "a staged tile must fit");
-struct InsDmaShared {
-  float f[2][8 * kDmaRows];
-  double pre[kInsTile + 8];
-  double h[kInsTapBlock];
-  double red[kInsThreads / 64];
-};
-
-// Staging of a tile straight from memory into LDS (global_load_lds: each lane's
-// dword lands at the wave's LDS base + 4 lane), one wave instruction per plane
-// and block of 64 rows, so no register holds it and the copy runs while the
-// workgroup computes.  Offsets past the real taps load a pixel of the tile
-// (they meet zero taps only).
-__device__ inline void tile_dma(const float *F, uint32_t n32, const InsTile &t, int T, int tbp,
-                                float *fbuf) {
-  const int need = t.span + tbp - 1;
-  const int real = t.span + T - 1;
-  const int nrb = (((need + 7) >> 3) + 63) >> 6;  // blocks of 64 rows, <= 5
-  const int lane = threadIdx.x & 63;
-  for (int q = threadIdx.x >> 6; q < 8 * nrb; q += kInsThreads / 64) {
-    const int j = q & 7, rb = q >> 3;
-    const int x = 8 * (rb * 64 + lane) + j;
-    uint32_t i = t.base + (uint32_t)(x < real ? x : 0);
-    if (i >= n32) i -= n32;
-    if (i >= n32) i %= n32;
-    __builtin_amdgcn_global_load_lds(F + i, fbuf + j * kDmaRows + rb * 64, 4, 0, 0);
-  }
-}
-
-// conv_block over a staged FP32 tile (each value converted once on load).
-__device__ inline void conv_block_f32(int tbp, double (&acc)[kInsPerLane], const float *fbuf,
-                                      const double *taps) {
-  const float *p = fbuf + threadIdx.x;
-  double wa[8], wb[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) wa[j] = (double)p[j * kDmaRows];
-  for (int u = 0; u < tbp; u += 16) {
-    const int b = u >> 3;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) wb[j] = (double)p[j * kDmaRows + b + 1];
-    conv_step(u, wa, wb, acc, taps);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) wa[j] = (double)p[j * kDmaRows + b + 2];
-    conv_step(u + 8, wb, wa, acc, taps);
-  }
-}
-
-// Prefix sums of a convolved tile, then its bins (with the noise draws nz read
-// ahead for the first kNzPre of this thread's bins): each bin is the
-// difference of the interpolated cumulative integral at its edges
+// Prefix sums of a convolved tile, then its bins: each bin is the difference of the interpolated cumulative integral at its edges
 // e(j) = e_lo + j q (relative to p0), divided by its width.
 __device__ void finish_tile(const InsArgs &a, const InsSkewer &k, const InsTile &t,
-                            const double (&acc)[kInsPerLane], double Z,
-                            const float (&nz)[kNzPre], double *pre, double *red) {
+                            const double (&acc)[kInsPerLane], double Z, double *pre,
+                            double *red) {
   const int span = t.span;
   // pre[i] = sum_{i' < i} Fc[i']; only outputs inside the span enter (lanes
   // past it hold garbage)
@@ -412,104 +378,298 @@ __device__ void finish_tile(const InsArgs &a, const InsSkewer &k, const InsTile 
   float *out = a.out + k.out_off + t.k_lo + j0;
   const float *noise = a.noise ? a.noise + k.out_off + t.k_lo + j0 : nullptr;
   double c0 = cum(__builtin_fma((double)j0, k.q, t.e_lo));
-#pragma unroll
-  for (int r = 0; r < kNzPre; ++r) {
-    if (r < cnt) {
-      const double c1 = cum(__builtin_fma((double)(j0 + r + 1), k.q, t.e_lo));
-      out[r] = (float)__builtin_fma(c1 - c0, k.inv_q, a.sigma * (double)nz[r]);
-      c0 = c1;
-    }
-  }
-  for (int r = kNzPre; r < cnt; ++r) {
+  for (int r = 0; r < cnt; ++r) {
     const double c1 = cum(__builtin_fma((double)(j0 + r + 1), k.q, t.e_lo));
     out[r] = (float)__builtin_fma(c1 - c0, k.inv_q, a.sigma * (double)(noise ? noise[r] : 0.0f));
     c0 = c1;
   }
 }
 
-// Forward: one workgroup per skewer, walking its tiles in order.  When the
-// taps fit one block (2M + 1 <= kInsTapBlock) the skewer's taps and their sum
-// are formed once and the next tile's flux is copied into the other LDS buffer
-// (and its noise draws read) while the current tile is convolved; wider
-// line-spread functions stage the taps block by block for every tile.
-union InsLds {
-  InsShared w;     // wide line-spread functions
-  InsDmaShared d;  // taps in one block
+// ---- Line-spread functions of one block of taps: a wave per piece ----
+//
+// A wave takes kInsPiece outputs, eight to a lane, with their halo, through LDS of
+// its own: the staged flux (FP32, 8 planes of kPieceRows rows: element x at plane
+// x mod 8, row x / 8; 64 lanes write and read 64 different banks), later the
+// prefix sums.  The waves of a workgroup share the skewer's taps and no barrier.
+constexpr int kInsPiece = 64 * kInsPerLane;  // 512
+constexpr int kInsWaves = kInsThreads / 64;
+static_assert(kInsWaves == 4, "a workgroup holds whole skewers of 1, 2 or 4 parts");
+constexpr int kPieceRows = 104;
+constexpr int kPieceDoubles = 9 * 64;  // prefix sums, nine to a lane
+constexpr int kPieceLoads = (kInsPiece + kInsTapBlock) / 64;
+static_assert(8 * kPieceRows >= kInsPiece + kInsTapBlock + 16, "a staged piece must fit");
+static_assert(kPieceRows % 16 == 8, "planes must start on different banks");
+static_assert(8 * kPieceRows * sizeof(float) <= kPieceDoubles * sizeof(double),
+              "the prefix sums take the staged values' place");
+static_assert(kInsMaxRatio + 3 < kInsPiece / 2 + 1, "half a piece is left at the widest bins");
+
+// LDS operations of a wave complete in order: only the compiler has to keep it.
+__device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory"); }
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add_d(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xF, false);
+  return x + __hiloint2double(hi, lo);
+}
+// Inclusive sums over the wave.
+__device__ __forceinline__ double wave_scan_d(double x) {
+  x = dpp_add_d<0x111, 0xF>(x);  // row_shr:1, 2, 4, 8 (zero from outside the row)
+  x = dpp_add_d<0x112, 0xF>(x);
+  x = dpp_add_d<0x114, 0xF>(x);
+  x = dpp_add_d<0x118, 0xF>(x);
+  x = dpp_add_d<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
+  x = dpp_add_d<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+// x of the lane below, 0 in lane 0.
+__device__ __forceinline__ double wave_below_d(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x138, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x138, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);  // wave_shr:1
+}
+
+// x of the lane above, 0 in lane 63.
+__device__ __forceinline__ double wave_above_d(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x130, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x130, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);  // wave_shl:1
+}
+
+__device__ inline int64_t uniform_i64(int64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)(uint64_t)x);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)x >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// i mod n in [0, n) as wrap_index, by the rounded inverse of n (the quotient is
+// off by one at most).
+__device__ inline uint32_t wrap_fast(double i, double nd, double inv_nd) {
+  double r = __builtin_fma(-floor(i * inv_nd), nd, i);
+  if (r < 0.0) r += nd;
+  if (r >= nd) r -= nd;
+  return (uint32_t)r;
+}
+
+// The skewer's taps into the wave's h; returns the inverse of their sum.
+__device__ __forceinline__ double wave_taps(const InsArgs &a, const InsSkewer &k, double *h) {
+  const int T = 2 * k.M + 1, tbp = (T + 7) & ~7;
+  const double scale = tap_scale(a, k);
+  double z = 0.0;
+  wave_lds_order();
+  for (int u = threadIdx.x & 63; u < tbp; u += 64) {
+    const double g = u < T ? tap_value(a, k, k.M - u, scale) : 0.0;
+    h[u] = g;
+    z += g;
+  }
+  wave_lds_order();
+  z = wave_scan_d(z);
+  const int lo = __builtin_amdgcn_readlane(__double2loint(z), 63);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(z), 63);
+  return 1.0 / __hiloint2double(hi, lo);
+}
+
+// Piece c of the forward: the bins whose lower edge lies in pixels [c W, (c+1) W)
+// from the first bin's edge, W = kInsPiece - 3 - ceil(bin width), so that the
+// pixels they cover are at most kInsPiece.
+struct InsPiece {
+  int64_t k_lo;   // first bin
+  int nb;         // bins (none: past the last)
+  int span;       // pixels covered
+  uint32_t base;  // pixel of staged offset 0
+  double e_lo;    // lower edge of the first bin relative to the span, pixels
 };
-
-__global__ __launch_bounds__(kInsThreads) __attribute__((amdgpu_waves_per_eu(4))) void instrument_kernel(
-    InsArgs a, const int2 *__restrict__ items) {
-  __shared__ InsLds lds;
-  const InsSkewer k = ins_skewer(a, items[blockIdx.x].x);
-  if (!k.ok) {
-    if (threadIdx.x == 0) atomicOr(a.status, LYAF_STATUS_DOMAIN);
-    return;
+__device__ inline InsPiece ins_piece(const InsArgs &a, const InsSkewer &k, int c, int W, double nd,
+                                     double inv_nd) {
+  const auto first = [&](int64_t x) -> int64_t {  // first bin from pixel x on
+    if (x >= k.n) return k.n_out;
+    const int64_t kb = (int64_t)ceil((double)(int)x * k.inv_q);
+    return kb >= k.n_out ? k.n_out : kb;
+  };
+  InsPiece t;
+  t.k_lo = uniform_i64(c == 0 ? 0 : first((int64_t)c * W));
+  const int64_t k_hi = uniform_i64(first((int64_t)(c + 1) * W));
+  t.nb = (int)(k_hi - t.k_lo);
+  t.span = 0;
+  t.base = 0;
+  t.e_lo = 0.0;
+  if (t.nb > 0) {
+    const double xa = bin_edge(a, k, t.k_lo), xb = bin_edge(a, k, k_hi);
+    const double p0 = floor(xa);
+    t.e_lo = wave_uniform(xa - p0);
+    t.span = __builtin_amdgcn_readfirstlane((int)(floor(xb) - p0) + 1);
+    t.base = __builtin_amdgcn_readfirstlane(wrap_fast(p0 - (double)k.M, nd, inv_nd));
   }
-  const int T = 2 * k.M + 1;
-  const float *F = a.in + k.off;
+  return t;
+}
+
+// The forward of one wave: pieces part, part + parts, .. of the skewer, the flux of
+// the next one read into registers while this one's bins are formed.
+__device__ __forceinline__ void ins_forward_pieces(const InsArgs &a, const InsSkewer &k,
+                                                   double *lds, double *taps, int part,
+                                                   int parts) {
+  const int lane = threadIdx.x & 63;
+  const int T = 2 * k.M + 1, tbp = (T + 7) & ~7;
+  const int W = __builtin_amdgcn_readfirstlane(kInsPiece - 3 - (int)ceil(k.q));
+  const int nt = (int)((k.n + W - 1) / W);
+  const double nd = (double)(int)k.n, inv_nd = wave_uniform(1.0 / nd);
   const uint32_t n32 = (uint32_t)k.n;
-  if (T > kInsTapBlock) {
-    // a wider line-spread function: taps staged block by block for every tile
-    InsShared &sh = lds.w;
-    const int nt = (int)((k.n + kInsWindow - 1) / kInsWindow);
-    InsTile t = ins_tile(a, k, 0, nullptr);
-    for (int c = 0; c < nt && t.k_lo < t.k_hi; ++c) {
-      if (t.span > kInsTile) {  // excluded by the bin-width limit; never expected
-        if (threadIdx.x == 0) atomicOr(a.status, LYAF_STATUS_DOMAIN);
-        return;
+  const float *F = a.in + k.off;
+  float *st = reinterpret_cast<float *>(lds);
+  float R[kPieceLoads];
+  const auto load = [&](const InsPiece &t) {
+    const int real = t.span + T - 1, nr = (t.span + tbp - 1 + 63) >> 6;
+    const bool whole = t.base + (uint32_t)real <= n32;  // no end of the box inside
+#pragma unroll
+    for (int r = 0; r < kPieceLoads; ++r) {
+      R[r] = 0.0f;
+      if (r < nr) {
+        const int x = 64 * r + lane;
+        uint32_t i = t.base + (uint32_t)(x < real ? x : 0);
+        if (!whole) i = i >= n32 ? (i - n32 >= n32 ? i % n32 : i - n32) : i;
+        R[r] = F[i];
       }
-      float nz[kNzPre];
-      noise_loads(a, k, t, nz);
-      const uint32_t base = t.base;
-      const auto src = [&](int x) -> double { return (double)tile_flux(F, n32, base, x); };
-      double acc[kInsPerLane];
-      const double Z = convolve_tile(a, k, t.span, src, acc, sh);
-      finish_tile(a, k, t, acc, Z, nz, sh.s, sh.red);
-      const InsTile tn = ins_tile(a, k, c + 1, &t);
-      t = tn;
     }
-    return;
-  }
-  InsDmaShared &d = lds.d;
-  const int tbp = (T + 15) & ~15;
-  const int n_tiles = (int)((k.n + kInsWindow - 1) / kInsWindow);
-
-  InsTile t = ins_tile(a, k, 0, nullptr);
-  float nz[kNzPre];
-  if (t.k_lo < t.k_hi && t.span <= kInsTile) tile_dma(F, n32, t, T, tbp, d.f[0]);
-  noise_loads(a, k, t, nz);
-  const double Z = block_sum_d(stage_taps(a, k, 0, T, tbp, d.h), d.red);
-
-  for (int c = 0; c < n_tiles && t.k_lo < t.k_hi; ++c) {
-    if (t.span > kInsTile) {  // excluded by the bin-width limit; never expected
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      if (threadIdx.x == 0) atomicOr(a.status, LYAF_STATUS_DOMAIN);
+  };
+  if (part >= nt) return;
+  InsPiece t = ins_piece(a, k, part, W, nd, inv_nd);
+  if (t.nb > 0 && t.span <= kInsPiece) load(t);
+  const double invZ = wave_taps(a, k, taps);  // while the first piece's flux is on its way
+  for (int c = part; c < nt && t.nb > 0; c += parts) {
+    if (t.span > kInsPiece) {  // excluded by the bin-width limit; never expected
+      if (lane == 0) atomicOr(a.status, LYAF_STATUS_DOMAIN);
       return;
     }
-    // this tile's copy is complete for every wave
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    // the next tile goes to the other buffer (last read by tile c - 1, whose
-    // readers are past the barriers of its prefix sums) while this one computes
-    const InsTile tn = ins_tile(a, k, c + 1, &t);
-    const bool more = c + 1 < n_tiles && tn.k_lo < tn.k_hi && tn.span <= kInsTile;
-    float nzn[kNzPre];
-    if (more) {
-      tile_dma(F, n32, tn, T, tbp, d.f[(c + 1) & 1]);
-      noise_loads(a, k, tn, nzn);
+    {
+      const int real = t.span + T - 1, nr = (t.span + tbp - 1 + 63) >> 6;
+      float *w = st + (lane & 7) * kPieceRows + (lane >> 3);
+      wave_lds_order();
+#pragma unroll
+      for (int r = 0; r < kPieceLoads; ++r)
+        if (r < nr) w[8 * r] = 64 * r + lane < real ? R[r] : 0.0f;
+      wave_lds_order();
     }
+    InsPiece tn = t;
+    tn.nb = 0;
+    if (c + parts < nt) tn = ins_piece(a, k, c + parts, W, nd, inv_nd);
+    const float *noise = a.noise ? a.noise + k.out_off + t.k_lo : nullptr;
     double acc[kInsPerLane];
 #pragma unroll
     for (int q = 0; q < kInsPerLane; ++q) acc[q] = 0.0;
-    if ((int)(threadIdx.x & ~63u) * kInsPerLane < t.span)
-      conv_block_f32(tbp, acc, d.f[c & 1], d.h);
-    finish_tile(a, k, t, acc, Z, nz, d.pre, d.red);
-    if (!(c + 1 < n_tiles && tn.k_lo < tn.k_hi)) break;
-    t = tn;
+    conv_walk<kPieceRows>(tbp, acc, st + lane, taps);
+    if (tn.nb > 0 && tn.span <= kInsPiece) load(tn);
+    // prefix sums: pre[9 l + q] = sum of the outputs before 8 l + q, q = 0 .. 8 (the
+    // neighbours of an interpolation are then in one row).  Outputs past the span
+    // enter only sums past it.
+    double run = 0.0;
 #pragma unroll
-    for (int j = 0; j < kNzPre; ++j) nz[j] = nzn[j];
+    for (int q = 0; q < kInsPerLane; ++q) {
+      acc[q] *= invZ;
+      run += acc[q];
+    }
+    double s = wave_below_d(wave_scan_d(run));
+    wave_lds_order();
+    double *pre = lds + 9 * lane;
+    pre[0] = s;
+#pragma unroll
+    for (int q = 0; q < kInsPerLane; ++q) {
+      s += acc[q];
+      pre[q + 1] = s;
+    }
+    wave_lds_order();
+    const int last = t.span - 1;
+    const auto cum = [&](double e) -> double {
+      const int i = min((int)e, last);
+      const double f = e - (double)i;
+      const double *r = lds + (i + (i >> 3));
+      return __builtin_fma(f, r[1] - r[0], r[0]);
+    };
+    float *out = a.out + k.out_off + t.k_lo;
+    // 63 bins at a time: a bin's upper edge is the lower one of the lane above
+    for (int j0 = 0; j0 < t.nb; j0 += 63) {
+      const int j = j0 + lane;
+      const float z = noise ? noise[min(j, t.nb - 1)] : 0.0f;
+      const double c0 = cum(fmin(__builtin_fma((double)j, k.q, t.e_lo), (double)t.span));
+      const double c1 = wave_above_d(c0);
+      if (lane < 63 && j < t.nb)
+        out[j] = (float)__builtin_fma(c1 - c0, k.inv_q, a.sigma * (double)z);
+    }
+    t = tn;
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// Forward.  When the taps fit one block (2M + 1 <= kInsTapBlock) a wave walks a
+// skewer, or one of its parts, by itself; wider line-spread functions stage the taps
+// block by block for every tile, the workgroup together.
+struct InsPieceShared {
+  double w[kInsWaves][kPieceDoubles];
+  double h[kInsWaves][kInsTapBlock];
+};
+union InsLds {
+  InsShared w;       // wide line-spread functions
+  InsPieceShared p;  // taps in one block
+};
+
+__device__ void ins_forward_wide(const InsArgs &a, const InsSkewer &k, InsShared &sh) {
+  const float *F = a.in + k.off;
+  const uint32_t n32 = (uint32_t)k.n;
+  const int nt = (int)((k.n + kInsWindow - 1) / kInsWindow);
+  InsTile t = ins_tile(a, k, 0, nullptr);
+  for (int c = 0; c < nt && t.k_lo < t.k_hi; ++c) {
+    if (t.span > kInsTile) {  // excluded by the bin-width limit; never expected
+      if (threadIdx.x == 0) atomicOr(a.status, LYAF_STATUS_DOMAIN);
+      return;
+    }
+    const uint32_t base = t.base;
+    const auto src = [&](int x) -> double { return (double)tile_flux(F, n32, base, x); };
+    double acc[kInsPerLane];
+    const double Z = convolve_tile(a, k, t.span, src, acc, sh);
+    finish_tile(a, k, t, acc, Z, sh.s, sh.red);
+    const InsTile tn = ins_tile(a, k, c + 1, &t);
+    t = tn;
+  }
+}
+
+// The part of a skewer that a wave takes: slot i is part i mod parts of item
+// i / parts.
+struct InsSlot {
+  int s, part;  // skewer (none: -1)
+};
+__device__ __forceinline__ InsSlot ins_slot(const int2 *items, int64_t n_items, int parts) {
+  const int64_t i = (int64_t)blockIdx.x * kInsWaves +
+                    __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  InsSlot t = {-1, 0};
+  if (i < n_items * parts) {
+    const uint32_t item = (uint32_t)i / (uint32_t)parts;  // i < 2^31
+    t.s = __builtin_amdgcn_readfirstlane(items[item].x);
+    t.part = (int)((uint32_t)i - item * (uint32_t)parts);
+  }
+  return t;
+}
+
+__global__ __launch_bounds__(kInsThreads) __attribute__((amdgpu_waves_per_eu(4))) void instrument_kernel(
+    InsArgs a, const int2 *__restrict__ items, int64_t n_items, int parts) {
+  __shared__ InsLds lds;
+  __shared__ int together[kInsWaves];  // the skewers that take the workgroup, or -1
+  const InsSlot t = ins_slot(items, n_items, parts);
+  const int wv = threadIdx.x >> 6;
+  InsSkewer k;
+  k.ok = false;
+  if (t.s >= 0) {
+    k = ins_skewer(a, t.s);
+    if (!k.ok && (threadIdx.x & 63) == 0) atomicOr(a.status, LYAF_STATUS_DOMAIN);
+  }
+  const bool narrow = k.ok && 2 * k.M + 1 <= kInsTapBlock;
+  if ((threadIdx.x & 63) == 0) together[wv] = k.ok && !narrow && t.part == 0 ? t.s : -1;
+  __syncthreads();
+  if (narrow) ins_forward_pieces(a, k, lds.p.w[wv], lds.p.h[wv], t.part, parts);
+#pragma unroll 1
+  for (int w = 0; w < kInsWaves; ++w) {
+    const int s = __builtin_amdgcn_readfirstlane(together[w]);
+    if (s < 0) continue;
+    __syncthreads();  // every wave is done with the LDS
+    ins_forward_wide(a, ins_skewer(a, s), lds.w);
+  }
 }
 
 // Adjoint of the binning for the cnt (<= 8) consecutive pixels i0 .. i0 + cnt
@@ -573,7 +733,7 @@ __device__ inline void bin_adjoint_run(const InsArgs &a, const InsSkewer &k, con
 // from memory) or none; the per-skewer kernel below takes the others.
 constexpr int kInsBwdBins = 4096;
 struct InsBwdShared {
-  float f[8 * kDmaRows];
+  float f[8 * kTileRows];
   double h[kInsTapBlock];
   double red[kInsThreads / 64];
 };
@@ -633,7 +793,7 @@ __global__ __launch_bounds__(kInsThreads) void instrument_backward_kernel(
         const int x0 = 8 * r + done;
         bin_adjoint_run(a, k, G, (int64_t)i, c, g_global, [&](int p, double v) {
           const int x = x0 + p;
-          d.f[(x & 7) * kDmaRows + (x >> 3)] = (float)v;
+          d.f[(x & 7) * kTileRows + (x >> 3)] = (float)v;
         });
         done += c;
         i = 0;
@@ -642,7 +802,7 @@ __global__ __launch_bounds__(kInsThreads) void instrument_backward_kernel(
     Z = block_sum_d(z_part, d.red);  // its barriers publish the staged values and the taps
 #pragma unroll
     for (int q = 0; q < kInsPerLane; ++q) acc[q] = 0.0;
-    if ((int)(threadIdx.x & ~63u) * kInsPerLane < span) conv_block_f32(tbp, acc, d.f, d.h);
+    if ((int)(threadIdx.x & ~63u) * kInsPerLane < span) conv_walk<kTileRows>(tbp, acc, d.f + threadIdx.x, d.h);
   } else {
     const auto src = [&](int x) -> double {
       uint32_t i = base + (uint32_t)x;
@@ -676,29 +836,182 @@ __global__ __launch_bounds__(kInsThreads) void instrument_backward_kernel(
 // block of taps by block.  A wave whose staged window is all zero (pixels that
 // no bin reaches within the taps) stores zeros without convolving.
 struct InsBwdSkShared {
-  float f[8 * kDmaRows];
+  float f[8 * kTileRows];
   double h[kInsTapBlock];
   double red[kInsThreads / 64];
   double tot[kInsThreads / 64];
-  uint8_t nz_row[kDmaRows];  // row r of the staged block holds a nonzero value
+  uint8_t nz_row[kTileRows];  // row r of the staged block holds a nonzero value
 };
 constexpr int kBwdPerThread = kInsBwdBins / kInsThreads;  // bins per thread in the prefix sums
 static_assert(kBwdPerThread * kInsThreads == kInsBwdBins, "the prefix sums cover every bin");
+constexpr int kBwdLaneBins = 10;  // bins per lane of a wave's piece at most
+constexpr int kBwdPieceDoubles = 640;  // a wave's share of P at least
+static_assert(8 * kPieceRows * sizeof(float) <= kBwdPieceDoubles * sizeof(double),
+              "a staged piece must fit");
 static_assert(64 + kInsTapBlock / 8 <= 128, "a wave's staged rows are two per lane at most");
 static_assert((kInsTile + kInsTapBlock) / 8 <= kInsThreads + kInsThreads / 8,
               "the staged rows past one per thread are at most one pixel per thread");
 
-// Four waves per SIMD (at most 128 VGPRs), as many as the LDS of a skewer
-// with up to ~2700 bins leaves room for.
-__global__ __launch_bounds__(kInsThreads) __attribute__((amdgpu_waves_per_eu(4))) void
-instrument_backward_skewer_kernel(InsArgs a, const int2 *__restrict__ items) {
-  __shared__ InsBwdSkShared sh;
-  extern __shared__ double P[];  // n_out + 1 prefix sums
-  const InsSkewer k = ins_skewer(a, items[blockIdx.x].x);
-  if (!k.ok) {
-    if (threadIdx.x == 0) atomicOr(a.status, LYAF_STATUS_DOMAIN);
-    return;
+// The backward of one wave, taps in one block: pieces part, part + parts, .. of
+// kInsPiece pixels.  The binning adjoint at the piece's staged pixels needs the prefix sums of
+// the bins over them alone (differences of C do not see the sum's start): per image
+// of the box that meets the bins, the lanes sum runs of consecutive bins, the wave
+// scans the runs, and a lane takes C at the nine edges of its row of eight staged
+// pixels and at both edges of the few staged pixels past the 64 rows.  lds holds cap
+// doubles: the prefix sums, then the staged values.
+__device__ __forceinline__ void ins_backward_pieces(const InsArgs &a, const InsSkewer &k,
+                                                    double *lds, double *taps, int part,
+                                                    int parts) {
+  constexpr int kPast = kInsTapBlock / 64;
+  const int lane = threadIdx.x & 63;
+  const int T = 2 * k.M + 1, tbp = (T + 7) & ~7;
+  const int n = (int)k.n, nt = (n + kInsPiece - 1) / kInsPiece;
+  const double nd = (double)n, inv_nd = wave_uniform(1.0 / nd);
+  const double x_first = wave_uniform(bin_edge(a, k, 0));
+  const double x_last = wave_uniform(bin_edge(a, k, k.n_out));
+  const int nb = (int)k.n_out;
+  const float *g = a.in + k.out_off;
+  float *st = reinterpret_cast<float *>(lds);
+  const bool aligned = (((uintptr_t)(a.out + k.off)) & 15u) == 0;
+  // The bins of one image of the box over a piece's staged pixels.
+  struct Image {
+    double L, L_hi;  // this image and the last one that meets the bins
+    double t0;       // bin coordinate of the first staged pixel's lower edge
+    int k0, cnt;     // bins over the staged pixels
+  };
+  const auto image = [&](int c, double L, double L_hi) {
+    Image im;
+    const int need = min(kInsPiece, n - c * kInsPiece) + tbp - 1;
+    im.L = L;
+    im.L_hi = L_hi;
+    im.t0 = wave_uniform((__builtin_fma(L, nd, (double)(c * kInsPiece - k.M)) - x_first) *
+                         k.inv_q);
+    const double t1 = __builtin_fma((double)need, k.inv_q, im.t0);
+    im.k0 = __builtin_amdgcn_readfirstlane((int)fmin(fmax(floor(im.t0), 0.0), (double)nb));
+    im.cnt =
+        __builtin_amdgcn_readfirstlane((int)fmin(fmax(floor(t1) + 1.0, 0.0), (double)nb)) - im.k0;
+    return im;
+  };
+  const auto first_image = [&](int c) {
+    // images y = s0 + x + L n of the staged pixels that meet the bins
+    const int need = min(kInsPiece, n - c * kInsPiece) + tbp - 1;
+    const double s0 = (double)(c * kInsPiece - k.M);
+    return image(c, wave_uniform(ceil((x_first - (s0 + (double)need)) * inv_nd)),
+                 wave_uniform(floor((x_last - s0) * inv_nd)));
+  };
+  float v[kBwdLaneBins];
+  const auto load = [&](const Image &im) {
+    const int m = (im.cnt + 63) >> 6;  // bins per lane, <= kBwdLaneBins (none: im.cnt <= 0)
+#pragma unroll
+    for (int r = 0; r < kBwdLaneBins; ++r) {
+      v[r] = 0.0f;
+      if (r < m) v[r] = g[im.k0 + min(m * lane + r, im.cnt - 1)];
+    }
+  };
+  if (part >= nt) return;
+  Image im = first_image(part);
+  load(im);
+  const double invZ = wave_taps(a, k, taps);  // while the first piece's bins are on their way
+  for (int c = part; c < nt; c += parts) {
+    const int p0 = c * kInsPiece, span = min(kInsPiece, n - p0);
+    const int need = span + tbp - 1;
+    double G[8], Gx[kPast];
+#pragma unroll
+    for (int p = 0; p < 8; ++p) G[p] = 0.0;
+#pragma unroll
+    for (int p = 0; p < kPast; ++p) Gx[p] = 0.0;
+    for (;;) {
+      if (im.cnt > 0 && im.L <= im.L_hi) {
+      const int m = (im.cnt + 63) >> 6;
+#pragma unroll
+      for (int r = 0; r < kBwdLaneBins; ++r)
+        if (r < m && m * lane + r >= im.cnt) v[r] = 0.0f;
+      double run = 0.0;
+#pragma unroll
+      for (int r = 0; r < kBwdLaneBins; ++r)
+        if (r < m) run += (double)v[r];
+      double s = wave_below_d(wave_scan_d(run));
+      wave_lds_order();
+      double *P = lds + m * lane;
+      P[0] = s;
+#pragma unroll
+      for (int r = 0; r < kBwdLaneBins; ++r)
+        if (r < m) {
+          s += (double)v[r];
+          if (r + 1 < m || lane == 63) P[r + 1] = s;
+        }
+      wave_lds_order();
+      const int cnt = im.cnt;
+      const double tc = wave_uniform(im.t0 - (double)im.k0), top = wave_uniform((double)cnt);
+      int ln = lane;
+      asm volatile("" : "+v"(ln));  // the pixels' FP64 edges are not kept across pieces
+      const auto cum = [&](int x) -> double {  // C at the lower edge of staged pixel x
+        const double t = fmin(fmax(__builtin_fma((double)x, k.inv_q, tc), 0.0), top);
+        const int kb = min((int)t, cnt - 1);
+        const double *q = lds + kb;
+        return __builtin_fma(t - (double)kb, q[1] - q[0], q[0]);
+      };
+      double c0 = cum(8 * ln);
+#pragma unroll
+      for (int p = 0; p < 8; ++p) {
+        const double c1 = cum(8 * ln + p + 1);
+        G[p] += c1 - c0;
+        c0 = c1;
+        if (p == 2 || p == 5) __builtin_amdgcn_sched_barrier(0);  // few in flight: registers
+      }
+#pragma unroll
+      for (int p = 0; p < kPast; ++p)
+        if (kInsPiece + 64 * p < need) {
+          const int x = kInsPiece + 64 * p + ln;
+          Gx[p] += cum(x + 1) - cum(x);
+        }
+      }
+      if (im.L >= im.L_hi) break;
+      im = image(c, wave_uniform(im.L + 1.0), im.L_hi);
+      load(im);
+    }
+    bool any = false;
+    wave_lds_order();
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      const float v = (float)G[p];
+      any |= v != 0.0f;
+      st[p * kPieceRows + lane] = v;
+    }
+#pragma unroll
+    for (int p = 0; p < kPast; ++p)
+      if (kInsPiece + 64 * p < need) {
+        const float v = (float)Gx[p];
+        any |= v != 0.0f;
+        st[(lane & 7) * kPieceRows + ((kInsPiece + 64 * p + lane) >> 3)] = v;
+      }
+    wave_lds_order();
+    double acc[kInsPerLane];
+#pragma unroll
+    for (int q = 0; q < kInsPerLane; ++q) acc[q] = 0.0;
+    if (__any(any)) conv_walk<kPieceRows>(tbp, acc, st + lane, taps);
+    if (c + parts < nt) {  // the next piece's bins
+      im = first_image(c + parts);
+      load(im);
+    }
+    float *o = a.out + k.off + p0 + kInsPerLane * lane;
+    float f[kInsPerLane];
+#pragma unroll
+    for (int q = 0; q < kInsPerLane; ++q) f[q] = (float)(acc[q] * invZ);
+    if (aligned && kInsPerLane * lane + 7 < span) {
+      *reinterpret_cast<float4 *>(o) = make_float4(f[0], f[1], f[2], f[3]);
+      *reinterpret_cast<float4 *>(o + 4) = make_float4(f[4], f[5], f[6], f[7]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < kInsPerLane; ++q)
+        if (kInsPerLane * lane + q < span) o[q] = f[q];
+    }
   }
+}
+
+// The backward of a skewer by the workgroup together.
+__device__ void ins_backward_skewer(const InsArgs &a, const InsSkewer &k, InsBwdSkShared &sh,
+                                    double *P) {
   const int nb = (int)k.n_out;
   const float *g = a.in + k.out_off;
   // P[j + 1] = sum_{j' <= j} g_j': thread t sums bins 16t .. 16t + 15, then the
@@ -795,7 +1108,7 @@ instrument_backward_skewer_kernel(InsArgs a, const int2 *__restrict__ items) {
             const int x = x0 + p;
             const float gv = (float)G[p];
             any |= gv != 0.0f;
-            sh.f[(x & 7) * kDmaRows + (x >> 3)] = gv;
+            sh.f[(x & 7) * kTileRows + (x >> 3)] = gv;
           }
         }
         return any;
@@ -836,13 +1149,63 @@ instrument_backward_skewer_kernel(InsArgs a, const int2 *__restrict__ items) {
       const int r1 = r0 + 64;
       const bool mine = (r0 < rows && sh.nz_row[r0]) ||
                         (lane <= tbp / 8 - 1 && r1 < rows && sh.nz_row[r1]);
-      if (wave_active && __any(mine)) conv_block_f32(tbp, acc, sh.f, sh.h);
+      if (wave_active && __any(mine)) conv_walk<kTileRows>(tbp, acc, sh.f + threadIdx.x, sh.h);
     }
     const int t0 = threadIdx.x * kInsPerLane;
 #pragma unroll
     for (int q = 0; q < kInsPerLane; ++q)
       if (t0 + q < span) gF[p0 + t0 + q] = (float)(acc[q] * invZ);
   }
+}
+
+// Four waves per SIMD (at most 128 VGPRs), as many as the LDS of a skewer
+// with up to ~2700 bins leaves room for.  Dynamic LDS: the prefix sums of a skewer, or
+// the waves' pieces.
+__global__ __launch_bounds__(kInsThreads) __attribute__((amdgpu_waves_per_eu(4))) void
+instrument_backward_skewer_kernel(InsArgs a, const int2 *__restrict__ items, int64_t n_items,
+                                  int parts, int lds_doubles) {
+  __shared__ InsBwdSkShared sh;
+  __shared__ int together[kInsWaves];  // the skewers that take the workgroup, or -1
+  extern __shared__ double P[];
+  static_assert(sizeof(sh.f) >= kInsWaves * kInsTapBlock * sizeof(double), "the waves' taps");
+  const InsSlot t = ins_slot(items, n_items, parts);
+  const int wv = threadIdx.x >> 6;
+  const int cap = lds_doubles / kInsWaves;
+  InsSkewer k;
+  k.ok = false;
+  bool alone = false;
+  if (t.s >= 0) {
+    k = ins_skewer(a, t.s);
+    if (!k.ok && (threadIdx.x & 63) == 0) atomicOr(a.status, LYAF_STATUS_DOMAIN);
+    // taps in one block and the bins over a staged piece within the wave's share of P
+    const int T = 2 * k.M + 1, tbp = (T + 7) & ~7;
+    const double most = fmin((double)k.n_out, (double)(kInsPiece + tbp) * k.inv_q + 3.0);
+    alone = k.ok && T <= kInsTapBlock && most <= (double)min(64 * kBwdLaneBins, cap - 65);
+  }
+  if ((threadIdx.x & 63) == 0) together[wv] = k.ok && !alone && t.part == 0 ? t.s : -1;
+  __syncthreads();
+  if (alone)
+    ins_backward_pieces(a, k, P + wv * cap,
+                        reinterpret_cast<double *>(sh.f) + wv * kInsTapBlock, t.part, parts);
+#pragma unroll 1
+  for (int w = 0; w < kInsWaves; ++w) {
+    const int s = __builtin_amdgcn_readfirstlane(together[w]);
+    if (s < 0) continue;
+    __syncthreads();  // every wave is done with the LDS
+    ins_backward_skewer(a, ins_skewer(a, s), sh, P);
+  }
+}
+
+// Parts of a skewer, a wave each, 1, 2 or 4 so that a workgroup holds whole skewers:
+// four up to 2047 skewers, which otherwise leave waves' places empty, fewer beyond, as
+// each part reads the skewer's constants and forms its taps.  4096 skewers of 4096 at
+// 2 km/s, forward and backward: one part 84.9 and 80.7, two 86.1 and 82.2, four 97.3
+// and 92.8 us; two up to 8191, so that the last round of waves is never a whole
+// skewer each.  One for boxes of a few hundred pixels at most, whose skewers have one
+// piece (2000 of 200) and never take the workgroup together.
+int ins_parts(int64_t n_items, int64_t max_n) {
+  if (n_items >= 8192 || (n_items >= 1024 && max_n < kInsTapBlock)) return 1;
+  return n_items >= 2048 ? 2 : 4;
 }
 
 }  // namespace
@@ -860,19 +1223,25 @@ int ins_items_per_skewer(int64_t n, int64_t n_out, bool backward) {
 
 hipError_t launch_instrument(const InsArgs &a, const int2 *items, int64_t n_items,
                              const int2 *skewer_items, int64_t n_skewer_items, int max_bins,
-                             bool backward, hipStream_t st) {
+                             int64_t max_n, bool backward, hipStream_t st) {
   if (backward) {
     // each skewer is taken by exactly one of the two kernels
-    if (n_skewer_items > 0)
-      hipLaunchKernelGGL(instrument_backward_skewer_kernel, dim3((unsigned)n_skewer_items),
-                         dim3(kInsThreads), sizeof(double) * (size_t)(max_bins + 1), st, a,
-                         skewer_items);
+    if (n_skewer_items > 0) {
+      const int lds = std::max(max_bins + 1, kInsWaves * kBwdPieceDoubles);
+      const int parts = ins_parts(n_skewer_items, max_n);
+      hipLaunchKernelGGL(instrument_backward_skewer_kernel,
+                         dim3((unsigned)((n_skewer_items * parts + kInsWaves - 1) / kInsWaves)),
+                         dim3(kInsThreads), sizeof(double) * (size_t)lds, st, a, skewer_items,
+                         n_skewer_items, parts, lds);
+    }
     if (n_items > 0)
       hipLaunchKernelGGL(instrument_backward_kernel, dim3((unsigned)n_items), dim3(kInsThreads),
                          0, st, a, items);
   } else if (n_items > 0) {
-    hipLaunchKernelGGL(instrument_kernel, dim3((unsigned)n_items), dim3(kInsThreads), 0, st, a,
-                       items);
+    const int parts = ins_parts(n_items, max_n);
+    hipLaunchKernelGGL(instrument_kernel,
+                       dim3((unsigned)((n_items * parts + kInsWaves - 1) / kInsWaves)),
+                       dim3(kInsThreads), 0, st, a, items, n_items, parts);
   }
   return hipGetLastError();
 }

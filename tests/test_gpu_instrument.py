@@ -124,6 +124,46 @@ def test_instrument_backward_matches_oracle(name):
     assert float(np.max(np.abs(got - want), initial=0.0)) <= G_INS * scale
 
 
+@pytest.mark.parametrize("lens,dvs,fwhm,bin_kms,v0", [
+    # one piece of 512 outputs less the bins' width, and its neighbours; a bin on
+    # every pixel edge, bins that straddle pieces
+    ([506, 507, 508, 512, 513, 1014, 1015, 1019], 2.0, 7.0, 2.0, 0.0),
+    ([511, 1023, 1024, 1025, 2047, 2049], 2.0, 7.0, 3.0826, -700.3),
+    # 2 M + 1 = 255 and 257 taps: a wave by itself, the workgroup together; both
+    # kinds in one workgroup
+    ([1500, 1500, 700, 1500, 90], [2.0, 1.98, 2.0, 7.0, 2.0], 70.7, 9.0, 31.0),
+    # bins of 100 and 252 pixels
+    ([3000, 257, 260], 1.0, 9.0, 100.0, 5.0),
+    ([3000, 600], 1.0, 9.0, 252.0, -5.0),
+    # bins finer than the pixels: few enough for a wave, and too many
+    ([900, 4500], 3.0, 10.0, 2.9, 1.0),
+    ([900, 4500], 3.0, 10.0, 1.0, 1.0),
+    # one, two and four parts to a skewer
+    ([61] * 1030, 2.0, 7.0, 3.0826, 0.0),
+    ([530] + [3] * 2050, 2.0, 7.0, 3.0826, 0.0),
+    ([1100] + [2] * 8200, 2.0, 7.0, 1.7, 0.0),
+])
+def test_instrument_pieces_and_parts(lens, dvs, fwhm, bin_kms, v0):
+    dvs = [dvs] * len(lens) if isinstance(dvs, float) else dvs
+    off, oo = offs(lens), offs(n_bins(lens, dvs, bin_kms))
+    dv = np.asarray(dvs, np.float32)
+    rng = np.random.default_rng(17)
+    F = np.exp(-rng.exponential(1.0, off[-1])).astype(np.float32)
+    eps = rng.standard_normal(int(oo[-1])).astype(np.float32)
+    print(f"case: instrument pieces {len(lens)} x {lens[0]} bin={bin_kms}", flush=True)
+    got = gpu_instrument(F, dv, off, oo, fwhm, bin_kms, v0, eps, 0.02)
+    want = O.instrument(F.astype(np.float64), off, dv.astype(np.float64), oo, fwhm, bin_kms, v0,
+                        eps.astype(np.float64), 0.02)
+    assert np.all(np.isfinite(got))
+    assert float(np.max(np.abs(got - want))) <= F_ABS
+    g = rng.standard_normal(int(oo[-1])).astype(np.float32)
+    got = gpu_instrument_bwd(g, dv, off, oo, fwhm, bin_kms, v0)
+    want = O.instrument_backward(g.astype(np.float64), off, dv.astype(np.float64), oo, fwhm,
+                                 bin_kms, v0)
+    assert np.all(np.isfinite(got))
+    assert float(np.max(np.abs(got - want))) <= G_INS * float(np.max(np.abs(want)))
+
+
 def test_instrument_autograd_and_noise_independence():
     import torch
     from paper_1105_4747_amd import lyaf as L
