@@ -76,11 +76,18 @@ __device__ inline void dft4(V a0, V a1, V a2, V a3, V &y0, V &y1, V &y2, V &y3) 
   y3 = cadd(d02, mul_pi(d13));
 }
 
+// Position of element e of a single transform of N points in LDS: the index within
+// eight XORed with the number of the eight, so that the first passes' writes, eight
+// elements apart, meet all of the banks (half of the LDS cycles of a 2048-point FP64
+// transform were conflicts).  Steps of 64 elements leave the XOR as it is.
+__device__ inline int fft_swizzle(int e, int N) { return N >= 512 ? e ^ ((e >> 3) & 7) : e; }
+
 // One in-place pass of radix R over C = 2^lgC transforms of N points (see the
 // header).  CAP bounds N C over every call of the instantiation, so each of
 // the THREADS threads holds at most CAP / (R THREADS) butterflies.  A length-8
 // DFT is two length-4 DFTs of x_k + x_{k+4} and (x_k - x_{k+4}) e^{-2 pi i k/8}.
-template <int R, int THREADS, int CAP, typename V>
+// FIRST: the pass of Ns = 1 without its twiddles, which are 1.  SWZ: see fft_batch.
+template <int R, int THREADS, int CAP, bool SWZ, bool FIRST, typename V>
 __device__ void fft_pass(V *buf, const double2 *__restrict__ T, int N, int lgC, int Ns) {
   using S = decltype(V{}.x);
   constexpr int B = (CAP / R + THREADS - 1) / THREADS;
@@ -95,20 +102,24 @@ __device__ void fft_pass(V *buf, const double2 *__restrict__ T, int N, int lgC, 
       const int c = q & cmask;
       const int j = q >> lgC;
       const int k = j & (Ns - 1);
-      const V w = twiddle_as<V>(T[k * step]);
+      V w;
+      if constexpr (!FIRST) w = twiddle_as<V>(T[k * step]);
       V x[R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) x[r] = buf[((j + r * (N / R)) << lgC) + c];
+      for (int r = 0; r < R; ++r)  // N / R is a multiple of 64 wherever elements are swizzled
+        x[r] = buf[SWZ ? fft_swizzle(j, N) + r * (N / R) : ((j + r * (N / R)) << lgC) + c];
       if constexpr (R == 8) {
-        const V w2 = cmul(w, w), w3 = cmul(w2, w), w4 = cmul(w2, w2);
-        const V w5 = cmul(w4, w), w6 = cmul(w3, w3), w7 = cmul(w6, w);
-        x[1] = cmul(x[1], w);
-        x[2] = cmul(x[2], w2);
-        x[3] = cmul(x[3], w3);
-        x[4] = cmul(x[4], w4);
-        x[5] = cmul(x[5], w5);
-        x[6] = cmul(x[6], w6);
-        x[7] = cmul(x[7], w7);
+        if constexpr (!FIRST) {
+          const V w2 = cmul(w, w), w3 = cmul(w2, w), w4 = cmul(w2, w2);
+          const V w5 = cmul(w4, w), w6 = cmul(w3, w3), w7 = cmul(w6, w);
+          x[1] = cmul(x[1], w);
+          x[2] = cmul(x[2], w2);
+          x[3] = cmul(x[3], w3);
+          x[4] = cmul(x[4], w4);
+          x[5] = cmul(x[5], w5);
+          x[6] = cmul(x[6], w6);
+          x[7] = cmul(x[7], w7);
+        }
         constexpr S h = (S)0.70710678118654752440;  // sqrt(1/2)
         const V b0 = csub(x[0], x[4]);
         const V t1 = csub(x[1], x[5]);
@@ -124,13 +135,17 @@ __device__ void fft_pass(V *buf, const double2 *__restrict__ T, int N, int lgC, 
              y[b][2], y[b][4], y[b][6]);
         dft4(b0, b1, b2, b3, y[b][1], y[b][3], y[b][5], y[b][7]);
       } else if constexpr (R == 4) {
-        const V w2 = cmul(w, w), w3 = cmul(w2, w);
-        dft4(x[0], cmul(x[1], w), cmul(x[2], w2), cmul(x[3], w3), y[b][0], y[b][1], y[b][2],
-             y[b][3]);
+        if constexpr (!FIRST) {
+          const V w2 = cmul(w, w), w3 = cmul(w2, w);
+          x[1] = cmul(x[1], w);
+          x[2] = cmul(x[2], w2);
+          x[3] = cmul(x[3], w3);
+        }
+        dft4(x[0], x[1], x[2], x[3], y[b][0], y[b][1], y[b][2], y[b][3]);
       } else {
-        const V a1 = cmul(x[1], w);
-        y[b][0] = cadd(x[0], a1);
-        y[b][1] = csub(x[0], a1);
+        if constexpr (!FIRST) x[1] = cmul(x[1], w);
+        y[b][0] = cadd(x[0], x[1]);
+        y[b][1] = csub(x[0], x[1]);
       }
     }
     // one butterfly's inputs live at a time: without this the compiler reads
@@ -146,8 +161,23 @@ __device__ void fft_pass(V *buf, const double2 *__restrict__ T, int N, int lgC, 
       const int j = q >> lgC;
       const int k = j & (Ns - 1);
       const int base = (j - k) * R + k;
+      if constexpr (SWZ) {  // fft_swizzle(base + r Ns), by the forms it takes
+        const bool on = N >= 512;
+        const int b0 = fft_swizzle(base, N);
+        if (on && FIRST) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) buf[((base + r * Ns) << lgC) + c] = y[b][r];
+          for (int r = 0; r < R; ++r) buf[b0 ^ r] = y[b][r];  // R = 8
+        } else if (on && Ns == 8) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) buf[(b0 ^ r) + 8 * r] = y[b][r];
+        } else {
+#pragma unroll
+          for (int r = 0; r < R; ++r) buf[b0 + r * Ns] = y[b][r];
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) buf[((base + r * Ns) << lgC) + c] = y[b][r];
+      }
     }
   }
   lds_barrier();
@@ -297,18 +327,32 @@ __device__ inline void wave_fft(V (&x)[E], V *col, const V *tw1, const V *tw2, i
 // The whole forward transform of the batch (N >= 1; N = 1 is the identity).
 // The caller has published buf with a barrier; the last pass ends with one
 // (LDS only: global loads issued before the transform may still be in flight).
-template <int THREADS, int CAP, typename V>
+// SWZ: a single transform (lgC = 0) with element e at fft_swizzle(e, N), its first
+// pass by itself (in the batches along ky that costs 60 spilled registers).
+template <int THREADS, int CAP, bool SWZ = false, typename V>
 __device__ void fft_batch(V *buf, const double2 *__restrict__ T, int N, int lgC) {
   int Ns = 1;
+  if constexpr (SWZ) {  // the pass of Ns = 1 by itself, without its twiddles
+    if (N >= 8) {
+      fft_pass<8, THREADS, CAP, true, true>(buf, T, N, 0, 1);
+      Ns = 8;
+    } else if (N == 4) {
+      fft_pass<4, THREADS, CAP, true, true>(buf, T, N, 0, 1);
+      Ns = 4;
+    } else if (N == 2) {
+      fft_pass<2, THREADS, CAP, true, true>(buf, T, N, 0, 1);
+      Ns = 2;
+    }
+  }
   while (Ns * 8 <= N) {
-    fft_pass<8, THREADS, CAP>(buf, T, N, lgC, Ns);
+    fft_pass<8, THREADS, CAP, SWZ, false>(buf, T, N, lgC, Ns);
     Ns *= 8;
   }
   if (Ns * 4 <= N) {
-    fft_pass<4, THREADS, CAP>(buf, T, N, lgC, Ns);
+    fft_pass<4, THREADS, CAP, SWZ, false>(buf, T, N, lgC, Ns);
     Ns *= 4;
   }
-  if (Ns * 2 <= N) fft_pass<2, THREADS, CAP>(buf, T, N, lgC, Ns);
+  if (Ns * 2 <= N) fft_pass<2, THREADS, CAP, SWZ, false>(buf, T, N, lgC, Ns);
 }
 
 }  // namespace lyaf

@@ -83,17 +83,18 @@ __global__ __launch_bounds__(kLineThreads) void p3d_line_kernel(P3dArgs a) {
   const int n = a.n, M = n / 2;
   const float *f = a.F + (size_t)s * n;
   for (int j = threadIdx.x; j < M; j += kLineThreads)
-    lds_line[j] = make_double2(__builtin_fma((double)f[2 * j], a.inv_mean, -1.0),
-                               __builtin_fma((double)f[2 * j + 1], a.inv_mean, -1.0));
+    lds_line[fft_swizzle(j, M)] =
+        make_double2(__builtin_fma((double)f[2 * j], a.inv_mean, -1.0),
+                     __builtin_fma((double)f[2 * j + 1], a.inv_mean, -1.0));
   __syncthreads();
-  fft_batch<kLineThreads, kP3dMaxN / 2>(lds_line, a.twiddle, M, 0);
+  fft_batch<kLineThreads, kP3dMaxN / 2, true>(lds_line, a.twiddle, M, 0);
   double s1, c1;
   sincospi(-1.0 / (double)M, &s1, &c1);
   const double2 half_step = make_double2(c1, s1);
   double2 *out = a.G + (size_t)s * a.H;
   for (int m = threadIdx.x; m <= M; m += kLineThreads) {
-    const double2 zm = lds_line[m == M ? 0 : m];
-    const double2 zc = conj(lds_line[m == 0 ? 0 : M - m]);
+    const double2 zm = lds_line[fft_swizzle(m == M ? 0 : m, M)];
+    const double2 zc = conj(lds_line[fft_swizzle(m == 0 ? 0 : M - m, M)]);
     const double2 E = make_double2(0.5 * (zm.x + zc.x), 0.5 * (zm.y + zc.y));
     const double2 d = csub(zm, zc);
     const double2 O = make_double2(0.5 * d.y, -0.5 * d.x);

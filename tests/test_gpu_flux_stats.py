@@ -114,6 +114,19 @@ def test_power_matches_oracle(lens):
     assert_power_close(got, want, off, f"lens {lens}")
 
 
+@pytest.mark.parametrize("n", [16, 64, 256, 512, 1024, 2048, 4096])
+def test_power_of_every_length(n):
+    """Transforms of M = n / 2 points: swizzled from 512 points on, with a last pass
+    of radix 2, 4 or none."""
+    rng = np.random.default_rng(n)
+    off = np.arange(4, dtype=np.int64) * n
+    F = np.exp(-rng.exponential(0.5, off[-1])).astype(np.float32)
+    dv = np.array([2.0, 3.0, 4.0], np.float32)
+    print(f"case: flux power n={n}", flush=True)
+    want, _ = FS.flux_power(F.astype(np.float64), off, dv.astype(np.float64), 0.7)
+    assert_power_close(gpu_power(F, dv, off, 0.7), want, off, f"n {n}")
+
+
 def test_power_of_the_c1_flux():
     w, F = c1_flux()
     print("case: flux power of C1 F", flush=True)
