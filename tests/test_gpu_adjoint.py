@@ -117,6 +117,25 @@ def test_normalise_backward_against_oracle():
         assert_grad_close(out.cpu().numpy(), ref, f"dL/dtau implicit={implicit}", rel=1e-5)
 
 
+@pytest.mark.parametrize("which", ["F", "tau"])
+def test_autograd_of_one_output_alone(which):
+    """A loss of one output sends no gradient for the other: the result is that of an
+    explicit gradient of zeros."""
+    import torch
+    from paper_1105_4747_amd import lyaf as L
+    w = fields.small_workload(n_skewers=3, n_pix=700, seed=47)
+    d = OnDevice(w)
+    x = [a.clone().requires_grad_(True) for a in (d.delta, d.vpec, d.T0, d.gamma)]
+    ts, F, _ = L.tau_flux(*x, d.dv, w.offsets, w.target_F, window_k=w.window_k)
+    g = to_dev(np.random.default_rng(6).normal(size=w.n_pix).astype(np.float32))
+    z = torch.zeros_like(g)
+    print(f"case: autograd of {which} alone", flush=True)
+    one = torch.autograd.grad(F if which == "F" else ts, x, g, retain_graph=True)
+    both = torch.autograd.grad([ts, F], x, [z, g] if which == "F" else [g, z])
+    for a, b in zip(one, both):
+        assert torch.equal(a, b)
+
+
 def _c5_subset(n=16):
     w = fields.config5().subset(range(n))
     _, F_t, _ = _oracle_F(w, T0=1.1 * w.T0.astype(np.float64),
