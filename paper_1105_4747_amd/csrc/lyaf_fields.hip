@@ -70,16 +70,6 @@ __device__ inline void field_factors(const FieldArgs &a, int mx, int my, int mz,
   fv = (m2 > 0) ? a.E_over_kfun * (float)mz / m2f * A : 0.f;
 }
 
-// Block index -> work item with the items of each XCD contiguous: workgroup b
-// runs on XCD b mod 8, so neighbouring mz runs of one mx (which share cache
-// lines) are taken by the same L2.
-__device__ inline int xcd_item(int n_items) {
-  const int per = (int)gridDim.x >> 3;  // gridDim.x is a multiple of 8
-  const int b = (int)blockIdx.x;
-  const int item = (b & 7) * per + (b >> 3);
-  return item < n_items ? item : -1;
-}
-
 // Persistent: workgroup b takes items b', b' + G, .. (G workgroups; b' puts
 // the workgroups of one XCD on consecutive items, whose mz runs share cache
 // lines), and reads the next item's modes into registers while the current
