@@ -64,24 +64,43 @@ __global__ __launch_bounds__(kPdfThreads) void flux_pdf_kernel(const float *__re
   }
   for (; i < n; i += stride) atomicAdd(&cnt[pdf_slot(F[i]) * kPdfThreads + tid], 1u);
   __syncthreads();
-  if (tid < kPdfSlots) {
-    uint32_t s = 0;  // rotated start: the 24 summing lanes read different banks
-    for (int l = 0; l < kPdfThreads; ++l) s += cnt[tid * kPdfThreads + ((l + tid) & 255)];
-    part[(int64_t)blockIdx.x * kPdfSlots + tid] = s;
+  if (tid < 8 * kPdfSlots) {  // eight lanes to a slot, the 64 of a wave on different banks
+    const int slot = tid >> 3;
+    uint32_t s = 0;
+#pragma unroll 8
+    for (int l = 0; l < kPdfThreads / 8; ++l)
+      s += cnt[slot * kPdfThreads + (tid & 7) + 8 * ((l + slot) & 31)];
+    for (int m = 4; m >= 1; m >>= 1) s += __shfl_xor(s, m);
+    if ((tid & 7) == 0) part[(int64_t)blockIdx.x * kPdfSlots + slot] = s;
   }
 }
 
-// Sum of the workgroups' counts (integers: exact in any order): one wave per
-// slot, each lane summing a strided share with its reads in flight, then a
-// shuffle reduction.
-__global__ __launch_bounds__(64) void flux_pdf_sum_kernel(const uint32_t *__restrict__ part,
-                                                          int blocks,
-                                                          int64_t *__restrict__ counts) {
+// Sum of the workgroups' counts (integers: exact in any order): one workgroup per
+// slot, each thread's reads in flight at once (kPdfMaxBlocks / 256 = 4; one wave with
+// sixteen reads in turn took 6.2 us at 1024 workgroups, this one 4.6), then a shuffle
+// reduction per wave.
+__global__ __launch_bounds__(kPdfThreads) void flux_pdf_sum_kernel(
+    const uint32_t *__restrict__ part, int blocks, int64_t *__restrict__ counts) {
+  __shared__ uint64_t sh[kPdfThreads / 64];
+  constexpr int kReads = kPdfMaxBlocks / kPdfThreads;
+  static_assert(kReads * kPdfThreads == kPdfMaxBlocks, "every workgroup's counts are read");
   const int slot = blockIdx.x;
+  uint32_t v[kReads];
+#pragma unroll
+  for (int r = 0; r < kReads; ++r) {
+    const int g = threadIdx.x + r * kPdfThreads;
+    v[r] = g < blocks ? part[(int64_t)g * kPdfSlots + slot] : 0u;
+  }
   uint64_t s = 0;
-  for (int g = threadIdx.x; g < blocks; g += 64) s += part[(int64_t)g * kPdfSlots + slot];
+#pragma unroll
+  for (int r = 0; r < kReads; ++r) s += v[r];
   for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
-  if (threadIdx.x == 0) counts[slot] = (int64_t)s;
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kPdfThreads / 64; ++w) s += sh[w];
+    counts[slot] = (int64_t)s;
+  }
 }
 
 // Twiddle table of the largest transform, exp(-2 pi i t / 4096), t < 2048; the
@@ -183,7 +202,8 @@ hipError_t launch_flux_pdf(int64_t n, const float *F, uint32_t *part, int64_t *c
   const int blocks = pdf_blocks(n);
   hipLaunchKernelGGL(flux_pdf_kernel, dim3((unsigned)blocks), dim3(kPdfThreads), 0, st, F, n,
                      part);
-  hipLaunchKernelGGL(flux_pdf_sum_kernel, dim3(kPdfSlots), dim3(64), 0, st, part, blocks, counts);
+  hipLaunchKernelGGL(flux_pdf_sum_kernel, dim3(kPdfSlots), dim3(kPdfThreads), 0, st, part, blocks,
+                     counts);
   return hipGetLastError();
 }
 
