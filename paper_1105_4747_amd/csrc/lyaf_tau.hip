@@ -581,12 +581,13 @@ __device__ __forceinline__ int wave_max(int x) {
 // t_k = t_0 + k a (a = dv r), t_k^2 - t_(k-1)^2 = a (2 t_(k-1) + a), so
 // E_k = exp2(-t_k^2) = E_(k-1) G_(k-1) with G_0 = exp2(-a (2 t_0 + a)) and
 // G_k = G_(k-1) C, C = exp2(-2 a^2) per source: two exp2 per source and lane
-// instead of four.  These records hold (w, a, v r + p a, C), p = 0 .. 3 the
-// source's plane: the four steps of a block have offsets fd = F, F - 1, F - 2,
-// F - 3, so t_0 = (fd dv - v) r = F a - (v r + p a) is one FMA on the block's
-// exact offset F, which takes one subtraction per block.  a and the third entry
-// are rounded once each, which adds about u (|fd a| + |v r|) to t_0 (on the
-// 4096 x 4096 workload's fields, 1e-7 of tau at most).  The chain starts
+// instead of four.  These records hold (w, a, v r, C), so that
+// t_0 = (fd dv - v) r = fd a - v r is one FMA on the exact offset fd; a and
+// v r are rounded once each, which adds about u (|fd a| + |v r|) to t_0 (on the
+// 4096 x 4096 workload's fields, 1e-7 of tau at most).  (With the step's share
+// p a of the offset in the record, v r + p a, a block of four steps needs one
+// subtraction instead of four and 1 % of a plan's time, but that second rounding moves
+// tau by up to 4e-7 and A of one spectrum of 1000 pixels by 2e-9: not kept.)  The chain starts
 // at the lane's first target; it is exact to rounding unless E_0 underflows
 // while a later E_k matters, which needs a > 1.16 (|t_0| > 11.2 and
 // |t_0 + 3a| < 7.75), so a tile with any source of a > kRecMaxA (unresolved
@@ -631,12 +632,11 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
   // A thread issues its global reads in rounds of SIT ahead of the arithmetic of
   // the round.  The window bounds of every group of positions (highest last and
   // lowest first pixel, kept as biased 16-bit highest values) meet in a DPP
-  // reduction over the lanes that hold them.  About 45 operations a position, a
-  // tile staging 1.2 (M = 8) to 1.3 positions per target, beside the walk's 29 a
-  // step (M = 8; 32 with a subtraction per step and the clamp): with 100, by
-  // branches and IEEE minima, a plan of 4096 x 4096 pixels took 360 us, now 329,
-  // the ragged 20000-skewer one 1.78 ms, now 1.72, the 512 x 512 x 4096 box 19.6,
-  // now 18.8.
+  // reduction over the lanes that hold them.  About 50 operations a position, a
+  // tile staging 1.2 (M = 8) to 1.3 positions per target, beside the walk's 30 a
+  // step (M = 8; one more with the clamp): with 100, by branches and IEEE minima, a
+  // plan of 4096 x 4096 pixels took 356 us, now 334, the ragged 20000-skewer one
+  // 1.742 ms, now 1.726, the 512 x 512 x 4096 box 19.58, now 19.23.
   constexpr int SIT = 8;  // positions per thread per round of reads
   constexpr int G = SH::kGroup;
   const int e_lo = i0 - RH;
@@ -645,14 +645,11 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
   const char *const dbase = reinterpret_cast<const char *>(b.delta + off);
   const char *const vbase = reinterpret_cast<const char *>(b.vpec + off);
   const bool inside = e_lo >= 0 && e_lo + cnt <= n;  // no periodic image in the tile
-  // half window in pixels: k b / dv = (k sqrt(log2 e) / dv) / r, widened by 0.01
-  // so that the rounding of the bounds drops no source at the window's edge
-  const float hk = b.window_k * (float)kSqrtLog2e * K.inv_dv;
+  const float wk = b.window_k;
   bool bad = false;
   float a_max = 0.f;  // largest a of a line
-  // chain_layout: records (w, a, v r + p a, C) for the recurrence, else (w, r, v, a)
+  // chain_layout: records (w, a, v r, C) for the recurrence, else (w, r, v, a)
   auto stage = [&](const bool chain_layout) {
-    const float pf = (float)(threadIdx.x & 3);  // the plane p: c mod 4, alike for every round
     float4 *const slot = rec + (threadIdx.x & 3) * PL + (threadIdx.x >> 2);
     int *const gslot = gwin + threadIdx.x / G;
     for (int c0 = 0; c0 < cnt; c0 += SIT * NT) {
@@ -686,18 +683,19 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
         const float a = K.dv * r;
         // an empty pixel (0 or NaN here) has no line: w = 0, E = G = 1 whatever its v
         const bool line = w > 0.f;
-        // bias so that the bounds are positive: |v / dv| + h <= RH < 2^9, c < 2^12
-        const float cc = __builtin_fmaf(v, K.inv_dv, (float)c + 4096.f);
-        const float h = __builtin_fmaf(hk, __builtin_amdgcn_rcpf(r), 0.01f);
-        const uint32_t hi = (uint32_t)(cc + h), nlo = (uint32_t)((8192.f - cc) + h);
-        uint32_t win = line ? (hi | (nlo << 16)) : 0u;
+        // the line's centre and half window in pixels; the bounds of a line, |v / dv| + h
+        // <= RH < 2^9 and c < 2^12, are kept as integers biased to be positive
+        const float cc = __builtin_fmaf(v, K.inv_dv, (float)c);
+        const float h = wk * (K.B * fexp2(0.5f * x)) * K.inv_dv;
+        const int hi = (int)floorf(cc + h) + 4096, nlo = 4096 - (int)ceilf(cc - h);
+        uint32_t win = line ? (uint32_t)hi | ((uint32_t)nlo << 16) : 0u;
         if (c < cnt) {
           if (chain_layout) {
             const float C = fexp2(-2.f * a * a);
             a_max = fmaxf(a_max, line ? a : 0.f);
             slot[(c0 >> 2) + u * (NT / 4)] =
                 make_float4(line ? w : 0.f, line ? a : 0.f,
-                            line ? __builtin_fmaf(pf, a, v * r) : 0.f, line ? C : 1.f);
+                            line ? v * r : 0.f, line ? C : 1.f);
           } else {
             slot[(c0 >> 2) + u * (NT / 4)] = make_float4(line ? w : 0.f, r, v, a);
           }
@@ -783,7 +781,7 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
       }
     };
     // one source against the lane's kSkewM targets by the recurrence; F is the
-    // exact offset of the block's first step (the record holds the step's share)
+    // exact offset of the step
     auto pair_chain = [&](auto cl, const float4 q, const float F, const bool first) {
       const float tt0 = __builtin_fmaf(F, q.y, -q.z);
       const float a = q.y;
@@ -807,9 +805,9 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
       if constexpr (decltype(wk)::value != kWalkDirect) {
         const std::integral_constant<bool, decltype(wk)::value == kWalkClamp> cl;
         pair_chain(cl, q[0], F, first);
-        pair_chain(cl, q[1], F, false);
-        pair_chain(cl, q[2], F, false);
-        pair_chain(cl, q[3], F, false);
+        pair_chain(cl, q[1], F - 1.f, false);
+        pair_chain(cl, q[2], F - 2.f, false);
+        pair_chain(cl, q[3], F - 3.f, false);
         // the block's 8 exps, one per 7 (M = 4) or 18 (M = 8: the last ones
         // early, measured best) other VALU instructions
 #pragma unroll
