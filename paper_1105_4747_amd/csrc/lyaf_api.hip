@@ -1221,11 +1221,10 @@ std::vector<int2> build_items(const lyaf_plan *p, int tile) {
   for (int64_t s = 0; s < S; ++s) {
     const int64_t n = p->offsets[s + 1] - p->offsets[s];
     const int R = p->skc_host.empty() ? 0 : p->skc_host[s].reach;
-    const int half = p->skc_host.empty() ? 0 : p->skc_host[s].half;
     const int64_t nt = (n + tile - 1) / tile;
     for (int64_t t = 0; t < nt; ++t) {
       const double tg = (double)std::min<int64_t>(tile, n - t * tile);
-      const bool full = (int64_t)(2 * half + 8) > n || R >= n;
+      const bool full = (int64_t)(32 + 2 * R + 24) > n;
       items.push_back(make_int2((int)s, (int)t));
       cost.push_back(full ? tg * (double)n : tg * (double)std::min<int64_t>(n, 64 + 2 * R));
     }

@@ -196,6 +196,16 @@ def test_mean_flux_scale_of_one_spectrum_stays(seed, A):
     assert abs(_mean_flux_scale(1, 1000, 2.0, seed) / A - 1) <= 1e-9
 
 
+@pytest.mark.parametrize("n_skewers,n_pix,dv,seed,A", [
+    (1, 64, 7.0, 100, 0.31973622474544894), (1, 64, 7.0, 102, 0.28765354457107106),
+    (1, 64, 8.0, 102, 0.2860123295094974), (3, 100, 7.0, 100, 0.342958651109107),
+    (2, 128, 6.0, 101, 0.35422876378919876), (2, 333, 2.0, 102, 0.3318706514227351)])
+def test_mean_flux_scale_of_short_boxes_stays(n_skewers, n_pix, dv, seed, A):
+    """The same of boxes that hold two half windows but not two reaches of their
+    velocities: they sum over every source (windows moved these by 3e-9 to 4.7e-8)."""
+    assert abs(_mean_flux_scale(n_skewers, n_pix, dv, seed) / A - 1) <= 1e-9
+
+
 # ---------------------------------------------------------------- mean flux
 def test_normalise_config1(c1):
     d = OnDevice(c1)
