@@ -191,12 +191,15 @@ constexpr int kSampleWaves = kSampleThreads / kWave;
 constexpr int kSampleGroups = kSampleN / kSampleThreads;  // one gathered pixel per thread
 constexpr int kSampleIters = 32;
 constexpr int kSmallPixels = 16384;  // most pixels of norm_small
-// The second and third pass usually find nothing to do, but cost 4.6 us each as
-// kernels: up to kAlonePixels (16 MB for one workgroup to pass over, when it has to)
-// the first pass's last workgroup makes them, 2e6 pixels 33.7 -> 29.0 us; beyond,
-// 128 workgroups keep their launch short.
-constexpr int kReserveBlocks = 128;
-constexpr int64_t kAlonePixels = int64_t(1) << 22;
+// The second and third pass usually find nothing to do, but their launches cost
+// 4 to 5 us together: up to kAlonePixels the first pass's last workgroup makes them.
+// There it pays either way: 32768 pixels take 25 us with the launches and 20 without
+// when the first pass's step is accepted, 32 and 30 when it is refused.  A refused step
+// costs the one workgroup about 35 FP64 operations a pixel and pass: 34 against 39 us
+// at 65536 pixels, 38 against 296 at 2^20 and 57 against 1109 at 2^22.  (Fewer
+// workgroups for the later launches save nothing when there is nothing to do, and cost
+// a refused step 15 us of 95 at 2^24 pixels.)
+constexpr int64_t kAlonePixels = 32768;
 // the sample iteration stops at this step: its root is only ~1e-2 from the
 // batch's, which the first full pass's series step corrects
 constexpr double kSampleTol = 1e-3;
@@ -738,9 +741,8 @@ hipError_t launch_norm_buffers(int64_t n_pix, float *tau, float *F, double targe
   const bool alone = n_pix <= kAlonePixels;
   const int passes = alone ? 1 : kNormPasses;
   for (int k = 0; k < passes; ++k)
-    hipLaunchKernelGGL(norm_pass_kernel, dim3(k == 0 ? grid : std::min(grid, kReserveBlocks)),
-                       dim3(kPassThreads), 0, st, tau, n_pix, partials, ns->st + k,
-                       ns->st + k + 1, &ns->arrived, status, alone ? 1 : 0);
+    hipLaunchKernelGGL(norm_pass_kernel, dim3(grid), dim3(kPassThreads), 0, st, tau, n_pix,
+                       partials, ns->st + k, ns->st + k + 1, &ns->arrived, status, alone ? 1 : 0);
   const int fgrid = (int)std::min<int64_t>((n_pix + 4095) / 4096, 2048);
   hipLaunchKernelGGL(norm_finalise_kernel, dim3(std::max(fgrid, 1)), dim3(kNormThreads), 0, st,
                      tau, F, n_pix, ns->st + passes, A_dev, status);

@@ -331,6 +331,40 @@ def test_normalise_at_the_edges_of_its_kernels(P, offset):
     assert np.max(np.abs(F.cpu().numpy() - np.exp(-want.astype(np.float64)))) <= 1e-6
 
 
+@pytest.mark.parametrize("P", [1 << 16, 1 << 20, 1 << 22])
+def test_normalise_refused_step_is_not_left_to_one_workgroup(P):
+    """A sample 20 % off the batch (every sampled pixel tau = 1, the others 1.2) has the
+    first pass's step refused: the later passes take the whole chip, as the first one
+    does, so the call takes less than twice what a sample 8 % off takes, whose step is
+    accepted (1.3 to 1.4 times; up to 29 times when one workgroup made them)."""
+    import torch
+    from paper_1105_4747_amd import lyaf as L
+    sampled = np.arange(SAMPLE_N, dtype=np.int64) * P // SAMPLE_N
+    times, A = {}, torch.zeros((), device="cuda:0", dtype=torch.float64)
+    for other in (1.08, 1.2):
+        raw = np.full(P, other, np.float32)
+        raw[sampled] = 1.0
+        src = torch.from_numpy(raw).to("cuda:0")
+        t, F = torch.empty_like(src), torch.empty_like(src)
+        L.status_read()
+        best = math.inf
+        for _ in range(12):  # the least of repeats: the GPU's own time
+            t.copy_(src)
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            L.normalise_mean_flux(t, F, 0.8, A)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        assert L.status_read() == 0
+        A_ref, _ = O.mean_flux_A(raw.astype(np.float64), 0.8)
+        assert abs(float(A.cpu()) / A_ref - 1) <= A_REL
+        times[other] = best
+    print(f"rescale of {P} pixels: {times[1.08] * 1e3:.1f} us accepted, "
+          f"{times[1.2] * 1e3:.1f} us refused", flush=True)
+    assert times[1.2] <= 2 * times[1.08]
+
+
 def test_normalise_one_workgroup_from_a_far_start():
     """Two levels of tau four decades apart in one workgroup's batch: the iteration
     starts far from the root and takes many steps (and the verdicts of a batch of
