@@ -117,6 +117,13 @@ hipError_t timed_kernel(const char *name, hipStream_t st, F &&launch) {
   return hipSuccess;
 }
 
+// Whether `st` is being captured into a graph: nothing can be allocated then, and an
+// upload would be recorded instead of made.
+bool is_capturing(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+}
+
 template <typename T>
 hipError_t grow_dev(T *&p, int64_t &cap, int64_t need) {
   if (need <= cap) return hipSuccess;
@@ -431,13 +438,15 @@ struct HostFieldPlan {
   int64_t h_row_of_y_cap = 0, d_row_of_y_cap = 0;
   int64_t d_rows_cap = 0, d_groups_cap = 0, d_lines_cap = 0, d_first_cap = 0;
   // the fused kernels' slots, [0] of the 3D power's mode kernel, [1] of the field
-  // planes, each built on its first use of the plan: 0 not built, 1 built, -1
-  // these sight-lines do not fit
+  // planes: 0 not built, 1 built, -1 these sight-lines do not fit.  A workspace
+  // builds a kind on its first use, and from then on with every new plan, so that a
+  // call under capture finds the slots of columns that the other entry point planned.
   int slots[2] = {0, 0};
   int *h_slots[2] = {nullptr, nullptr}, *d_slots[2] = {nullptr, nullptr};
   int64_t h_slots_cap[2] = {0, 0}, d_slots_cap[2] = {0, 0};
 };
 std::map<Workspace *, HostFieldPlan> g_field_plans;
+int ensure_slots(Workspace *ws, HostFieldPlan *hp, int n, bool planes);
 
 int ensure_field_plan(Workspace *ws, int64_t n, int64_t S, const int32_t *sx, const int32_t *sy,
                       HostFieldPlan **out) {
@@ -505,6 +514,9 @@ int ensure_field_plan(Workspace *ws, int64_t n, int64_t S, const int32_t *sx, co
   hp.sx.assign(sx, sx + S);
   hp.sy.assign(sy, sy + S);
   hp.n = n;
+  // a failure here leaves the slots to their next use
+  if (hp.d_slots[0] && n <= kP3dMaxN) ensure_slots(ws, &hp, (int)n, false);
+  if (hp.d_slots[1] && field_planes_fit((int)n, S)) ensure_slots(ws, &hp, (int)n, true);
   return LYAF_OK;
 }
 
@@ -518,12 +530,13 @@ int ensure_field_plan(Workspace *ws, int64_t n, int64_t S, const int32_t *sx, co
 //   row far above the others, does not fit: slots[0] = -1.
 //   field planes (planes = true): the sums are per sight-line, so a row is cut
 //   where its thread is full, at the average that all threads get.
+// Slots that are not built stay so under capture: the upload would only be recorded.
 // Layout of the upload, in int32: words (x | last of row << 11 | y << 12),
 // sight-lines, first spill of each thread, a pad to 8 bytes, the spill's
 // (sight-line, x) pairs.
 int ensure_slots(Workspace *ws, HostFieldPlan *hp, int n, bool planes) {
   const int kind = planes ? 1 : 0;
-  if (hp->slots[kind] != 0) return LYAF_OK;
+  if (hp->slots[kind] != 0 || is_capturing(ws->stream)) return LYAF_OK;
   static_assert(kP3dModeThreads == kFieldThreads, "one table layout");
   constexpr int T = kFieldThreads;
   const int K = planes ? kFieldSlots : kP3dModeSlots;
@@ -907,9 +920,15 @@ int lyaf_field_skewers(const lyaf_field_params *fp, const void *modes, const dou
   const int64_t n_planes = planes ? H * 2 * kFieldSlotSum : 0;
   if (planes) {
     if ((e = field_planes_attributes((int)N, &resident)) != hipSuccess) return map_err(e);
-    e = grow_dev(ws->field_C, ws->field_C_cap,
-                 n_planes + (int64_t)field_last_parts((int)N, resident) * 2 * kFieldSlotSum);
-  } else {
+    const int64_t need =
+        n_planes + (int64_t)field_last_parts((int)N, resident) * 2 * kFieldSlotSum;
+    // under capture, the three kernels may have the room that the fused one lacks
+    if (need > ws->field_C_cap && is_capturing(st))
+      planes = false;
+    else
+      e = grow_dev(ws->field_C, ws->field_C_cap, need);
+  }
+  if (!planes) {
     if ((e = field_kernel_attributes(&resident)) == hipSuccess &&
         (e = grow_dev(ws->field_T, ws->field_T_cap, 2 * (int64_t)hp->n_rows * N * H)) ==
             hipSuccess)
@@ -991,19 +1010,28 @@ int lyaf_flux_power_3d(const lyaf_power3d_params *pp, int64_t n_lines, const flo
   if ((rc = ensure_slots(ws, hp, (int)n, false))) return rc;
   // the fused kernel whenever the sight-lines fit its registers; a crowded
   // plane (over about 7000 sight-lines, or one very long row) goes through D1
-  const bool modes = hp->slots[0] > 0;
+  bool modes = hp->slots[0] > 0;
   const int64_t H = n / 2 + 1;
   const int nb = p3d_shell_bins((int)n, (int)pp->n_bins);
   int geom_grid = 0, grid = 0;
   hipError_t e;
-  if ((e = p3d_kernel_attributes((int)n, nb, modes, &geom_grid, &grid)) != hipSuccess)
-    return map_err(e);
-  // G, and D1 without the fused kernel
-  const int64_t n_c = n_lines * H + (modes ? 0 : n * (int64_t)hp->n_rows * H);
-  const int64_t p1d_parts = modes ? 0 : (n_lines + kP3dP1dChunk - 1) / kP3dP1dChunk;
-  // P1d, P2d, data shells, geometry shells, P1d partials
-  const int64_t n_shells = (int64_t)grid * 2 * nb;
-  const int64_t n_r = H + n * n + n_shells + (int64_t)geom_grid * 2 * nb + p1d_parts * H;
+  int64_t n_c = 0, n_r = 0, n_shells = 0;
+  const auto sizes = [&]() -> hipError_t {
+    const hipError_t err = p3d_kernel_attributes((int)n, nb, modes, &geom_grid, &grid);
+    // G, and D1 without the fused kernel
+    n_c = n_lines * H + (modes ? 0 : n * (int64_t)hp->n_rows * H);
+    const int64_t p1d_parts = modes ? 0 : (n_lines + kP3dP1dChunk - 1) / kP3dP1dChunk;
+    // P1d, P2d, data shells, geometry shells, P1d partials
+    n_shells = (int64_t)grid * 2 * nb;
+    n_r = H + n * n + n_shells + (int64_t)geom_grid * 2 * nb + p1d_parts * H;
+    return err;
+  };
+  if ((e = sizes()) != hipSuccess) return map_err(e);
+  // under capture, the general kernels may have the room that the fused one lacks
+  if (modes && (n_c > ws->p3d_c_cap || n_r > ws->p3d_r_cap) && is_capturing(st)) {
+    modes = false;
+    if ((e = sizes()) != hipSuccess) return map_err(e);
+  }
   const bool need_geom = ws->p3d_geom_n != (int)n || ws->p3d_geom_nb != nb;
   if (need_geom) ws->p3d_geom_n = ws->p3d_geom_nb = 0;
   if ((e = grow_dev(ws->p3d_c, ws->p3d_c_cap, n_c)) != hipSuccess ||

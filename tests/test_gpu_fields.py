@@ -178,3 +178,60 @@ def test_fused_planes_at_512():
         for name, got in (("b", b), ("v", v)):
             full = ref[name][:S]
             assert np.max(np.abs(got - full)) <= 2 * FIELD_TOL * np.sqrt(np.mean(full * full))
+
+
+def test_capture_of_columns_planned_by_the_other_entry_point():
+    """A call captured into a graph right after the other entry point has planned its
+    columns (on a stream whose buffers earlier columns have grown): the tables of the
+    fused kernels are there before the capture, so an eager call before the first
+    replay, and every replay, give the result of an untouched stream (the power to
+    1e-11 of its largest value: its shell sums are FP64 atomics in any order)."""
+    import torch
+    from paper_1105_4747_amd import lyaf as Lb
+    from synth import fields
+    dev = torch.device("cuda:0")
+    N, nb, box = 512, 200, 120.0
+    rng = np.random.default_rng(31)
+    first = [rng.integers(0, N, 900) for _ in range(2)]
+    second = [rng.integers(0, N, 700) for _ in range(2)]
+    pk, dk = _table(N, box, n=900)
+    p = torch.from_numpy(pk).to(dev)
+    modes = fields.field_modes_white(N, 5, dev)
+    F = torch.exp(-0.3 * torch.rand(900 * N, device=dev))
+    fb = [torch.zeros(900, N, device=dev) for _ in range(2)]
+    pb = [torch.zeros(nb, device=dev, dtype=torch.float64) for _ in range(4)]
+
+    def synthesis(cols):
+        S = len(cols[0])
+        Lb.field_skewers(modes, p, *cols, fb[0][:S], fb[1][:S], N, box, 1.3, 6.5, 73.0, dk)
+
+    def power(cols):
+        S = len(cols[0])
+        Lb.flux_power_3d(F[:S * N], 0.85, *cols, N, box, nb, *pb)
+
+    def result(call, run):
+        for x in fb + pb:
+            x.zero_()
+        run()
+        out = [x.clone() for x in (fb if call is synthesis else pb)]
+        torch.cuda.synchronize()
+        return out
+
+    want = {call: result(call, lambda: call(second)) for call in (synthesis, power)}
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        for call, other in ((synthesis, power), (power, synthesis)):
+            print(f"capture: {call.__name__} of columns planned by {other.__name__}", flush=True)
+            synthesis(first)
+            power(first)
+            other(second)
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=s):
+                call(second)
+            for run in (lambda: call(second), graph.replay, graph.replay, lambda: call(second),
+                        graph.replay):
+                for got, ref in zip(result(call, run), want[call]):
+                    bar = 0.0 if call is synthesis else 1e-11 * float(ref.abs().max())
+                    assert float((got - ref).abs().max()) <= bar
+        assert Lb.status_read() == 0
