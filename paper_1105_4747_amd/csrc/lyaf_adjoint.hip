@@ -242,10 +242,13 @@ __global__ __launch_bounds__(kAdjThreads) void tau_adjoint_kernel(
   // staged margin: a run reaches at most vpx + half from its source, and its outer
   // blocks up to 8 more.  A box of at least two half windows of 6 b or more holds
   // one image of every pair that matters (the others' terms are below exp(-36)), if
-  // the velocities reach less than the box.
+  // the velocities reach less than the box; a window of less than 6 b ends where the
+  // terms matter, so such a box has to hold two reaches.
   const int RH = K.vpx + K.half + kAdjMargin;
-  const bool windowed =
-      kTauTile + 2 * RH <= kAdjChunk && 2 * K.half + 8 <= n && K.vpx < n;
+  const bool one_image = b.window_k >= 6.f
+                             ? 2 * K.half + 8 <= n && K.vpx < n
+                             : 2 * ((K.reach + kAdjMargin + 3) & ~3) + 8 <= n;
+  const bool windowed = kTauTile + 2 * RH <= kAdjChunk && one_image;
   if (windowed) {
     const int cnt = (j_end - j0) + 2 * RH;
     const float *gs = g + off;

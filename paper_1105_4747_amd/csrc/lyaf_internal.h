@@ -43,7 +43,7 @@ struct SkewerConst {
   float inv_dv;  // 1 / dv
   int32_t reach; // max_j (|v_j| + k b_j) / dv, rounded up, plus margin (pixels)
   int32_t n;     // pixels in the skewer
-  int32_t half;  // max_j k b_j / dv, rounded up, plus margin (pixels; n if k = 0, see reach_kernel)
+  int32_t half;  // max_j k b_j / dv, rounded up, plus margin (pixels, at most n; n if k = 0)
   int32_t vpx;   // max_j |v_j| / dv, rounded up, plus margin (pixels, at most n)
 };
 

@@ -199,10 +199,7 @@ __global__ __launch_bounds__(kReachReaders + kWave) void reach_kernel(Batch b) {
     }
     const auto pixels = [&](float x) { return x < 1e8f ? min(n, (int)ceilf(x) + 2) : n; };
     K.reach = b.window_k > 0.f ? pixels(mr) : n;
-    // a window of less than 6 b ends where the terms matter: such boxes are windowed
-    // only where the reach allows it, and summed whole at window_k = 0
-    K.half = b.window_k >= 6.f ? pixels(b.window_k * mb * K.inv_dv)
-                               : (b.window_k > 0.f ? min(n, K.reach + kSkewMargin + 3) : n);
+    K.half = b.window_k > 0.f ? pixels(b.window_k * mb * K.inv_dv) : n;
     K.vpx = pixels(mv * K.inv_dv);
     b.skc[s] = K;
     if (shbad[0]) atomicOr(b.status, LYAF_STATUS_DOMAIN);

@@ -95,6 +95,30 @@ def test_tau_backward_windows(n_pix, dv, v_max):
     assert_per_skewer_close(gg.cpu().numpy(), rg, "dL/dgamma")
 
 
+def test_tau_backward_narrow_window_beside_a_large_velocity():
+    """A window of 2 b (26 pixels of 1 km/s here) keeps its runs when one velocity
+    takes the reach to 480 pixels: a cotangent on one target reaches the sources
+    within the window and its rounding to blocks, and no others (a sum over every
+    target, many times as long, gives exp(-(60 / 12.8)^2) at 60 pixels)."""
+    import torch
+    from paper_1105_4747_amd import lyaf as L
+    n, i = 4096, 2048
+    w = fields.small_workload(n_skewers=1, n_pix=n, seed=47, dv=1.0, gamma=1.0, T0=1.0e4,
+                              window_k=2.0)
+    w.vpec[:] = 0.0
+    w.vpec[100] = 450.0
+    d = OnDevice(w)
+    g = np.zeros(n, np.float32)
+    g[i] = 1.0
+    gd, gv = torch.empty_like(d.delta), torch.empty_like(d.vpec)
+    print("case: adjoint window_k=2, reach 480", flush=True)
+    L.tau_backward(d.delta, d.vpec, d.dv, d.T0, d.gamma, d.offsets, to_dev(g), gd, gv,
+                   window_k=2.0)
+    gd = gd.cpu().numpy()
+    assert (gd[i - 20:i + 21] > 0).all()
+    assert (gd[:i - 50] == 0).all() and (gd[i + 51:] == 0).all()
+
+
 def test_normalise_backward_against_oracle():
     import torch
     from paper_1105_4747_amd import lyaf as L
