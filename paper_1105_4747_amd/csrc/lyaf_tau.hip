@@ -690,7 +690,9 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
                 make_float4(line ? w : 0.f, line ? a : 0.f,
                             line ? v * r : 0.f, line ? C : 1.f);
           } else {
-            slot[(c0 >> 2) + u * (NT / 4)] = make_float4(line ? w : 0.f, r, v, a);
+            // (the r of an empty pixel may be infinite: 0 exp2(-(0 r)^2) has to stay 0)
+            slot[(c0 >> 2) + u * (NT / 4)] =
+                make_float4(line ? w : 0.f, line ? r : 0.f, line ? v : 0.f, line ? a : 0.f);
           }
         } else {
           win = 0u;

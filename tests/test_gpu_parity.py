@@ -152,6 +152,24 @@ def test_tau_empty_pixels_of_any_velocity(shape):
     assert_tau_close(got, oracle_tau(w), f"empty pixels shape {shape}")
 
 
+@pytest.mark.parametrize("shape", [0, 1, 4, 5])
+def test_tau_empty_pixels_of_a_steep_relation(shape):
+    """gamma = 4: T ~ Delta^3, so that the inverse line width at the least density
+    (1e-30, where empty pixels are evaluated) is past the FP32 range; at rest their
+    offset from a target is 0, and they must still contribute nothing.  Lines a pixel
+    wide (T0 = 500 K) take the recurrence shapes to the direct form."""
+    from paper_1105_4747_amd import lyaf as L
+    w = fields.small_workload(n_skewers=2, n_pix=3000, seed=48, gamma=4.0, T0=500.0)
+    w.delta_pivot = 1.0
+    w.delta[:] = 1.0
+    w.vpec[:] = 0.0
+    w.delta[np.r_[0, 70, 1023:1026, 2000:2300, 2999, 3000, 5999]] = 0.0
+    print(f"case: empty pixels, gamma 4, shape={shape}", flush=True)
+    got = gpu_tau(w, flags=L.FLAG_SHAPE(shape)).cpu().numpy()
+    assert L.status_read() == 0
+    assert_tau_close(got, oracle_tau(w), f"empty pixels, gamma 4, shape {shape}")
+
+
 @pytest.mark.parametrize("shape", [0, 4, 5])
 @pytest.mark.parametrize("window_k", [6.0, 9.0])
 def test_tau_short_boxes_of_large_velocities(shape, window_k):
