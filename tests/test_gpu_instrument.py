@@ -164,6 +164,41 @@ def test_instrument_pieces_and_parts(lens, dvs, fwhm, bin_kms, v0):
     assert float(np.max(np.abs(got - want))) <= G_INS * float(np.max(np.abs(want)))
 
 
+@pytest.mark.parametrize("S", [1023, 2051, 8203])
+def test_instrument_wide_and_narrow_skewers_in_turn(S):
+    """Skewers whose taps fit a wave beside ones that take the workgroup (a box of 257
+    to 300 pixels of 0.5 km/s, every tap of it), with four, two and one parts of a
+    skewer per wave, skewers without bins among them: bitwise what calls of 400
+    skewers give, and the first of those against the oracle."""
+    lens = np.array([300, 300, 41, 257, 120, 300, 256])[np.arange(S) % 7]
+    dv = np.array([0.5, 8.0, 8.0, 0.5, 2.0], np.float32)[np.arange(S) % 5]
+    fwhm, bin_kms, v0 = 40.0, 6.0, 1.0
+    nb = np.where(np.arange(S) % 11 == 3, 0, (lens * dv / bin_kms * 0.8).astype(int))
+    off, oo = offs(lens), offs(nb)
+    rng = np.random.default_rng(23)
+    F = np.exp(-rng.exponential(1.0, off[-1])).astype(np.float32)
+    eps = rng.standard_normal(int(oo[-1])).astype(np.float32)
+    g = rng.standard_normal(int(oo[-1])).astype(np.float32)
+    print(f"case: instrument wide and narrow, {S} skewers", flush=True)
+    got = gpu_instrument(F, dv, off, oo, fwhm, bin_kms, v0, eps, 0.02)
+    grad = gpu_instrument_bwd(g, dv, off, oo, fwhm, bin_kms, v0)
+    for a in range(0, S, 400):
+        b = min(a + 400, S)
+        p, q = slice(off[a], off[b]), slice(oo[a], oo[b])
+        o1, o2 = off[a:b + 1] - off[a], oo[a:b + 1] - oo[a]
+        assert np.array_equal(got[q], gpu_instrument(F[p], dv[a:b], o1, o2, fwhm, bin_kms, v0,
+                                                     eps[q], 0.02))
+        assert np.array_equal(grad[p], gpu_instrument_bwd(g[q], dv[a:b], o1, o2, fwhm, bin_kms,
+                                                          v0))
+        if a == 0:
+            d64 = dv[:b].astype(np.float64)
+            want = O.instrument(F[p].astype(np.float64), o1, d64, o2, fwhm, bin_kms, v0,
+                                eps[q].astype(np.float64), 0.02)
+            assert float(np.max(np.abs(got[q] - want))) <= F_ABS
+            want = O.instrument_backward(g[q].astype(np.float64), o1, d64, o2, fwhm, bin_kms, v0)
+            assert float(np.max(np.abs(grad[p] - want))) <= G_INS * float(np.max(np.abs(want)))
+
+
 def test_instrument_autograd_and_noise_independence():
     import torch
     from paper_1105_4747_amd import lyaf as L
