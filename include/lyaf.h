@@ -425,8 +425,10 @@ int lyaf_status_read(void *stream, uint32_t *device_status);
  *                the kernel); "tau_plain" the plain full-sum kernels
  *   "normalise", "normalise_backward", "tau_adjoint", "instrument",
  *   "instrument_backward", "flux_pdf", "flux_power",
- *   "field_planes", "field_z" (lyaf_field_skewers on grids of 512 and 1024),
- *   "field_ky", "field_kx", "field_z" (its three kernels otherwise),
+ *   "field_ky", "field_kx", "field_z" (the stages of lyaf_field_skewers; in its
+ *                fused form, on grids of 512 and 1024, "field_ky" is the kernel of
+ *                both transforms across the sight-lines, "field_kx" the sum of its
+ *                last plane, and "field_planes" both together),
  *   "flux_power_3d" (every kernel of lyaf_flux_power_3d).
  * Launches under stream capture (plans, caller graphs) are not recorded, and
  * recording stops after 65536 launches.  lyaf_kernel_timing(0) stops and

@@ -971,9 +971,16 @@ int lyaf_field_skewers(const lyaf_field_params *fp, const void *modes, const dou
   a.v_z = v_z;
   a.twiddle = ws->ps_twiddle;
   if (planes) {
-    if ((e = timed("field_planes", st, [&] { return launch_field_planes(a, resident, st); })) !=
-        hipSuccess)
-      return map_err(e);
+    // the stage across (kx, ky) is recorded as a whole, and its two kernels under the
+    // names of the general path's, which together stand for the same stage
+    e = timed("field_planes", st, [&] {
+      const hipError_t err =
+          timed("field_ky", st, [&] { return launch_field_planes(a, resident, st); });
+      return err != hipSuccess
+                 ? err
+                 : timed("field_kx", st, [&] { return launch_field_last(a, resident, st); });
+    });
+    if (e != hipSuccess) return map_err(e);
     return map_err(timed("field_z", st, [&] { return launch_field_z_planes(a, st); }));
   }
   if ((e = timed("field_ky", st, [&] { return launch_field_ky(a, resident, st); })) !=

@@ -567,6 +567,10 @@ hipError_t launch_field_planes(const FieldArgs &a, int resident, hipStream_t st)
   else
     hipLaunchKernelGGL((field_planes_kernel<8, kFieldSlots>), dim3(resident), dim3(kFieldThreads),
                        sizeof(FieldPlanesLds<8>), st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_field_last(const FieldArgs &a, int resident, hipStream_t st) {
   hipLaunchKernelGGL(field_last_kernel, dim3((2 * kFieldSlotSum + 255) / 256), dim3(256), 0, st,
                      a, field_last_parts(a.N, resident));
   return hipGetLastError();

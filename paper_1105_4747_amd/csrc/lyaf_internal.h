@@ -226,6 +226,7 @@ bool field_planes_fit(int N, int64_t n_lines);
 int field_last_parts(int N, int resident);  // workgroups with a part of the last plane
 hipError_t field_planes_attributes(int N, int *resident);
 hipError_t launch_field_planes(const FieldArgs &a, int resident, hipStream_t st);
+hipError_t launch_field_last(const FieldArgs &a, int resident, hipStream_t st);
 hipError_t launch_field_z_planes(const FieldArgs &a, hipStream_t st);
 int field_ky_columns(int N);  // mz values per field_ky work item
 // Sets the kernels' LDS limits once per device; *ky_resident: resident

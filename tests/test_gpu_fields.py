@@ -235,3 +235,25 @@ def test_capture_of_columns_planned_by_the_other_entry_point():
                     bar = 0.0 if call is synthesis else 1e-11 * float(ref.abs().max())
                     assert float((got - ref).abs().max()) <= bar
         assert Lb.status_read() == 0
+
+
+@pytest.mark.parametrize("N", [64, 512])
+def test_kernel_timing_names_of_every_path(N):
+    """A program that times the synthesis reads the same three names whichever kernels
+    a grid takes; the fused form records its two together as well."""
+    from paper_1105_4747_amd import lyaf as Lb
+    from synth import fields
+    modes = fields.field_modes_white(N, 3, "cuda:0")
+    pk, dk = _table(N, 60.0, n=900)
+    print(f"field synthesis timing: N={N}", flush=True)
+    Lb.kernel_timing(True)
+    for _ in range(2):
+        _run(modes, pk, dk, 1.0, 60.0, 6.5, 73.0, np.arange(20), np.arange(20))
+    ms = {}
+    for name in ("field_ky", "field_kx", "field_z", "field_planes"):
+        ms[name], n = Lb.kernel_timing_read(name)
+        assert n == (0 if name == "field_planes" and N == 64 else 2)
+    Lb.kernel_timing(False)
+    assert all(ms[k] > 0 for k in ("field_ky", "field_kx", "field_z"))
+    if N == 512:
+        assert ms["field_planes"] >= ms["field_ky"]
