@@ -135,6 +135,44 @@ def test_tau_recurrence_with_and_without_its_clamp(shape, v_max, a):
     assert_tau_close(got, oracle_tau(w), f"clamp shape {shape}")
 
 
+@pytest.mark.parametrize("shape,a,RH,density", [(4, 0.24, 476, 0.2), (5, 0.36, 200, 0.43)])
+def test_tau_recurrence_is_the_same_with_its_clamp(shape, a, RH, density):
+    """The tile leaves the clamp of G_0 out where 2 a^2 (2 RH + 9) <= 120 for its largest
+    a and its margin RH = (reach + 15) & ~3.  A skewer whose lines are all of one width
+    and of velocity +V or -V by turns of 32 pixels stays below; with one pixel at a lower
+    density, whose line is narrower, the tiles that stage it take the clamp, and that line
+    is met, where those of velocity -V around its mirror position are centred, at an
+    exponent past the FP32 range.  A clamped factor only ever multiplies an E_0 that is 0,
+    so tau is bitwise the same wherever that line's own Gaussian is 0, and finite."""
+    from paper_1105_4747_amd import lyaf as L
+    dv, n, k, p = 4.0, 6000, 6.0, 2082
+    w = fields.small_workload(n_skewers=1, n_pix=n, seed=49, dv=dv, gamma=1.5, window_k=k)
+    w.delta_pivot = 1.0
+    w.delta[:] = np.exp(np.abs(np.log(w.delta)))  # from 1 on: one temperature
+    b = dv * math.sqrt(math.log2(math.e)) / a
+    w.T0[:] = (b / 0.12845065404917816) ** 2
+    V = np.float32((RH - 17) * dv - k * b)
+    plus = np.arange(n) // 32 % 2 == 1
+    w.vpec[:] = np.where(plus, V, -V)
+    # the line's group of 4 or 8 sources keeps its outermost windows without it
+    assert plus[p] and p % 4 in (1, 2)
+    margin = (math.ceil((float(V) + k * b) / dv) + 2 + 15) & ~3
+    bound = lambda a: 2 * a * a * (2 * margin + 9)  # noqa: E731
+    narrow = a * density ** -0.25
+    assert margin == RH and bound(a) <= 118 and bound(narrow) >= 122
+    assert 2 * narrow ** 2 * ((2 * float(V) + k * b) / dv - 1) > 128
+    print(f"case: clamp, shape={shape} bounds {bound(a):.0f} and {bound(narrow):.0f}", flush=True)
+    without = gpu_tau(w, flags=L.FLAG_SHAPE(shape)).cpu().numpy()
+    w.delta[p] = density
+    clamped = gpu_tau(w, flags=L.FLAG_SHAPE(shape)).cpu().numpy()
+    assert L.status_read() == 0
+    assert np.all(np.isfinite(without)) and np.all(np.isfinite(clamped))
+    # exp2(-t^2) is 0 in FP32 from |t| = 12.3 on (2^-150), t = a per pixel
+    away = np.abs(np.arange(n) - (p + float(V) / dv)) > 12.5 / a
+    assert np.array_equal(without[away], clamped[away])
+    assert not np.array_equal(without[~away], clamped[~away])
+
+
 @pytest.mark.parametrize("shape", [0, 4, 5])
 def test_tau_empty_pixels_of_any_velocity(shape):
     """Empty pixels (Delta = 0) contribute nothing whatever their velocity, which
@@ -381,6 +419,46 @@ def test_normalise_refused_step_is_not_left_to_one_workgroup(P):
     print(f"rescale of {P} pixels: {times[1.08] * 1e3:.1f} us accepted, "
           f"{times[1.2] * 1e3:.1f} us refused", flush=True)
     assert times[1.2] <= 2 * times[1.08]
+
+
+def test_normalise_in_several_passes():
+    """Batches large enough that every pass is a kernel of its own, whose first step is
+    not the last: biased samples, a sample of zeros alone (the passes start in FP32), and
+    the verdicts that only unsampled pixels reveal.  An ordinary batch after each one, on
+    the same stream, finds the counters between the passes clear."""
+    import torch
+    from paper_1105_4747_amd import lyaf as L
+    P = 8 * (1 << 20) + 3
+    sampled = np.arange(SAMPLE_N, dtype=np.int64) * P // SAMPLE_N
+    rng = np.random.default_rng(8)
+    easy = np.exp(rng.normal(-0.5, 1.0, P)).astype(np.float32)
+    d_easy = torch.from_numpy(easy).to("cuda:0")
+    A_easy, _ = O.mean_flux_A(easy.astype(np.float64), 0.7)
+
+    def batch(sample, others, nan_at=None):
+        raw = np.full(P, others, np.float32) if np.isscalar(others) else others.copy()
+        raw[sampled] = sample
+        if nan_at is not None:
+            raw[nan_at] = np.nan
+        return raw
+
+    lognormal = (easy * 0.4).astype(np.float32)
+    for name, raw, status in (("biased 1.2", batch(1.0, 1.2), 0),
+                              ("biased 1.6", batch(1.0, 1.6), 0),
+                              ("sample of zeros", batch(0.0, lognormal), 0),
+                              ("no root", batch(1.0, 0.0), L.STATUS_NOROOT),
+                              ("NaN", batch(1.0, 1.2, 1027), L.STATUS_DOMAIN)):
+        assert 1027 not in sampled
+        print(f"case: several passes, {name}", flush=True)
+        L.status_read()
+        _, _, A = gpu_normalise(torch.from_numpy(raw).to("cuda:0"), 0.8)
+        assert L.status_read() == status
+        if status == 0:
+            A_ref, _ = O.mean_flux_A(raw.astype(np.float64), 0.8)
+            assert abs(float(A.cpu()) / A_ref - 1) <= A_REL
+        _, _, A = gpu_normalise(d_easy, 0.7)
+        assert L.status_read() == 0
+        assert abs(float(A.cpu()) / A_easy - 1) <= A_REL
 
 
 def test_normalise_one_workgroup_from_a_far_start():
