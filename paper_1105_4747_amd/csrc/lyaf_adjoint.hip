@@ -63,18 +63,18 @@ __device__ __forceinline__ double adj_rcp(double x) {
   return fma(r, fma(-x, r, 1.0), r);
 }
 
-// A source: w, r, a = dv r, its gradient of tau's three sums.
+// c 2^y to FP32's exp2 and a first-order term for the part of y that its argument drops.
 __device__ __forceinline__ double adj_scaled_exp2(float c, double y) {
   const float yh = (float)y;
   const double e = (double)c * (double)aexp2(yh);
   return fma(e, kLn2 * (y - (double)yh), e);
 }
+// A source's w and r, each rounded once, and log2 D.
 struct AdjSource {
-  float delta, v, w, r, l2D;
+  float w, r, l2D;
 };
-__device__ __forceinline__ AdjSource adj_source(const SkewerConst &K, float pivot, float delta,
-                                                float v) {
-  AdjSource s = {delta, v, 0.f, K.R, 0.f};
+__device__ __forceinline__ AdjSource adj_source(const SkewerConst &K, float pivot, float delta) {
+  AdjSource s = {0.f, K.R, 0.f};
   if (delta > 0.f) {
     const float D = fmaxf(fminf(delta, pivot), 1e-30f);
     s.l2D = alog2(D);
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(kAdjThreads) void tau_adjoint_kernel(
     // an invalid density sets the sticky domain bit (the reach pass may not
     // have read Delta)
     bad |= !(delta >= 0.f) || !isfinite(delta);
-    const AdjSource s = adj_source(K, b.pivot, delta, v);
+    const AdjSource s = adj_source(K, b.pivot, delta);
     double S0, S1, S2;
     if (windowed) {
       const bool line = s.w > 0.f;

@@ -334,8 +334,9 @@ __device__ inline void bin_range(const InsTile &t, int &j0, int &cnt) {
 constexpr int kTileRows = 320;  // rows of a plane of a staged FP32 tile, 5 blocks of 64
 static_assert(8 * kTileRows >= kInsTile + kInsTapBlock + 16, "a staged tile must fit");
 
-// Prefix sums of a convolved tile, then its bins: each bin is the difference of the interpolated cumulative integral at its edges
-// e(j) = e_lo + j q (relative to p0), divided by its width.
+// Prefix sums of a convolved tile, then its bins: each bin is the difference of the
+// interpolated cumulative integral at its edges e(j) = e_lo + j q (relative to p0),
+// divided by its width.
 __device__ void finish_tile(const InsArgs &a, const InsSkewer &k, const InsTile &t,
                             const double (&acc)[kInsPerLane], double Z, double *pre,
                             double *red) {
@@ -802,7 +803,8 @@ __global__ __launch_bounds__(kInsThreads) void instrument_backward_kernel(
     Z = block_sum_d(z_part, d.red);  // its barriers publish the staged values and the taps
 #pragma unroll
     for (int q = 0; q < kInsPerLane; ++q) acc[q] = 0.0;
-    if ((int)(threadIdx.x & ~63u) * kInsPerLane < span) conv_walk<kTileRows>(tbp, acc, d.f + threadIdx.x, d.h);
+    if ((int)(threadIdx.x & ~63u) * kInsPerLane < span)
+      conv_walk<kTileRows>(tbp, acc, d.f + threadIdx.x, d.h);
   } else {
     const auto src = [&](int x) -> double {
       uint32_t i = base + (uint32_t)x;
@@ -922,49 +924,49 @@ __device__ __forceinline__ void ins_backward_pieces(const InsArgs &a, const InsS
     for (int p = 0; p < kPast; ++p) Gx[p] = 0.0;
     for (;;) {
       if (im.cnt > 0 && im.L <= im.L_hi) {
-      const int m = (im.cnt + 63) >> 6;
-#pragma unroll
-      for (int r = 0; r < kBwdLaneBins; ++r)
-        if (r < m && m * lane + r >= im.cnt) v[r] = 0.0f;
-      double run = 0.0;
-#pragma unroll
-      for (int r = 0; r < kBwdLaneBins; ++r)
-        if (r < m) run += (double)v[r];
-      double s = wave_below_d(wave_scan_d(run));
-      wave_lds_order();
-      double *P = lds + m * lane;
-      P[0] = s;
-#pragma unroll
-      for (int r = 0; r < kBwdLaneBins; ++r)
-        if (r < m) {
-          s += (double)v[r];
-          if (r + 1 < m || lane == 63) P[r + 1] = s;
+        const int m = (im.cnt + 63) >> 6;
+  #pragma unroll
+        for (int r = 0; r < kBwdLaneBins; ++r)
+          if (r < m && m * lane + r >= im.cnt) v[r] = 0.0f;
+        double run = 0.0;
+  #pragma unroll
+        for (int r = 0; r < kBwdLaneBins; ++r)
+          if (r < m) run += (double)v[r];
+        double s = wave_below_d(wave_scan_d(run));
+        wave_lds_order();
+        double *P = lds + m * lane;
+        P[0] = s;
+  #pragma unroll
+        for (int r = 0; r < kBwdLaneBins; ++r)
+          if (r < m) {
+            s += (double)v[r];
+            if (r + 1 < m || lane == 63) P[r + 1] = s;
+          }
+        wave_lds_order();
+        const int cnt = im.cnt;
+        const double tc = wave_uniform(im.t0 - (double)im.k0), top = wave_uniform((double)cnt);
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // the pixels' FP64 edges are not kept across pieces
+        const auto cum = [&](int x) -> double {  // C at the lower edge of staged pixel x
+          const double t = fmin(fmax(__builtin_fma((double)x, k.inv_q, tc), 0.0), top);
+          const int kb = min((int)t, cnt - 1);
+          const double *q = lds + kb;
+          return __builtin_fma(t - (double)kb, q[1] - q[0], q[0]);
+        };
+        double c0 = cum(8 * ln);
+  #pragma unroll
+        for (int p = 0; p < 8; ++p) {
+          const double c1 = cum(8 * ln + p + 1);
+          G[p] += c1 - c0;
+          c0 = c1;
+          if (p == 2 || p == 5) __builtin_amdgcn_sched_barrier(0);  // few in flight: registers
         }
-      wave_lds_order();
-      const int cnt = im.cnt;
-      const double tc = wave_uniform(im.t0 - (double)im.k0), top = wave_uniform((double)cnt);
-      int ln = lane;
-      asm volatile("" : "+v"(ln));  // the pixels' FP64 edges are not kept across pieces
-      const auto cum = [&](int x) -> double {  // C at the lower edge of staged pixel x
-        const double t = fmin(fmax(__builtin_fma((double)x, k.inv_q, tc), 0.0), top);
-        const int kb = min((int)t, cnt - 1);
-        const double *q = lds + kb;
-        return __builtin_fma(t - (double)kb, q[1] - q[0], q[0]);
-      };
-      double c0 = cum(8 * ln);
-#pragma unroll
-      for (int p = 0; p < 8; ++p) {
-        const double c1 = cum(8 * ln + p + 1);
-        G[p] += c1 - c0;
-        c0 = c1;
-        if (p == 2 || p == 5) __builtin_amdgcn_sched_barrier(0);  // few in flight: registers
-      }
-#pragma unroll
-      for (int p = 0; p < kPast; ++p)
-        if (kInsPiece + 64 * p < need) {
-          const int x = kInsPiece + 64 * p + ln;
-          Gx[p] += cum(x + 1) - cum(x);
-        }
+  #pragma unroll
+        for (int p = 0; p < kPast; ++p)
+          if (kInsPiece + 64 * p < need) {
+            const int x = kInsPiece + 64 * p + ln;
+            Gx[p] += cum(x + 1) - cum(x);
+          }
       }
       if (im.L >= im.L_hi) break;
       im = image(c, wave_uniform(im.L + 1.0), im.L_hi);

@@ -100,8 +100,9 @@ constexpr int kMaxPartialBlocks = 512;  // workgroups of a root-find pass
 constexpr int kPartStride = 8;          // doubles per workgroup partial
 constexpr int kSampleN = 8192;          // pixels the root-find samples first
 constexpr int kSampleCap = 16384;       // room for the sample in the partials allocation
-// The partials allocation also holds the sample (up to kSampleCap floats)
-// after the two partial buffers.
+// The partials allocation holds the workgroups' partials of a pass, as much again
+// unused (the scratch size of the allocation-free rescale is public), and the sample
+// (up to kSampleCap floats).
 constexpr int64_t kPartialsDoubles = 2 * kPartStride * kMaxPartialBlocks + kSampleCap / 2;
 static_assert(kSampleN <= kSampleCap, "the sample fits its room");
 constexpr double kNormAcceptStep = 1e-5;

@@ -756,9 +756,9 @@ hipError_t launch_norm(int64_t n_pix, float *tau, float *F, double target_F, dou
 }
 
 // ---------------------------------------------------------------------------
-// Allocation-free variant: the root-find's scratch (the FP64 partials of two
-// passes and room for the sample, the iteration states, and a status word for
-// callers that pass none) lives in one file-scope device array instead of
+// Allocation-free variant: the root-find's scratch (the FP64 partials of a pass
+// and the sample, the iteration states, and a status word for callers that pass
+// none) lives in one file-scope device array instead of
 // a workspace.  The passes use at most kMaxPartialBlocks workgroups and a
 // fixed sample whatever n_pix is, so this fixed size serves every batch.  In
 // host code `scratch` names a host-side stand-in, not device memory: the

@@ -310,20 +310,21 @@ __global__ __launch_bounds__(kYThreads) void p3d_y_kernel(P3dArgs a, int lgC, in
 }
 
 // The modes of one mz at a time, straight from the sight-lines' transforms: no
-// D1 in memory.  Workgroup b takes an equal run of the (mz, p) sequence, p = 0 ..
-// n/2 standing for the pair mx = p, -p, so it stays on one mz (two at most) and
-// holds that mz's weighted G_s in registers, up to kModeSlots sight-lines per
-// thread.  A thread owns whole rows y (its sight-lines of a row are consecutive
-// slots, the last one flagged), so D1(+-p, y, mz) is a sum in one thread, stored
-// without atomics; the products of G with cos and sin serve both signs of mx
-// (four FMAs per sight-line for two modes).  Rows with more sight-lines than the
-// slots read the rest from memory in every step (at most kModeSpill).  The two
-// columns are transformed along y in LDS (radix 4, then 2; one element of
-// padding per 8 spreads the passes' strided writes over the banks), and the
-// modes (+-p, +-my), which share a shell, enter the LDS shell sums as one term.
-// Bound by LDS traffic (bank-conflicted table reads and pass writes: 2.8 ms of
-// LDS cycles at n = 1024 and 6250 sight-lines) and FP64 issue (2.2 ms).  There it
-// takes 4.4 ms, where the D1 form took 3.25 + 5.49 ms (and 8.6 GB of workspace).
+// D1 in memory.  Workgroup b takes an equal run of the (mz, p) sequence, p = 0 .. n/2
+// standing for the pair mx = p, -p, so it meets few mz (two at n = 1024, up to six at
+// 2048, where a compute unit holds one workgroup) and holds the present one's
+// weighted G_s in registers, up to kModeSlots sight-lines per thread.  A thread owns
+// whole rows y (its sight-lines of a row are consecutive slots, the last one
+// flagged), so D1(+-p, y, mz) is a sum in one thread, stored without atomics; the
+// products of G with cos and sin serve both signs of mx (four FMAs per sight-line for
+// two modes).  Rows with more sight-lines than the slots read the rest from memory in
+// every step (at most kP3dMaxSpill).  The two columns are transformed along y in LDS
+// (radix 4, then 2; one element of padding per 8 spreads the passes' strided writes
+// over the banks), and the modes (+-p, +-my), which share a shell, enter the LDS
+// shell sums as one term. Bound by LDS traffic (bank-conflicted table reads and pass
+// writes: 2.8 ms of LDS cycles at n = 1024 and 6250 sight-lines) and FP64 issue (2.2
+// ms).  There it takes 4.4 ms, where the D1 form took 3.25 + 5.49 ms (and 8.6 GB of
+// workspace).
 constexpr int kModeThreads = kP3dModeThreads;
 constexpr int kModeSlots = kP3dModeSlots;
 

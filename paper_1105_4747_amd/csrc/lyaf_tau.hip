@@ -24,8 +24,9 @@
 //                       targets, visits the contiguous run of source groups
 //                       whose windows reach it, and sums the streams in a DPP
 //                       butterfly.
-//   Short or very wide skewers (tile + 2 reach > N) take a full-sum path over
-//   every source with the minimal periodic image chosen per pair.
+//   Boxes shorter than twice the reach (with its margin), and reaches beyond what a
+//   tile stages, take a full-sum path over every source with the minimal periodic
+//   image chosen per pair.
 //   tau_plain_kernel    the literal full O(N^2) sum, one thread per target,
 //                       naive FP32 accumulation (the comparison baseline).
 #include <math.h>
