@@ -118,10 +118,28 @@ hipError_t timed_kernel(const char *name, hipStream_t st, F &&launch) {
 }
 
 // Whether `st` is being captured into a graph: nothing can be allocated then, and an
-// upload would be recorded instead of made.
+// upload on it would be recorded instead of made.
 bool is_capturing(hipStream_t st) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   return hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+}
+
+// An upload that is made now, while another stream is captured: on a stream of its
+// own, complete on return.
+hipError_t upload_beside_capture(void *dst, const void *src, size_t bytes) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // exchanged for the caller's
+  hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) return e;
+  hipStream_t own = nullptr;
+  e = hipStreamCreateWithFlags(&own, hipStreamNonBlocking);
+  if (e == hipSuccess) {
+    e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, own);
+    const hipError_t done = hipStreamSynchronize(own);
+    if (e == hipSuccess) e = done;
+    (void)hipStreamDestroy(own);
+  }
+  const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
+  return e != hipSuccess ? e : back;
 }
 
 template <typename T>
@@ -438,15 +456,13 @@ struct HostFieldPlan {
   int64_t h_row_of_y_cap = 0, d_row_of_y_cap = 0;
   int64_t d_rows_cap = 0, d_groups_cap = 0, d_lines_cap = 0, d_first_cap = 0;
   // the fused kernels' slots, [0] of the 3D power's mode kernel, [1] of the field
-  // planes: 0 not built, 1 built, -1 these sight-lines do not fit.  A workspace
-  // builds a kind on its first use, and from then on with every new plan, so that a
-  // call under capture finds the slots of columns that the other entry point planned.
+  // planes, each built on its first use of the plan: 0 not built, 1 built, -1
+  // these sight-lines do not fit
   int slots[2] = {0, 0};
   int *h_slots[2] = {nullptr, nullptr}, *d_slots[2] = {nullptr, nullptr};
   int64_t h_slots_cap[2] = {0, 0}, d_slots_cap[2] = {0, 0};
 };
 std::map<Workspace *, HostFieldPlan> g_field_plans;
-int ensure_slots(Workspace *ws, HostFieldPlan *hp, int n, bool planes);
 
 int ensure_field_plan(Workspace *ws, int64_t n, int64_t S, const int32_t *sx, const int32_t *sy,
                       HostFieldPlan **out) {
@@ -514,9 +530,6 @@ int ensure_field_plan(Workspace *ws, int64_t n, int64_t S, const int32_t *sx, co
   hp.sx.assign(sx, sx + S);
   hp.sy.assign(sy, sy + S);
   hp.n = n;
-  // a failure here leaves the slots to their next use
-  if (hp.d_slots[0] && n <= kP3dMaxN) ensure_slots(ws, &hp, (int)n, false);
-  if (hp.d_slots[1] && field_planes_fit((int)n, S)) ensure_slots(ws, &hp, (int)n, true);
   return LYAF_OK;
 }
 
@@ -530,13 +543,15 @@ int ensure_field_plan(Workspace *ws, int64_t n, int64_t S, const int32_t *sx, co
 //   row far above the others, does not fit: slots[0] = -1.
 //   field planes (planes = true): the sums are per sight-line, so a row is cut
 //   where its thread is full, at the average that all threads get.
-// Slots that are not built stay so under capture: the upload would only be recorded.
+// Under capture (of a call whose columns the other entry point planned) a table that
+// an earlier plan has allocated is built and uploaded beside the capture; without one
+// the slots stay unbuilt, and the call takes the general kernels.
 // Layout of the upload, in int32: words (x | last of row << 11 | y << 12),
 // sight-lines, first spill of each thread, a pad to 8 bytes, the spill's
 // (sight-line, x) pairs.
 int ensure_slots(Workspace *ws, HostFieldPlan *hp, int n, bool planes) {
   const int kind = planes ? 1 : 0;
-  if (hp->slots[kind] != 0 || is_capturing(ws->stream)) return LYAF_OK;
+  if (hp->slots[kind] != 0) return LYAF_OK;
   static_assert(kP3dModeThreads == kFieldThreads, "one table layout");
   constexpr int T = kFieldThreads;
   const int K = planes ? kFieldSlots : kP3dModeSlots;
@@ -587,6 +602,9 @@ int ensure_slots(Workspace *ws, HostFieldPlan *hp, int n, bool planes) {
   const int64_t pad = ((int64_t)2 * K * T + T + 2) & ~int64_t(1);
   const int64_t words = pad + 2 * (int64_t)n_spill;
   hipError_t e;
+  const bool capturing = is_capturing(ws->stream);
+  if (capturing && (words > hp->h_slots_cap[kind] || words > hp->d_slots_cap[kind]))
+    return LYAF_OK;
   if ((e = grow_host(hp->h_slots[kind], hp->h_slots_cap[kind], words)) != hipSuccess ||
       (e = grow_dev(hp->d_slots[kind], hp->d_slots_cap[kind], words)) != hipSuccess)
     return map_err(e);
@@ -614,9 +632,13 @@ int ensure_slots(Workspace *ws, HostFieldPlan *hp, int n, bool planes) {
     }
   }
   sf[T] = ns;
-  if ((e = hipMemcpyAsync(hp->d_slots[kind], hp->h_slots[kind], sizeof(int) * (size_t)words,
-                          hipMemcpyHostToDevice, ws->stream)) != hipSuccess)
-    return map_err(e);
+  const size_t bytes = sizeof(int) * (size_t)words;
+  // no kernel reads the table meanwhile: planning the columns waited for the stream,
+  // and nothing of this kind has been launched on them
+  e = capturing ? upload_beside_capture(hp->d_slots[kind], hp->h_slots[kind], bytes)
+                : hipMemcpyAsync(hp->d_slots[kind], hp->h_slots[kind], bytes,
+                                 hipMemcpyHostToDevice, ws->stream);
+  if (e != hipSuccess) return map_err(e);
   hp->slots[kind] = 1;
   return LYAF_OK;
 }

@@ -183,7 +183,7 @@ def test_fused_planes_at_512():
 def test_capture_of_columns_planned_by_the_other_entry_point():
     """A call captured into a graph right after the other entry point has planned its
     columns (on a stream whose buffers earlier columns have grown): the tables of the
-    fused kernels are there before the capture, so an eager call before the first
+    fused kernels are made beside the capture, so an eager call before the first
     replay, and every replay, give the result of an untouched stream (the power to
     1e-11 of its largest value: its shell sums are FP64 atomics in any order)."""
     import torch
