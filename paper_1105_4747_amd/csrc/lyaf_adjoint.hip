@@ -16,20 +16,21 @@
 // wave (the lanes' largest half window): target less centre is the same integer
 // m on every lane, t = m a + t_c with a = dv r and |t_c| <= a / 2, and the run is
 // no longer than the widest of 64 neighbouring lines.  Per block of eight targets
-// the Gaussian follows a product recurrence outwards from the block's middle
-// (three exp2; the tau kernel's, from one end with two, put 1e-7 more on the
-// velocity gradients), and the sums are moments about that middle, B_n =
-// sum_k k^n g E, folded every 16 targets into FP64 moments in m, from which
+// the Gaussian follows a product recurrence outwards from two of them (four exp2), and
+// the sums are moments about the block's middle, B_n = sum_k k^n g E, folded every 16
+// targets into FP64 moments in m, from which
 //   sum g E t = a M1 + t_c M0,  sum g E t^2 = a^2 M2 + 2 a t_c M1 + t_c^2 M0
 // (M1 is signed and cancels across the line centre).  A wave with a line too
 // narrow for the recurrence evaluates every exp2.  Short or wide skewers sum
 // over every target with the minimal image chosen per pair.  The per-skewer
 // T0/gamma terms are summed in FP64 per workgroup and then per skewer in a fixed
-// order.  Bound by VALU issue: 4096 skewers of 2048 pixels at 2 km/s 246 -> 220 us
-// (6.9 operations a visited pair, where the Kahan-folded direct form took 9), 37
-// ragged ones of up to 8192 31 -> 21 us.  w and r are rounded once, from FP64: the
-// gradients' errors against 64 bits stay at or below the direct form's (velocity
-// 1.75e-7 -> 1.67e-7, density 1.15e-7 -> 1.15e-7 at 2 km/s).
+// order.  Bound by VALU issue: 4096 skewers of 2048 pixels at 2 km/s, forward and
+// backward, 501 us; 480 with a recurrence outwards from the middle alone (three exp2, its
+// kernel 220 us where the Kahan-folded direct form's took 246), which is not kept for
+// its errors.  Errors against 64 bits over 16 seeds at six settings, relative to the
+// direct form's: velocity 0.80-0.94, density 0.82-0.97, gamma 0.92-1.00, T0 0.96-1.02;
+// from the middle alone gamma 1.02-1.15 and T0 1.01-1.06, as its E kept the mean error
+// of 4.75 exp2.
 #include <math.h>
 
 #include <type_traits>
@@ -47,6 +48,10 @@ constexpr int kAdjChunk = 2048;                     // targets staged in LDS at 
 constexpr int kAdjMargin = 12;                      // staged targets beyond the reach
 constexpr float kAdjMaxA = 0.25f;                   // coarsest grid of the recurrence
 constexpr float kAdjMaxExp = 120.f;                 // exponent of the recurrence's ratio
+// The hardware's exp2 is 3.2e-9 too small on average (gfx950, 2^22 arguments in each of
+// nine ranges between -10 and 0.5), which every sum of the gradients' would keep; an E
+// of the recurrence holds three exp2 on average.
+constexpr double kAdjChainMean = 1.0 + 3.0 * 3.2e-9;
 
 __device__ __forceinline__ int adj_wave_max(int x) {
 #pragma unroll
@@ -69,18 +74,23 @@ __device__ __forceinline__ double adj_scaled_exp2(float c, double y) {
   const double e = (double)c * (double)aexp2(yh);
   return fma(e, kLn2 * (y - (double)yh), e);
 }
-// A source's w and r, each rounded once, and log2 D.
+// A source: r (not rounded), a = dv r rounded once, w times that rounding (a line's
+// integral over the targets goes as w / a), log2 D.
 struct AdjSource {
-  float w, r, l2D;
+  double w, r;
+  float a, l2D;
 };
 __device__ __forceinline__ AdjSource adj_source(const SkewerConst &K, float pivot, float delta) {
-  AdjSource s = {0.f, K.R, 0.f};
+  AdjSource s = {0.0, K.R, 0.f, 0.f};
   if (delta > 0.f) {
     const float D = fmaxf(fminf(delta, pivot), 1e-30f);
     s.l2D = alog2(D);
     const double x = (double)K.gm1 * (double)s.l2D;
-    s.w = (float)((double)delta * (double)delta * adj_scaled_exp2(K.W, kTempExpW * x));
-    s.r = (float)adj_scaled_exp2(K.R, kTempExpR * x);
+    s.r = adj_scaled_exp2(K.R, kTempExpR * x);
+    const double a = (double)K.dv * s.r;
+    s.a = (float)a;
+    s.w = (double)delta * (double)delta * adj_scaled_exp2(K.W, kTempExpW * x) * (double)s.a *
+          adj_rcp(a);
   }
   return s;
 }
@@ -94,7 +104,7 @@ __device__ __forceinline__ void adjoint_run(const float *gl, int p, int H, float
                                             bool chain, double &S0, double &S1, double &S2) {
   double M0 = 0.0, M1 = 0.0, M2 = 0.0;
   const int left = (H + 3) >> 3, right = (H + 4) >> 3;  // blocks beside the central one
-  const float C = aexp2(-2.f * a * a);
+  const float C = aexp2(-2.f * a * a), C4 = aexp2(-8.f * a * a);
   float B0, B1, B2;  // moments about the first block's middle, up to two blocks
   // the eight targets around m = 8 i, added to the moments about 8 (i - O)
   const auto block = [&](auto form, auto O, int i) {
@@ -102,22 +112,20 @@ __device__ __forceinline__ void adjoint_run(const float *gl, int p, int H, float
     const float fi = (float)(8 * i);
     float e[8];
     if constexpr (decltype(form)::value) {
-      // outwards from the middle, so that no factor is raised far: E_(k+1) = E_k U_k
-      // and E_(k-1) = E_k D_k, both ratios falling by C per step
-      const float tm = __builtin_fmaf(fi, a, tc);
-      e[4] = aexp2(-(tm * tm));
-      float U = aexp2(-(__builtin_fmaf(2.f, tm, a) * a));
-      float D = aexp2(__builtin_fmaf(2.f, tm, -a) * a);
-#pragma unroll
-      for (int k = 5; k < 8; ++k) {
-        e[k] = e[k - 1] * U;
-        if (k < 7) U *= C;
-      }
-#pragma unroll
-      for (int k = 3; k >= 0; --k) {
-        e[k] = e[k + 1] * D;
-        if (k > 0) D *= C;
-      }
+      // outwards from k = 2 and k = 6, so that no ratio is raised above its square:
+      // E_(k+1) = E_k U_k and E_(k-1) = E_k D_k, both falling by C per step outwards
+      const float t2 = __builtin_fmaf(fi - 2.f, a, tc), t6 = __builtin_fmaf(fi + 2.f, a, tc);
+      e[2] = aexp2(-(t2 * t2));
+      e[6] = aexp2(-(t6 * t6));
+      const float U2 = aexp2(-(__builtin_fmaf(2.f, t2, a) * a));
+      const float D6 = aexp2(__builtin_fmaf(2.f, t6, -a) * a);
+      const float U6 = U2 * C4, D2 = D6 * C4;
+      e[3] = e[2] * U2;
+      e[1] = e[2] * D2;
+      e[0] = e[1] * (D2 * C);
+      e[7] = e[6] * U6;
+      e[5] = e[6] * D6;
+      e[4] = e[5] * (D6 * C);
     } else {
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -168,10 +176,14 @@ __device__ __forceinline__ void adjoint_run(const float *gl, int p, int H, float
       fold(i);
     }
   };
-  if (chain)
+  if (chain) {
     run(std::true_type{});
-  else
+    M0 *= kAdjChainMean;
+    M1 *= kAdjChainMean;
+    M2 *= kAdjChainMean;
+  } else {
     run(std::false_type{});
+  }
   const double ad = a, td = tc;
   S0 = M0;
   S1 = fma(ad, M1, td * M0);
@@ -273,28 +285,28 @@ __global__ __launch_bounds__(kAdjThreads) void tau_adjoint_kernel(
     const AdjSource s = adj_source(K, b.pivot, delta);
     double S0, S1, S2;
     if (windowed) {
-      const bool line = s.w > 0.f;
-      const float a = line ? K.dv * s.r : 0.f;
+      const bool line = s.w > 0.0;
+      const float a = line ? s.a : 0.f, r = (float)s.r;
       // the target nearest the centre, and the centre's distance from it: exact to
       // one rounding of a value below dv
       const float vs = line ? fminf(fmaxf(rintf(v * K.inv_dv), (float)-K.vpx), (float)K.vpx) : 0.f;
-      const float tc = line ? __builtin_fmaf(vs, K.dv, -v) * s.r : 0.f;
-      const float h = b.window_k * (float)kSqrtLog2e * K.inv_dv / s.r;  // k b / dv
+      const float tc = line ? __builtin_fmaf(vs, K.dv, -v) * r : 0.f;
+      const float h = b.window_k * (float)kSqrtLog2e * K.inv_dv / r;  // k b / dv
       const int Hl = line ? (int)fminf(h + 1.51f, (float)K.half) : 0;
       const int H = __builtin_amdgcn_readfirstlane(adj_wave_max(Hl));
       const bool wide = !(a <= kAdjMaxA) || !(2.f * a * a * ((float)H + 10.f) <= kAdjMaxExp);
       adjoint_run(gl, (j - j0) + RH + (int)vs, H, a, tc, !__any(wide), S0, S1, S2);
     } else {
-      adjoint_full(K, g + off, gl, j, v, s.r, S0, S1, S2);
+      adjoint_full(K, g + off, gl, j, v, (float)s.r, S0, S1, S2);
     }
     if (j < j_end) {
       float gd = 0.f, gv = 0.f;
-      if (s.w > 0.f) {
+      if (s.w > 0.0) {
         // t = x sqrt(log2 e) and 1/b = r / sqrt(log2 e); Q = S2 - 1.2 S0 cancels
         // where x^2 ~ 1.2: formed in FP64
         const double w = s.w;
         const double Q = w * (S2 * (1.0 / kLog2e) - 1.2 * S0);
-        gv = (float)(2.0 * w * S1 * (double)s.r * (1.0 / kLog2e));
+        gv = (float)(2.0 * w * S1 * s.r * (1.0 / kLog2e));
         const double below = (delta <= b.pivot) ? (double)K.gm1 : 0.0;
         gd = (float)(fma(below, Q, 2.0 * w * S0) * adj_rcp((double)delta));
         q_T0 += Q;
