@@ -35,8 +35,8 @@
 // one workgroup per tile, gathering by a merge walk over the bins in memory.
 //
 // 4096 skewers of 4096 pixels at 2 km/s (FWHM 7, bins of 3.08 km/s; 222 MB moved) and
-// at 18.3 km/s (FWHM 224, bins of 64 km/s), forward and backward together: 196 and
-// 199 -> 154 and 162 us, where a workgroup per skewer with tiles of 2048 waited at
+// at 18.3 km/s (FWHM 224, bins of 64 km/s), forward and backward together: 195 and
+// 198 -> 147 and 157 us, where a workgroup per skewer with tiles of 2048 waited at
 // five barriers per tile and left a third of its waves without outputs in the last
 // one.  Vector issue takes about half of that, the traffic a quarter; the FP64
 // windows hold the kernels to four waves per SIMD (at five they spill: 94 against 88
@@ -1195,18 +1195,18 @@ instrument_backward_skewer_kernel(InsArgs a, const int2 *__restrict__ items, int
 // Parts of a skewer, a wave each, 1, 2 or 4 so that a workgroup holds whole skewers:
 // four up to 2047 skewers, which otherwise leave waves' places empty, fewer beyond, as
 // each part reads the skewer's constants and forms its taps.  4096 skewers of 4096 at
-// 2 km/s, forward and backward: one part 84.9 and 80.7, two 86.1 and 82.2, four 97.3
-// and 92.8 us; two up to 8191, so that the last round of waves is never a whole
-// skewer each.  One for boxes of a few hundred pixels at most, whose skewers have one
-// piece (2000 of 200).
+// 2 km/s, forward and backward: one part 68.9 and 65.0, two 70.1 and 64.4, four 76.5
+// and 69.3 us (of 2047 50.3 and 44.2, 38.6 and 36.2, 41.7 and 38.0); two up to 8191,
+// so that the last round of waves is never a whole skewer each.  One for boxes of a few
+// hundred pixels at most, whose skewers have one piece (2000 of 200).
 int ins_parts(int64_t n_items, int64_t max_n) {
   if (n_items >= 8192 || (n_items >= 1024 && max_n < kInsTapBlock)) return 1;
   return n_items >= 2048 ? 2 : 4;
 }
 
 // Workgroups: one per skewer, which may take the workgroup, or as many as the waves'
-// slots fill where none can (by_waves: boxes whose taps and bins always fit a wave;
-// 20000 skewers of 300 pixels 49 us forward where the idle workgroups make it 61).
+// slots fill where none can (by_waves: boxes whose taps and bins always fit a wave).
+// The idle workgroups cost 20000 skewers of 300 pixels 12 of 62 us forward.
 unsigned ins_grid(int64_t n_items, int parts, bool by_waves) {
   return (unsigned)(by_waves ? (n_items * parts + kInsWaves - 1) / kInsWaves : n_items);
 }

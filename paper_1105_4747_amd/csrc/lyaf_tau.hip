@@ -630,10 +630,10 @@ __device__ __forceinline__ void tau_skew_tile(const Batch &b, const int2 item,
   // the round.  The window bounds of every group of positions (highest last and
   // lowest first pixel, kept as biased 16-bit highest values) meet in a DPP
   // reduction over the lanes that hold them.  About 50 operations a position, a
-  // tile staging 1.2 (M = 8) to 1.3 positions per target, beside the walk's 30 a
-  // step (M = 8; one more with the clamp): with 100, by branches and IEEE minima, a
-  // plan of 4096 x 4096 pixels took 356 us, now 334, the ragged 20000-skewer one
-  // 1.742 ms, now 1.726, the 512 x 512 x 4096 box 19.58, now 19.23.
+  // tile staging 1.2 (M = 8) to 1.3 positions per target, beside the walk's 32 a
+  // step with its block sums (M = 8): with 100, by branches and IEEE minima, a plan of
+  // 4096 x 4096 pixels took 356 us, now 336, the ragged 20000-skewer one 1.784 ms, now
+  // 1.773, the 512 x 512 x 4096 box 18.98, now 18.61.
   constexpr int SIT = 8;  // positions per thread per round of reads
   constexpr int G = SH::kGroup;
   const int e_lo = i0 - RH;
