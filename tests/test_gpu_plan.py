@@ -147,6 +147,25 @@ def test_tune_cache_rejects_entries_of_another_device_or_shape(tmp_path, monkeyp
     p3.close()
 
 
+def test_tune_cache_entries_saved_before_stay_in_use(tmp_path, monkeypatch):
+    """A tuning file of an earlier library: its entry, under the key of the v3 shapes, is
+    used, and the plan neither tunes again nor takes another shape."""
+    import torch
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("LYAF_TUNE_CACHE", str(cache))
+    w = ragged_mix(seed=53)
+    d = OnDevice(w)
+    prop = torch.cuda.get_device_properties(0)
+    head = (f"v3|{prop.gcnArchName.replace(':', '_')}|cu{prop.multi_processor_count}"
+            f"|S2^{round(np.log2(w.n_skewers))}|N2^{round(np.log2(w.n_pix / w.n_skewers))}")
+    cache.write_text("".join(f"{head}|R2^{r}|k6 3 0 1.0\n" for r in range(13)))
+    p, ts, F, A = _plan(w, d, autotune=True)
+    info = p.describe()
+    print(f"case: saved tune entry {info['key']}", flush=True)
+    assert info["from_cache"] and info["shape"] == 3 and info["persistent_grid"] == 0
+    p.close()
+
+
 def test_tuner_choice_follows_its_timings(tmp_path, monkeypatch):
     """The tuner keeps the fastest one-workgroup-per-item launch unless the
     persistent launch is faster by more than 2 %; every candidate is the
