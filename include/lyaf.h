@@ -354,9 +354,10 @@ typedef struct {
  *     shell's mode count, mean |k|, mean P_true and mean P_box (0 for empty
  *     shells).
  * The library keeps a workspace of 16 n_lines (n/2+1) + 8 n^2 bytes and a few
- * MB of shell partials; sight-lines beyond what its fused kernel holds (about
- * 7000, or 30 of one sy) take 16 n R (n/2+1) bytes more, R the number of
- * distinct sy values (about 8.6 GB at n = 1024 with every row in use).
+ * MB of shell partials; few sight-lines (under 192, or 48 on grids of 2048; none
+ * on 1024) and more than its fused kernel holds (about 7000, or 30 of one sy)
+ * take 16 n R (n/2+1) bytes more, R the number of distinct sy values (about
+ * 8.6 GB at n = 1024 with every row in use).
  * Errors: EINVAL (host checks above; n_lines >= 1), EDEVICE, ENOMEM. */
 int lyaf_flux_power_3d(const lyaf_power3d_params *pp, int64_t n_lines, const float *F,
                        const int32_t *sx, const int32_t *sy, const double *weights,

@@ -1036,10 +1036,13 @@ int lyaf_flux_power_3d(const lyaf_power3d_params *pp, int64_t n_lines, const flo
   HostFieldPlan *hp = nullptr;
   if ((rc = ensure_field_plan(ws, n, n_lines, sx, sy, &hp))) return rc;
   if ((rc = ensure_twiddles(ws, st))) return rc;
-  if ((rc = ensure_slots(ws, hp, (int)n, false))) return rc;
-  // the fused kernel whenever the sight-lines fit its registers; a crowded
+  // the fused kernel where it pays and the sight-lines fit its registers; a crowded
   // plane (over about 7000 sight-lines, or one very long row) goes through D1
-  bool modes = hp->slots[0] > 0;
+  bool modes = p3d_modes_pay((int)n, n_lines);
+  if (modes) {
+    if ((rc = ensure_slots(ws, hp, (int)n, false))) return rc;
+    modes = hp->slots[0] > 0;
+  }
   const int64_t H = n / 2 + 1;
   const int nb = p3d_shell_bins((int)n, (int)pp->n_bins);
   int geom_grid = 0, grid = 0;

@@ -274,6 +274,8 @@ struct P3dArgs {
   double *counts, *k_mean, *p_true, *p_box;  // device [n_bins] outputs
   const double2 *twiddle;  // the shared FFT table
 };
+// Whether the fused mode kernel is the faster one for n_lines sight-lines.
+bool p3d_modes_pay(int n, int64_t n_lines);
 int p3d_shell_bins(int n, int n_bins);  // shells kept in LDS
 int p3d_y_columns(int n);               // mz per item of the y transform
 // Sets the kernels' LDS limits once per device; *geom_grid: workgroups of the

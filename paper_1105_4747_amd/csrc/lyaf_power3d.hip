@@ -30,7 +30,8 @@
 //                    with the sight-lines' transforms in registers (no
 //                    intermediate).  The next two kernels take what does not
 //                    fit them (over about 7000 sight-lines, or a row of more
-//                    than 30), through D1 in memory;
+//                    than 30), and few sight-lines (p3d_modes_pay), through D1
+//                    in memory;
 //   p3d_x_kernel     one workgroup per (row y in use, 64 consecutive mz):
 //                    D1(mx, y, mz) = sum_{s in row y} w_s G_s(mz) e^{-2 pi i mx x_s / n}
 //                    for every mx (a direct sum over the row's few sight-lines);
@@ -602,6 +603,19 @@ int p3d_shell_bins(int n, int n_bins) {
 // mz columns per p3d_y item: the largest power of two (at most 16) whose
 // n C complex doubles fit kYCap and, with the shell sums of the largest
 // shell count, the LDS of one workgroup.
+// The fused kernel's time hardly depends on the number of sight-lines, D1's does, and
+// new columns cost the fused kernel's table, 20 to 70 us of host time.  Calls with the
+// same columns and with new ones, through D1 and fused, us: n = 32 31 and 26, 65 and 85
+// with 16 sight-lines, 60 and 29, 90 and 95 with 300; 128 47 and 44, 84 and 112 (16), 76
+// and 53, 117 and 127 (300); 256 130 and 123, 166 and 208 (128), 143 and 128, 184 and 217
+// (256), 185 and 153, 248 and 264 (1000); 512 597 and 591, 630 and 694 (128), 698 and
+// 592, 732 and 697 (200); 1024 4360 and 3468 with one; 2048 39.6 and 40.5 ms with 30, 40.8
+// and 40.4 with 45.
+bool p3d_modes_pay(int n, int64_t n_lines) {
+  if (n >= 1024) return n == 1024 || n_lines >= 48;
+  return n >= 32 && n_lines >= 192;
+}
+
 int p3d_y_columns(int n) {
   const size_t bins = 2 * sizeof(double) * (size_t)p3d_shell_bins(n, INT32_MAX);
   int C = 16;

@@ -174,3 +174,40 @@ def test_largest_grid_totals(S):
     tot = float(np.sum(cnt * pb))
     assert abs(tot / want - 1) <= 1e-11
     assert abs(float(np.sum(cnt * pt)) + L ** 2 * S * 0.4 / n) <= 1e-10 * tot
+
+
+@pytest.mark.parametrize("rows", [(14,) * 14, (15, 1, 14) + (3,) * 60, (30, 30, 2) + (5,) * 30,
+                                  (31,) + (3,) * 60], ids=lambda r: f"{len(r)}x{max(r)}")
+def test_row_sizes_around_the_slots_of_the_fused_kernel(rows):
+    """The same row sizes among enough sight-lines (192) for the fused kernel to take
+    them on a small grid; 31 in one row go through the stored intermediate."""
+    n = 64
+    rng = np.random.default_rng(sum(rows))
+    sy = np.repeat(rng.permutation(n)[:len(rows)], rows)
+    assert sy.size >= 192
+    _check(n, 0, seed=len(rows), weights=True, p_noise=0.3,
+           cols=(rng.integers(0, n, sy.size), sy))
+
+
+@pytest.mark.parametrize("n,S", [(16, 200), (32, 191), (32, 192), (256, 192)])
+def test_the_fewest_sight_lines_of_the_fused_kernel(n, S):
+    """The fewest that the fused kernel takes on small grids, one less, and the largest
+    grid that it leaves to the others (through the stored intermediate)."""
+    _check(n, S, seed=S, weights=True, p_noise=0.2)
+
+
+@pytest.mark.parametrize("n,S", [(512, 191), (512, 192), (1024, 1), (2048, 47), (2048, 48)])
+def test_the_fewest_sight_lines_on_large_grids(n, S):
+    """The same by the totals, to the bars of the 1024 workload."""
+    L = 500.0
+    rng = np.random.default_rng(n + S)
+    c = rng.choice(n * n, S, replace=False)
+    F = _flux(S, n, S)
+    nb = int(math.floor(math.sqrt(3) * n / 2)) + 1
+    print(f"power3d: n={n} S={S}", flush=True)
+    cnt, _, pt, pb = _run(F, 0.7, c // n, c % n, n, L, nb, p_noise=0.4)
+    assert cnt.sum() == n ** 3
+    delta = F.astype(np.float64) / 0.7 - 1.0
+    tot = float(np.sum(cnt * pb))
+    assert abs(tot / (L ** 3 / n ** 3 * float(np.sum(delta * delta))) - 1) <= 1e-11
+    assert abs(float(np.sum(cnt * pt)) + L ** 2 * S * 0.4 / n) <= 1e-10 * tot
