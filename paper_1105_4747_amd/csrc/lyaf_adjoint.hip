@@ -21,8 +21,10 @@
 // targets into FP64 moments in m, from which
 //   sum g E t = a M1 + t_c M0,  sum g E t^2 = a^2 M2 + 2 a t_c M1 + t_c^2 M0
 // (M1 is signed and cancels across the line centre).  A wave with a line too
-// narrow for the recurrence evaluates every exp2.  Short or wide skewers sum
-// over every target with the minimal image chosen per pair.  The per-skewer
+// narrow for the recurrence evaluates every exp2, over its window in steps of four
+// targets (4096 skewers of 1024 pixels of 9 km/s, a backward pass: 67 us, and 73 in
+// blocks of eight about the centre; 59 and 65 at 18 km/s, 84 and 91 at 5).  Short or
+// wide skewers sum over every target with the minimal image chosen per pair.  The per-skewer
 // T0/gamma terms are summed in FP64 per workgroup and then per skewer in a fixed
 // order.  Bound by VALU issue: 4096 skewers of 2048 pixels at 2 km/s, forward and
 // backward, 501 us; 480 with a recurrence outwards from the middle alone (three exp2, its
@@ -101,38 +103,30 @@ __device__ __forceinline__ AdjSource adj_source(const SkewerConst &K, float pivo
 // then taken about the centre itself: a narrow line's M1 and M2 are not
 // differences of moments about a far target.
 __device__ __forceinline__ void adjoint_run(const float *gl, int p, int H, float a, float tc,
-                                            bool chain, double &S0, double &S1, double &S2) {
+                                            double &S0, double &S1, double &S2) {
   double M0 = 0.0, M1 = 0.0, M2 = 0.0;
   const int left = (H + 3) >> 3, right = (H + 4) >> 3;  // blocks beside the central one
   const float C = aexp2(-2.f * a * a), C4 = aexp2(-8.f * a * a);
   float B0, B1, B2;  // moments about the first block's middle, up to two blocks
   // the eight targets around m = 8 i, added to the moments about 8 (i - O)
-  const auto block = [&](auto form, auto O, int i) {
+  const auto block = [&](auto O, int i) {
     const float *g8 = gl + p + 8 * i - 4;
     const float fi = (float)(8 * i);
     float e[8];
-    if constexpr (decltype(form)::value) {
-      // outwards from k = 2 and k = 6, so that no ratio is raised above its square:
-      // E_(k+1) = E_k U_k and E_(k-1) = E_k D_k, both falling by C per step outwards
-      const float t2 = __builtin_fmaf(fi - 2.f, a, tc), t6 = __builtin_fmaf(fi + 2.f, a, tc);
-      e[2] = aexp2(-(t2 * t2));
-      e[6] = aexp2(-(t6 * t6));
-      const float U2 = aexp2(-(__builtin_fmaf(2.f, t2, a) * a));
-      const float D6 = aexp2(__builtin_fmaf(2.f, t6, -a) * a);
-      const float U6 = U2 * C4, D2 = D6 * C4;
-      e[3] = e[2] * U2;
-      e[1] = e[2] * D2;
-      e[0] = e[1] * (D2 * C);
-      e[7] = e[6] * U6;
-      e[5] = e[6] * D6;
-      e[4] = e[5] * (D6 * C);
-    } else {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const float t = __builtin_fmaf(fi + (float)(k - 4), a, tc);
-        e[k] = aexp2(-(t * t));
-      }
-    }
+    // outwards from k = 2 and k = 6, so that no ratio is raised above its square:
+    // E_(k+1) = E_k U_k and E_(k-1) = E_k D_k, both falling by C per step outwards
+    const float t2 = __builtin_fmaf(fi - 2.f, a, tc), t6 = __builtin_fmaf(fi + 2.f, a, tc);
+    e[2] = aexp2(-(t2 * t2));
+    e[6] = aexp2(-(t6 * t6));
+    const float U2 = aexp2(-(__builtin_fmaf(2.f, t2, a) * a));
+    const float D6 = aexp2(__builtin_fmaf(2.f, t6, -a) * a);
+    const float U6 = U2 * C4, D2 = D6 * C4;
+    e[3] = e[2] * U2;
+    e[1] = e[2] * D2;
+    e[0] = e[1] * (D2 * C);
+    e[7] = e[6] * U6;
+    e[5] = e[6] * D6;
+    e[4] = e[5] * (D6 * C);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       const float gE = g8[k] * e[k];
@@ -159,35 +153,58 @@ __device__ __forceinline__ void adjoint_run(const float *gl, int p, int H, float
   };
   const std::integral_constant<int, 0> first;
   const std::integral_constant<int, 1> second;
-  const auto run = [&](auto form) {
-    int i = -left;
-    if (left & 1) {  // the central block is then the first of a pair
-      block(form, first, i);
-      fold(i);
-      ++i;
-    }
-    for (; i < right; i += 2) {
-      block(form, first, i);
-      block(form, second, i + 1);
-      fold(i);
-    }
-    if (i == right) {
-      block(form, first, i);
-      fold(i);
-    }
-  };
-  if (chain) {
-    run(std::true_type{});
-    M0 *= kAdjChainMean;
-    M1 *= kAdjChainMean;
-    M2 *= kAdjChainMean;
-  } else {
-    run(std::false_type{});
+  int i = -left;
+  if (left & 1) {  // the central block is then the first of a pair
+    block(first, i);
+    fold(i);
+    ++i;
   }
+  for (; i < right; i += 2) {
+    block(first, i);
+    block(second, i + 1);
+    fold(i);
+  }
+  if (i == right) {
+    block(first, i);
+    fold(i);
+  }
+  M0 *= kAdjChainMean;
+  M1 *= kAdjChainMean;
+  M2 *= kAdjChainMean;
   const double ad = a, td = tc;
   S0 = M0;
   S1 = fma(ad, M1, td * M0);
   S2 = fma(ad * ad, M2, td * fma(2.0 * ad, M1, td * M0));
+}
+
+// The same with an exp2 per pair, for waves with a line too narrow for the recurrence:
+// the targets m = -H .. H, four to a step, as the whole window may be no wider than a
+// block of eight (5 to 12 targets each side between 18 and 8 km/s); sums of 16 folded
+// into FP64.
+__device__ __forceinline__ void adjoint_pairs(const float *gl, int p, int H, float a, float tc,
+                                              double &S0, double &S1, double &S2) {
+  S0 = S1 = S2 = 0.0;
+  const float *gp = gl + p - H;
+  const int steps = (2 * H + 4) >> 2;
+  for (int st = 0; st < steps; st += 4) {
+    float s0 = 0.f, s1 = 0.f, s2 = 0.f;
+    const int end = min(st + 4, steps);
+    for (int q = st; q < end; ++q) {
+      const float t0 = __builtin_fmaf((float)(4 * q - H), a, tc);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float t = k == 0 ? t0 : __builtin_fmaf((float)k, a, t0);
+        const float tt = t * t;
+        const float gE = gp[4 * q + k] * aexp2(-tt);
+        s0 += gE;
+        s1 = __builtin_fmaf(gE, t, s1);
+        s2 = __builtin_fmaf(gE, tt, s2);
+      }
+    }
+    S0 += (double)s0;
+    S1 += (double)s1;
+    S2 += (double)s2;
+  }
 }
 
 // The same over every target, the minimal image chosen per pair; gl is filled
@@ -292,10 +309,14 @@ __global__ __launch_bounds__(kAdjThreads) void tau_adjoint_kernel(
       const float vs = line ? fminf(fmaxf(rintf(v * K.inv_dv), (float)-K.vpx), (float)K.vpx) : 0.f;
       const float tc = line ? __builtin_fmaf(vs, K.dv, -v) * r : 0.f;
       const float h = b.window_k * (float)kSqrtLog2e * K.inv_dv / r;  // k b / dv
-      const int Hl = line ? (int)fminf(h + 1.51f, (float)K.half) : 0;
+      const int Hl = line ? (int)fminf(h + 0.51f, (float)K.half) : 0;
       const int H = __builtin_amdgcn_readfirstlane(adj_wave_max(Hl));
-      const bool wide = !(a <= kAdjMaxA) || !(2.f * a * a * ((float)H + 10.f) <= kAdjMaxExp);
-      adjoint_run(gl, (j - j0) + RH + (int)vs, H, a, tc, !__any(wide), S0, S1, S2);
+      const bool wide = !(a <= kAdjMaxA) || !(2.f * a * a * ((float)H + 11.f) <= kAdjMaxExp);
+      const int at = (j - j0) + RH + (int)vs;
+      if (__any(wide))
+        adjoint_pairs(gl, at, H, a, tc, S0, S1, S2);
+      else
+        adjoint_run(gl, at, min(H + 1, K.half), a, tc, S0, S1, S2);
     } else {
       adjoint_full(K, g + off, gl, j, v, (float)s.r, S0, S1, S2);
     }

@@ -119,6 +119,35 @@ def test_tau_backward_narrow_window_beside_a_large_velocity():
     assert (gd[:i - 50] == 0).all() and (gd[i + 51:] == 0).all()
 
 
+@pytest.mark.parametrize("dv,half,walked", [(40.0, 0, 4), (18.0, 1, 4), (9.0, 2, 8), (5.0, 5, 12),
+                                            (3.5, 7, 16), (3.3, 7, 20)])
+def test_tau_backward_walks_its_window_on_coarse_pixels(dv, half, walked):
+    """Lines too narrow for the recurrence take the targets of their window, half window
+    ``half`` pixels (2 b here), rounded to steps of four and no further: a cotangent on
+    one target reaches that many sources (at 2 to 4 b every E is above exp(-40)).  The
+    sums over the window are the oracle's (the terms beyond 2 b left out on both sides)."""
+    import torch
+    from paper_1105_4747_amd import lyaf as L
+    n, i = 700, 350
+    w = fields.small_workload(n_skewers=1, n_pix=n, seed=48, dv=dv, gamma=1.0, T0=1.0e4,
+                              window_k=2.0)
+    w.vpec[:] = 0.0
+    d = OnDevice(w)
+    g = np.zeros(n, np.float32)
+    g[i] = 1.0
+    gd, gv = torch.empty_like(d.delta), torch.empty_like(d.vpec)
+    print(f"case: adjoint window_k=2 dv={dv}", flush=True)
+    L.tau_backward(d.delta, d.vpec, d.dv, d.T0, d.gamma, d.offsets, to_dev(g), gd, gv,
+                   window_k=2.0)
+    gd = gd.cpu().numpy()
+    at = np.nonzero(gd)[0]
+    assert at.min() <= i - half and at.max() >= i + half
+    assert len(at) <= walked and len(at) == at.max() - at.min() + 1
+    rd, _, _, _ = O.tau_grad(w.delta, w.vpec, w.dv, w.T0, w.gamma, g.astype(np.float64),
+                             offsets=w.offsets)
+    assert_grad_close(gd[at], rd[at], "dL/dDelta")
+
+
 @pytest.mark.parametrize("n_pix,dv,T0,gamma,bar", [(1000, 1.0, 2.4e4, 1.2, 3.5e-8),
                                                    (1500, 2.0, 2.2e4, 1.5, 1.6e-8)])
 def test_tau_backward_has_no_common_error(n_pix, dv, T0, gamma, bar):
