@@ -73,30 +73,19 @@ __device__ __forceinline__ void flag_bad_delta(const Batch &b, bool bad) {
 }
 __device__ __forceinline__ bool bad_delta(float d) { return !(d >= 0.f) || !isfinite(d); }
 
-template <typename T>
-__device__ __forceinline__ T block_reduce_max(T v, T *sh) {
-  for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m));
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) sh[w] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 1; k < (int)(blockDim.x >> 6); ++k) v = fmaxf(v, sh[k]);
-    sh[0] = v;
-  }
-  __syncthreads();
-  return sh[0];
-}
-
 // ---------------------------------------------------------------------------
-// Four waves read, the fifth forms the constants (logarithms and exponentials in
+// Three waves read, the fourth forms the constants (logarithms and exponentials in
 // FP64, as long a chain as the reads) meanwhile.  4096 x 4096 pixels: 19.0 us with
-// the constants in every thread by pow, 14.4 us so (67 MB, 4.7 TB/s: the reads).
+// the constants in every thread by pow, 16.4 with four readers and a fifth wave (six
+// workgroups to a compute unit instead of eight), 15.3 so (67 MB, 4.4 TB/s: the reads);
+// 20000 x 300: 57.5, 47.3 and 32.7; 4096 x 512 at gamma < 1, where Delta is read too:
+// 11.4, 15.9 and 11.8.
 constexpr double kTempRef07 = 630.95734448019325;  // (1e4 K)^0.7
-constexpr int kReachReaders = 256;
+constexpr int kReachReaders = 192;
 constexpr int kSkewMargin = 12;            // staged sources beyond the reach
 
 __global__ __launch_bounds__(kReachReaders + kWave) void reach_kernel(Batch b) {
-  __shared__ float shm[8];
+  __shared__ float shm[3 * (kReachReaders / kWave)];
   __shared__ int shbad[1];
   const int64_t s = blockIdx.x;
   const int64_t off = b.offsets[s];
@@ -112,6 +101,8 @@ __global__ __launch_bounds__(kReachReaders + kWave) void reach_kernel(Batch b) {
   K.gm1 = bad ? 0.f : gm - 1.f;
   K.inv_dv = (float)(1.0 / dvd);
   const bool reader = threadIdx.x < kReachReaders;
+  // whether the largest |v| (mr) gives the reach, or every source's own b is needed
+  const bool by_v = !bad && K.gm1 >= 0.f && isfinite(b.pivot);
   float b_piv = 0.f;  // the Doppler parameter at the pivot
   if (!reader) {
     const double R = kSqrtLog2e / (kBeta * sqrt(T0d));
@@ -122,14 +113,13 @@ __global__ __launch_bounds__(kReachReaders + kWave) void reach_kernel(Batch b) {
                   exp2(-1.2 * log2(T0d)) * ((double)K.R / R));
     K.dv = (float)dvd;
     K.n = n;
-    if (isfinite(b.pivot))
+    if (by_v)
       b_piv = (float)(kBeta * sqrt(T0d) * exp2(0.5 * (double)K.gm1 * log2((double)b.pivot)) *
                       (1.0 + 1e-6));
   }
   float mr = 0.f;
   float mv = 0.f, mb = 0.f;  // largest |v| and b
-  bool by_v = true;          // mr is the largest |v|, else the largest reach in pixels
-  if (!bad && K.gm1 >= 0.f && isfinite(b.pivot)) {
+  if (by_v) {
     if (reader) {
       // T rises with Delta up to the pivot, so b <= beta sqrt(T0 pivot^(gamma-1))
       // for every source: only the velocities are read.  The kernels that stage
@@ -171,28 +161,52 @@ __global__ __launch_bounds__(kReachReaders + kWave) void reach_kernel(Batch b) {
       for (int t = head + 4 * n4 + (int)threadIdx.x; t < n; t += bd) one(vp[t]);
     }
   } else {
-    by_v = false;
-    for (int j = threadIdx.x; reader && j < n; j += kReachReaders) {
-      const float d = b.delta[off + j], v = b.vpec[off + j];
-      if (!(d >= 0.f) || !isfinite(d) || !isfinite(v)) bad = 1;
-      if (d > 0.f) {
-        const float D = fmaxf(fminf(d, b.pivot), 1e-30f);
-        const float bj = K.B * fexp2(0.5f * (K.gm1 * flog2(D)));
-        mr = fmaxf(mr, (fabsf(v) + b.window_k * bj) * K.inv_dv);
-        mv = fmaxf(mv, fabsf(v));
-        mb = fmaxf(mb, bj);
+    // four pixels ahead per thread (4096 x 2048 pixels: 25 us one by one, 23 so)
+    constexpr int kAhead = 4;
+    for (int j = threadIdx.x; reader && j < n; j += kAhead * kReachReaders) {
+      float dd[kAhead], vv[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int q = j + u * kReachReaders;
+        dd[u] = q < n ? b.delta[off + q] : 0.f;
+        vv[u] = q < n ? b.vpec[off + q] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const float d = dd[u], v = vv[u];
+        if (!(d >= 0.f) || !isfinite(d) || !isfinite(v)) bad = 1;
+        if (d > 0.f) {
+          const float D = fmaxf(fminf(d, b.pivot), 1e-30f);
+          const float bj = K.B * fexp2(0.5f * (K.gm1 * flog2(D)));
+          mr = fmaxf(mr, (fabsf(v) + b.window_k * bj) * K.inv_dv);
+          mv = fmaxf(mv, fabsf(v));
+          mb = fmaxf(mb, bj);
+        }
       }
     }
   }
   if (bad) atomicOr(shbad, 1);
-  mr = block_reduce_max(mr, shm);
+  // the readers' highest values meet in the wave that holds the constants (the second
+  // and third only where Delta was read: the three in turn took up to 3 us)
+  const auto wave_highest = [&](float x, int at) {
+    for (int m = 32; m >= 1; m >>= 1) x = fmaxf(x, __shfl_xor(x, m));
+    if ((threadIdx.x & 63) == 0 && reader) shm[at + (threadIdx.x >> 6)] = x;
+  };
+  constexpr int W = kReachReaders / kWave;
+  wave_highest(mr, 0);
   if (!by_v) {
-    __syncthreads();  // shm is free again
-    mv = block_reduce_max(mv, shm);
-    __syncthreads();
-    mb = block_reduce_max(mb, shm);
+    wave_highest(mv, W);
+    wave_highest(mb, 2 * W);
   }
+  __syncthreads();
   if (threadIdx.x == kReachReaders) {
+    for (int k = 0; k < W; ++k) {
+      mr = fmaxf(mr, shm[k]);
+      if (!by_v) {
+        mv = fmaxf(mv, shm[W + k]);
+        mb = fmaxf(mb, shm[2 * W + k]);
+      }
+    }
     if (by_v) {
       mv = mr;
       mb = b_piv;
