@@ -23,14 +23,15 @@
 // (M1 is signed and cancels across the line centre).  A wave with a line too
 // narrow for the recurrence evaluates every exp2, over its window in steps of four
 // targets (4096 skewers of 1024 pixels of 9 km/s, a backward pass: 67 us, and 73 in
-// blocks of eight about the centre; 59 and 65 at 18 km/s, 84 and 91 at 5).  Short or
+// blocks of eight about the centre; 59 and 65 at 18 km/s, 84 and 91 at 5; with the
+// reach pass and the kernel's eight waves of now 61, 52 and 76).  Short or
 // wide skewers sum over every target with the minimal image chosen per pair.  The per-skewer
 // T0/gamma terms are summed in FP64 per workgroup and then per skewer in a fixed
 // order.  Bound by VALU issue: 4096 skewers of 2048 pixels at 2 km/s, forward and
 // backward, 501 us; 480 with a recurrence outwards from the middle alone (three exp2, its
 // kernel 220 us where the Kahan-folded direct form's took 246), which is not kept for
-// its errors.  Errors against 64 bits over 16 seeds at six settings, relative to the
-// direct form's: velocity 0.80-0.94, density 0.82-0.97, gamma 0.92-1.00, T0 0.96-1.02;
+// its errors.  Errors against 64 bits over 16 seeds at twelve settings of 1 to 18 km/s, relative
+// to the direct form's: velocity 0.80-0.95, density 0.82-0.93, gamma 0.92-1.00, T0 0.96-1.02;
 // from the middle alone gamma 1.02-1.15 and T0 1.01-1.06, as its E kept the mean error
 // of 4.75 exp2.
 #include <math.h>
@@ -91,8 +92,10 @@ __device__ __forceinline__ AdjSource adj_source(const SkewerConst &K, float pivo
     s.r = adj_scaled_exp2(K.R, kTempExpR * x);
     const double a = (double)K.dv * s.r;
     s.a = (float)a;
-    s.w = (double)delta * (double)delta * adj_scaled_exp2(K.W, kTempExpW * x) * (double)s.a *
-          adj_rcp(a);
+    // w a_f / a: the rounding is below 2^-24 of a, so its ratio needs no more than FP32
+    const float corr = (float)((double)s.a - a) * __builtin_amdgcn_rcpf(s.a);
+    const double w = (double)delta * (double)delta * adj_scaled_exp2(K.W, kTempExpW * x);
+    s.w = fma(w, (double)corr, w);
   }
   return s;
 }
@@ -249,9 +252,13 @@ __device__ void adjoint_full(const SkewerConst &K, const float *__restrict__ g, 
   }
 }
 
-__global__ __launch_bounds__(kAdjThreads) void tau_adjoint_kernel(
-    Batch b, const int2 *__restrict__ items, const float *__restrict__ g,
-    float *__restrict__ gdelta, float *__restrict__ gvpec, double *__restrict__ gpart) {
+// Eight waves per SIMD (64 VGPRs, none spilled): few targets a line leave a wave waiting
+// on its loads (78 VGPRs, 4096 x 1024 pixels of 18 km/s: 45.9 us, 43.7 so; of 3 km/s
+// 89.8 and 85.1; 4096 x 2048 of 2 km/s 201 and 196).
+__global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(8))) void
+tau_adjoint_kernel(Batch b, const int2 *__restrict__ items, const float *__restrict__ g,
+                   float *__restrict__ gdelta, float *__restrict__ gvpec,
+                   double *__restrict__ gpart) {
   __shared__ float gl[kAdjChunk];
   __shared__ double shd[8];
   const int2 item = items[blockIdx.x];
