@@ -174,12 +174,13 @@ def test_tau_recurrence_is_the_same_with_its_clamp(shape, a, RH, density):
 
 
 @pytest.mark.parametrize("gamma", [0.8, 1.4])
-@pytest.mark.parametrize("n", [767, 769, 1537, 3075])
+@pytest.mark.parametrize("n", [767, 769, 1537, 3075, 6149, 9221])
 def test_tau_reach_finds_one_fast_source_anywhere(n, gamma):
     """One source moving at 250 km/s among sources at rest, at the ends of the reach
     pass's rounds of reads and among the few pixels before and after them (skewers of odd
     lengths start off the 16-byte boundaries): its line is in place, 63 pixels away."""
-    at = [p for p in (0, 1, 191, 192, 767, 768, 1535, 1536, 3071, n - 2, n - 1) if p < n]
+    at = [p for p in (0, 1, 191, 192, 767, 768, 1535, 1536, 3071, 6143, 6144, n - 2, n - 1)
+          if p < n]
     w = fields.small_workload(n_skewers=len(at), n_pix=n, seed=49, dv=4.0, gamma=gamma,
                               sigma_lnD=0.5)
     w.vpec[:] = 0.0
