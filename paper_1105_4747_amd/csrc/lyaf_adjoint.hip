@@ -22,15 +22,13 @@
 //   sum g E t = a M1 + t_c M0,  sum g E t^2 = a^2 M2 + 2 a t_c M1 + t_c^2 M0
 // (M1 is signed and cancels across the line centre).  A wave with a line too
 // narrow for the recurrence evaluates every exp2, over its window in steps of four
-// targets (4096 skewers of 1024 pixels of 9 km/s, a backward pass: 67 us, and 73 in
-// blocks of eight about the centre; 59 and 65 at 18 km/s, 84 and 91 at 5; with the
-// reach pass and the kernel's eight waves of now 61, 52 and 76).  Short or
-// wide skewers sum over every target with the minimal image chosen per pair.  The per-skewer
-// T0/gamma terms are summed in FP64 per workgroup and then per skewer in a fixed
-// order.  Bound by VALU issue: 4096 skewers of 2048 pixels at 2 km/s, forward and
-// backward, 501 us; 480 with a recurrence outwards from the middle alone (three exp2, its
-// kernel 220 us where the Kahan-folded direct form's took 246), which is not kept for
-// its errors.  Errors against 64 bits over 16 seeds at twelve settings of 1 to 18 km/s, relative
+// targets (4096 skewers of 1024 pixels, a backward pass, with blocks of eight about the
+// centre and so: 73 and 67 us at 9 km/s, 65 and 59 at 18, 91 and 84 at 5; 61, 52 and
+// 76 with eight waves per SIMD and the present reach pass).  Short or wide skewers sum
+// over every target with the minimal image chosen per pair.  The per-skewer T0/gamma
+// terms are summed in FP64 per workgroup and then per skewer in a fixed order.  Bound by VALU issue: 4096 skewers of 2048 pixels at 2 km/s, forward and
+// backward, 474 us (546 with an exp2 per pair); 20 less with a recurrence outwards from the
+// middle alone (three exp2), which is not kept for its errors.  Errors against 64 bits over 16 seeds at twelve settings of 1 to 18 km/s, relative
 // to the direct form's: velocity 0.80-0.95, density 0.82-0.93, gamma 0.92-1.00, T0 0.96-1.02;
 // from the middle alone gamma 1.02-1.15 and T0 1.01-1.06, as its E kept the mean error
 // of 4.75 exp2.
